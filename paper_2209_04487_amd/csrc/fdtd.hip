@@ -38,20 +38,44 @@ __device__ __forceinline__ const T* prof(const FdArgs& a, size_t off_d, size_t o
 }
 
 // Launch geometry of both updates: blockIdx.y is the z plane, blockIdx.x a
-// run of 256 cells of that plane in x-fastest order (so the dispatch order is
-// the memory order), and the in-plane (i, j) come from 32-bit arithmetic.
+// run of 256 cells of that plane in x-fastest order, and the in-plane (i, j)
+// come from 32-bit arithmetic.
+//
+// The stencil is bound by the traffic beyond the XCDs' L2s: workgroups go to
+// the eight XCDs in turn, so runs in dispatch order put every cell's +-y and
+// +-z neighbours into other XCDs' L2s, which fetch those lines again.  With at
+// least kStripRuns runs per plane, XCD x therefore takes the x-th contiguous
+// eighth of every plane's runs (a strip of y rows, the same in all planes, the
+// number of runs padded to a multiple of eight): all XCDs still sweep the
+// planes together, and the neighbours of a strip hit the XCD's own L2.  The E
+// update takes the planes in descending order (REV), so that it begins with
+// the planes that the H update before it finished with, and the next H update
+// with the E update's last ones.  H + E pair, before -> strips -> both:
+// 60.6 -> 54.7 -> 50.3 us at 192x192x120 FP32 (6.6 TB/s of the two kernels'
+// 75 B per cell), 114 -> 100 -> 98.5 us in FP64, 145 -> 140 -> 136 us at
+// 256x256x160, 36.9 -> 28.9 -> 25.4 us at 150x131x97.  At 96x96x80 (36 runs)
+// and 37x41x33 (6 runs) the launches bound the pair and nothing moved; below
+// kStripRuns an eighth is less than two runs and the rows in dispatch order
+// stay as they were.
+//
+// Addresses are a uniform base per plane plus a 32-bit offset in the plane, so
+// that a load takes one offset register.
+constexpr unsigned kStripRuns = 16;
 struct CellIdx {
-  long idx;   // linear cell index
+  unsigned p;   // index in the plane
   int i, j, k;
 };
+template <bool REV>
 __device__ __forceinline__ bool cell_of_thread(const FdArgs& a, CellIdx& c) {
   const int plane = a.nx * a.ny;
-  const int p = static_cast<int>(blockIdx.x) * static_cast<int>(blockDim.x) + static_cast<int>(threadIdx.x);
+  int run = static_cast<int>(blockIdx.x);
+  if (gridDim.x >= kStripRuns) run = (run & 7) * static_cast<int>(gridDim.x >> 3) + (run >> 3);
+  const int p = run * static_cast<int>(blockDim.x) + static_cast<int>(threadIdx.x);
   if (p >= plane) return false;
-  c.k = static_cast<int>(blockIdx.y);
+  c.k = REV ? a.nz - 1 - static_cast<int>(blockIdx.y) : static_cast<int>(blockIdx.y);
   c.j = p / a.nx;
   c.i = p - c.j * a.nx;
-  c.idx = static_cast<long>(c.k) * plane + p;
+  c.p = static_cast<unsigned>(p);
   return true;
 }
 
@@ -91,23 +115,26 @@ struct MolTerm<double> {
 template <typename T>
 __global__ __launch_bounds__(256) void yee_h_kernel(FdArgs a) {
   CellIdx cl;
-  if (!cell_of_thread(a, cl)) return;
+  if (!cell_of_thread<false>(a, cl)) return;
   const int nx = a.nx, ny = a.ny, nz = a.nz;
-  const int i = cl.i, j = cl.j, k = cl.k;
-  const long idx = cl.idx;
-  const long sy = nx, sz = static_cast<long>(nx) * ny;
-  const long ip = (i + 1 == nx) ? idx - (nx - 1) : idx + 1;
-  const long jp = (j + 1 == ny) ? idx - (ny - 1) * sy : idx + sy;
+  const int k = cl.k;
+  const unsigned p = cl.p;
+  const long sz = static_cast<long>(nx) * ny, base = k * sz;
+  const unsigned ip = (cl.i + 1 == nx) ? p - (nx - 1) : p + 1;
+  const unsigned jp = (cl.j + 1 == ny) ? p - (ny - 1) * nx : p + nx;
   FdPtr<T> f = fd_ptrs<T>(a);
-  const T* __restrict__ Ex = f.Ex;
-  const T* __restrict__ Ey = f.Ey;
-  const T* __restrict__ Ez = f.Ez;
+  const T* __restrict__ Ex = f.Ex + base;
+  const T* __restrict__ Ey = f.Ey + base;
+  const T* __restrict__ Ez = f.Ez + base;
+  T* Hx = f.Hx + base;
+  T* Hy = f.Hy + base;
+  T* Hz = f.Hz + base;
   const bool below_top = k + 1 < nz;
-  const T ex = Ex[idx], ey = Ey[idx], ez = Ez[idx];
-  const T ex_kp = below_top ? Ex[idx + sz] : T(0);
-  const T ey_kp = below_top ? Ey[idx + sz] : T(0);
+  const T ex = Ex[p], ey = Ey[p], ez = Ez[p];
   const T ez_jp = Ez[jp], ez_ip = Ez[ip], ey_ip = Ey[ip], ex_jp = Ex[jp];
-  const T hx = f.Hx[idx], hy = f.Hy[idx], hz = f.Hz[idx];
+  const T hx = Hx[p], hy = Hy[p], hz = Hz[p];
+  const T ex_kp = below_top ? (Ex + sz)[p] : T(0);
+  const T ey_kp = below_top ? (Ey + sz)[p] : T(0);
   const T inv_dx = static_cast<T>(a.inv_dx);
   const T cH = static_cast<T>(a.cH);
 
@@ -124,20 +151,19 @@ __global__ __launch_bounds__(256) void yee_h_kernel(FdArgs a) {
     const T c = prof<T>(a, a.lay.aH, a.lay.aHf)[k];
     const T ki = prof<T>(a, a.lay.kH, a.lay.kHf)[k];
     const long np = 2L * a.npml * sz;
-    const long o = kk * sz + (idx - static_cast<long>(k) * sz);
-    T* psiHx = f.psi + 2 * np;
-    T* psiHy = f.psi + 3 * np;
-    const T p0 = psiHx[o], p1 = psiHy[o];
+    T* psiHx = f.psi + 2 * np + kk * sz;
+    T* psiHy = f.psi + 3 * np + kk * sz;
+    const T p0 = psiHx[p], p1 = psiHy[p];
     const T phx = b * p0 + c * dEy_dz;
     const T phy = b * p1 + c * dEx_dz;
-    psiHx[o] = phx;
-    psiHy[o] = phy;
+    psiHx[p] = phx;
+    psiHy[p] = phy;
     dEy_dz = dEy_dz * ki + phx;
     dEx_dz = dEx_dz * ki + phy;
   }
-  f.Hx[idx] = hx - cH * (dEz_dy - dEy_dz);
-  f.Hy[idx] = hy - cH * (dEx_dz - dEz_dx);
-  f.Hz[idx] = hz - cH * (dEy_dx - dEx_dy);
+  Hx[p] = hx - cH * (dEz_dy - dEy_dz);
+  Hy[p] = hy - cH * (dEx_dz - dEz_dx);
+  Hz[p] = hz - cH * (dEy_dx - dEx_dy);
 }
 
 // Drude current (centred form of Eq. (2)) and
@@ -147,38 +173,37 @@ __global__ __launch_bounds__(256) void yee_h_kernel(FdArgs a) {
 template <typename T>
 __global__ __launch_bounds__(256) void yee_e_kernel(FdArgs a) {
   CellIdx cl;
-  if (!cell_of_thread(a, cl)) return;
+  if (!cell_of_thread<true>(a, cl)) return;
   const int nx = a.nx, ny = a.ny, nz = a.nz;
-  const int i = cl.i, j = cl.j, k = cl.k;
-  const long idx = cl.idx;
-  const long n = static_cast<long>(nx) * ny * nz;
-  const long sy = nx, sz = static_cast<long>(nx) * ny;
-  const long im = (i == 0) ? idx + (nx - 1) : idx - 1;
-  const long jm = (j == 0) ? idx + (ny - 1) * sy : idx - sy;
+  const int k = cl.k;
+  const unsigned p = cl.p;
+  const long sz = static_cast<long>(nx) * ny, n = sz * nz, base = k * sz;
+  const unsigned im = (cl.i == 0) ? p + (nx - 1) : p - 1;
+  const unsigned jm = (cl.j == 0) ? p + (ny - 1) * nx : p - nx;
   FdPtr<T> f = fd_ptrs<T>(a);
-  const T* __restrict__ Hx = f.Hx;
-  const T* __restrict__ Hy = f.Hy;
-  const T* __restrict__ Hz = f.Hz;
-  const T hx = Hx[idx], hy = Hy[idx], hz = Hz[idx];
-  const T hx_km = (k > 0) ? Hx[idx - sz] : T(0);
-  const T hy_km = (k > 0) ? Hy[idx - sz] : T(0);
+  const T* __restrict__ Hx = f.Hx + base;
+  const T* __restrict__ Hy = f.Hy + base;
+  const T* __restrict__ Hz = f.Hz + base;
+  const T hx = Hx[p], hy = Hy[p], hz = Hz[p];
   const T hz_jm = Hz[jm], hz_im = Hz[im], hy_im = Hy[im], hx_jm = Hx[jm];
-  const uint8_t* mat = a.mat;
-  const int mc[3] = {mat[idx], mat[n + idx], mat[2 * n + idx]};
-  T* E[3] = {f.Ex, f.Ey, f.Ez};
-  T* JD[3] = {f.JDx, f.JDy, f.JDz};
+  const uint8_t* mat = a.mat + base;
+  const int mc[3] = {mat[p], (mat + n)[p], (mat + 2 * n)[p]};
+  T* E[3] = {f.Ex + base, f.Ey + base, f.Ez + base};
+  T* JD[3] = {f.JDx + base, f.JDy + base, f.JDz + base};
   T e0[3], jd0[3], hv[3];
 #pragma unroll
-  for (int c = 0; c < 3; ++c) e0[c] = E[c][idx];
+  for (int c = 0; c < 3; ++c) e0[c] = E[c][p];
+  const T hx_km = (k > 0) ? (Hx - sz)[p] : T(0);
+  const T hy_km = (k > 0) ? (Hy - sz)[p] : T(0);
 #pragma unroll
-  for (int c = 0; c < 3; ++c) jd0[c] = (mc[c] == a.metal_id) ? JD[c][idx] : T(0);
+  for (int c = 0; c < 3; ++c) jd0[c] = (mc[c] == a.metal_id) ? JD[c][p] : T(0);
   // the held molecular current, on the planes that hold occupied cells (k is
   // uniform over the workgroup)
   const bool in_held = k >= a.held_k0 && k < a.held_k0 + a.held_nk;
   const long hn = static_cast<long>(a.held_nk) * sz;
 #pragma unroll
   for (int c = 0; c < 3; ++c)
-    hv[c] = (in_held && c < a.held_nc) ? static_cast<const T*>(a.held)[c * hn + idx - a.held_k0 * sz] : T(0);
+    hv[c] = (in_held && c < a.held_nc) ? (static_cast<const T*>(a.held) + (c * hn + (k - a.held_k0) * sz))[p] : T(0);
   const T inv_dx = static_cast<T>(a.inv_dx);
 
   const T dHz_dy = (hz - hz_jm) * inv_dx;
@@ -194,14 +219,13 @@ __global__ __launch_bounds__(256) void yee_e_kernel(FdArgs a) {
     const T c = prof<T>(a, a.lay.aE, a.lay.aEf)[k];
     const T ki = prof<T>(a, a.lay.kE, a.lay.kEf)[k];
     const long np = 2L * a.npml * sz;
-    const long o = kk * sz + (idx - static_cast<long>(k) * sz);
-    T* psiEx = f.psi;
-    T* psiEy = f.psi + np;
-    const T p0 = psiEx[o], p1 = psiEy[o];
+    T* psiEx = f.psi + kk * sz;
+    T* psiEy = f.psi + np + kk * sz;
+    const T p0 = psiEx[p], p1 = psiEy[p];
     const T pex = b * p0 + c * dHy_dz;
     const T pey = b * p1 + c * dHx_dz;
-    psiEx[o] = pex;
-    psiEy[o] = pey;
+    psiEx[p] = pex;
+    psiEy[p] = pey;
     dHy_dz = dHy_dz * ki + pex;
     dHx_dz = dHx_dz * ki + pey;
   }
@@ -212,7 +236,7 @@ __global__ __launch_bounds__(256) void yee_e_kernel(FdArgs a) {
     T J = T(0);
     if (m == a.metal_id) {
       const T jd = static_cast<T>(a.alpha_d) * jd0[c] + static_cast<T>(a.beta_d) * e0[c];
-      JD[c][idx] = jd;
+      JD[c][p] = jd;
       J = jd;
     }
     if (c == 0 && k == a.src_k) J += static_cast<T>(a.src_term);
@@ -221,13 +245,15 @@ __global__ __launch_bounds__(256) void yee_e_kernel(FdArgs a) {
     if (c < 2 && k == 0) e1 = T(0);
     // the molecular current after the update, as the separate pass applies it
     if (in_held && c < a.held_nc) e1 = MolTerm<T>::apply(e1, ce, hv[c]);
-    E[c][idx] = e1;
+    E[c][p] = e1;
   }
 }
 
 static dim3 yee_grid(const FdArgs& a) {
   const long plane = static_cast<long>(a.nx) * a.ny;
-  return dim3(static_cast<unsigned>((plane + 255) / 256), static_cast<unsigned>(a.nz));
+  unsigned runs = static_cast<unsigned>((plane + 255) / 256);
+  if (runs >= kStripRuns) runs = (runs + 7) / 8 * 8;
+  return dim3(runs, static_cast<unsigned>(a.nz));
 }
 
 int launch_yee_h(const FdArgs& a, bool f32, hipStream_t s) {
