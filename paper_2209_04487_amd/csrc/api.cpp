@@ -447,6 +447,11 @@ int qd_init(const qd_desc* d, const double* U_g, const double* U_e, const double
   const int nr = d->n_r, nj = d->j_max + 1;
   if (qd_jmg_bytes(d) > 0 && !fill_jmg_tables(d->j_max, reinterpret_cast<double*>(host.data() + L.total)))
     return fail(MSQD_EDEVICE, "(j, m) coupling tables: eigen-decomposition did not converge");
+  {
+    double m = 0.0;   // largest |mu12 dt|, beside the status word
+    for (int k = 0; k < nr; ++k) m = std::max(m, std::fabs(t.mudt[k]));
+    put(L.status + 8, &m, 8);
+  }
   put(L.psi0, psi0, 8 * nr);
   put(L.kin_d, t.kin.data(), 16 * nr);
   put(L.tw_d, t.tw.data(), 16 * t.tw.size());

@@ -36,18 +36,25 @@ struct FftShape {
 template <int NR, typename T>
 constexpr int line_stride() { return NR + FftShape<NR, T>::R2; }
 
-// The fused forward step exchanges each line through LDS in SP rounds of
-// NR/SP radial points (the in-line transposes and the J<->angle exchange
-// alike), so that a molecule needs 1/SP of the LDS and more molecules fit on
-// a CU.  complex64 lines with an even number of columns per lane use two
-// rounds; complex128 lines (register-bound, one molecule per CU either way)
-// and the shortest grids use one.
+// The fused forward step exchanges each line through LDS in SP rounds (the
+// in-line transposes and the J<->angle exchange alike), so that a molecule
+// needs 1/SP of the LDS and more molecules fit on a CU.  complex64 lines with
+// an even number of columns per lane take two rounds of half the radial
+// points; the shortest complex64 grids use one.  complex128 lines take one
+// round, or two by parts (mol_step_kernel's PARTS): the real and the imaginary
+// parts in turn, as their lanes hold a single column at n_r = 256.
 template <int NR, typename T>
 constexpr int fwd_split() {
   return (sizeof(T) == 4 && (FftShape<NR, T>::R1 / FftShape<NR, T>::R2) % 2 == 0) ? 2 : 1;
 }
-template <int NR, typename T>
-constexpr int fwd_line_stride() { return NR / fwd_split<NR, T>() + FftShape<NR, T>::R2; }
+// Elements between the LDS rows of lines in SP rounds: NR/SP points, at least
+// the padded rows of R1 + 1 of the transposes.  By parts a line needs
+// R2 (R1 + 1) doubles, half as many elements; that stride puts the lines of a
+// half-wavefront on distinct banks in the row and the column accesses.
+template <int NR, typename T, int SP = fwd_split<NR, T>()>
+constexpr int fwd_line_stride() {
+  return NR / SP + FftShape<NR, T>::R2 / ((sizeof(T) == 8 && SP == 2) ? 2 : 1);
+}
 
 // The per-workgroup LDS copy of the transform tables (kinetic factors,
 // four-step twiddles, absorber mask), kept ahead of the lines (complex64
@@ -102,9 +109,9 @@ __device__ __forceinline__ void stage_tables_to_lds(cx<T>* kin_s, cx<T>* tw_s, T
   lds_stage(mask_s, mask_g, NR * sizeof(T));
 }
 
-template <int NR, typename T>
+template <int NR, typename T, int SP = fwd_split<NR, T>()>
 __device__ __forceinline__ int lds_row(int line) {
-  return lds_line_start(line, fwd_line_stride<NR, T>(), static_cast<int>(sizeof(cx<T>)));
+  return lds_line_start(line, fwd_line_stride<NR, T, SP>(), static_cast<int>(sizeof(cx<T>)));
 }
 
 __device__ __forceinline__ void wave_lds_sync() {
@@ -192,13 +199,49 @@ constexpr int tw_log2() { return NR <= 1 ? 0 : 1 + tw_log2<NR / 2>(); }
 template <int NR, typename T>
 constexpr bool tw_scaled() { return sizeof(T) == 4 && tw_log2<NR>() % 2 == 0; }
 
+// One in-line transpose of complex128 lines by parts: part c of the lane's
+// values, written as the row q of R2 rows of R1 + 1 doubles and read as its
+// columns a = q + R2 u (BACK: the reverse), the real parts in one round and the
+// imaginary parts in the next.
+template <int R1, int R2, bool BACK>
+__device__ __forceinline__ void transpose_by_parts(cx<double>* v, cx<double>* slot, int q) {
+  constexpr int U = R1 / R2, RS = R1 + 1;
+  double* sl = reinterpret_cast<double*>(slot);
+#pragma unroll
+  for (int c = 0; c < 2; ++c) {
+    if (BACK || c > 0) wave_lds_sync();   // the previous round's reads are done
+    if constexpr (!BACK) {
+#pragma unroll
+      for (int a = 0; a < R1; ++a) sl[q * RS + a] = c == 0 ? v[a].x : v[a].y;
+    } else {
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+#pragma unroll
+        for (int qq = 0; qq < R2; ++qq) sl[qq * RS + q + R2 * u] = c == 0 ? v[u * R2 + qq].x : v[u * R2 + qq].y;
+    }
+    wave_lds_sync();
+    if constexpr (!BACK) {
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+#pragma unroll
+        for (int qq = 0; qq < R2; ++qq) (c == 0 ? v[u * R2 + qq].x : v[u * R2 + qq].y) = sl[qq * RS + q + R2 * u];
+    } else {
+#pragma unroll
+      for (int a = 0; a < R1; ++a) (c == 0 ? v[a].x : v[a].y) = sl[q * RS + a];
+    }
+  }
+}
+
 template <typename T, int NR, bool CONJ = false, int SP = 1, int TWC = 0, bool TWS = false>
 __device__ __forceinline__ void kinetic_half(cx<T>* v, cx<T>* slot, int q, const cx<T>* __restrict__ kin,
                                              const cx<T>* __restrict__ tw2) {
   constexpr int R1 = FftShape<NR, T>::R1, R2 = FftShape<NR, T>::R2, U = R1 / R2;
+  // complex128 in two rounds: the transposes go by parts
+  constexpr bool PARTS = sizeof(T) == 8 && SP == 2;
   // SP rounds of RH = R1/SP columns each; the slot holds R2 rows of RH + 1
-  constexpr int RH = R1 / SP, UH = U / SP, RS = RH + 1;
-  static_assert(U % SP == 0, "columns per lane must split evenly");
+  constexpr int SC = PARTS ? 1 : SP;
+  constexpr int RH = R1 / SC, UH = U / SC, RS = RH + 1;
+  static_assert(U % SC == 0, "columns per lane must split evenly");
   static_assert(!TWS || tw_scaled<NR, T>(), "scaled twiddles need complex64 and an even log2 n_r");
   const T s_half = T(1) / T(1 << (tw_log2<NR>() / 2));   // n_r^(-1/2) (TWS)
   // pass 1: DFT over p, twiddle exp(-2 pi i q a / NR)
@@ -206,13 +249,16 @@ __device__ __forceinline__ void kinetic_half(cx<T>* v, cx<T>* slot, int q, const
   if constexpr (TWS) v[0] = cscale(v[0], s_half);
 #pragma unroll
   for (int a = 1; a < R1; ++a) v[a] = cmul(v[a], TWC > 0 ? tw2[q * TWC + a] : tw2[a * R1 + q]);
+  if constexpr (PARTS) transpose_by_parts<R1, R2, false>(v, slot, q);
 #pragma unroll
-  for (int h = 0; h < SP; ++h) {
-    if (h > 0) wave_lds_sync();
-    // this lane's row of the columns [h RH, (h+1) RH)
+  for (int h = 0; h < SC; ++h) {
+    if constexpr (!PARTS) {
+      if (h > 0) wave_lds_sync();
+      // this lane's row of the columns [h RH, (h+1) RH)
 #pragma unroll
-    for (int al = 0; al < RH; ++al) slot[q * RS + al] = v[h * RH + al];
-    wave_lds_sync();
+      for (int al = 0; al < RH; ++al) slot[q * RS + al] = v[h * RH + al];
+      wave_lds_sync();
+    }
     // pass 2 on the transposed data: frequency k = a + R1 b, columns
     // a = q + R2 u of this round, held in the registers written above
 #pragma unroll
@@ -221,8 +267,10 @@ __device__ __forceinline__ void kinetic_half(cx<T>* v, cx<T>* slot, int q, const
       const int a = q + R2 * u;
       const int al = q + R2 * uu;
       cx<T>* w = v + u * R2;
+      if constexpr (!PARTS) {
 #pragma unroll
-      for (int qq = 0; qq < R2; ++qq) w[qq] = slot[qq * RS + al];
+        for (int qq = 0; qq < R2; ++qq) w[qq] = slot[qq * RS + al];
+      }
       dft<R2, false, T>(w);
 #pragma unroll
       for (int b = 0; b < R2; ++b) {
@@ -236,17 +284,20 @@ __device__ __forceinline__ void kinetic_half(cx<T>* v, cx<T>* slot, int q, const
 #pragma unroll
       for (int qq = 1; qq < R2; ++qq) w[qq] = cmul_conj(w[qq], tw2[qq * (TWC > 0 ? TWC : R1) + a]);
     }
-    wave_lds_sync();
+    if constexpr (!PARTS) {
+      wave_lds_sync();
 #pragma unroll
-    for (int uu = 0; uu < UH; ++uu) {
-      const int al = q + R2 * uu;
+      for (int uu = 0; uu < UH; ++uu) {
+        const int al = q + R2 * uu;
 #pragma unroll
-      for (int qq = 0; qq < R2; ++qq) slot[qq * RS + al] = v[(h * UH + uu) * R2 + qq];
+        for (int qq = 0; qq < R2; ++qq) slot[qq * RS + al] = v[(h * UH + uu) * R2 + qq];
+      }
+      wave_lds_sync();
+#pragma unroll
+      for (int al = 0; al < RH; ++al) v[h * RH + al] = slot[q * RS + al];
     }
-    wave_lds_sync();
-#pragma unroll
-    for (int al = 0; al < RH; ++al) v[h * RH + al] = slot[q * RS + al];
   }
+  if constexpr (PARTS) transpose_by_parts<R1, R2, true>(v, slot, q);
   dft<R1, true, T>(v);
   wave_lds_sync();
 }
@@ -274,22 +325,26 @@ __device__ __noinline__ SinVers32 sin_vers_large(float a) {
   const float h = sinf(0.5f * a);
   return {s, 2.0f * h * h};
 }
+constexpr double kSinVersSeries64 = 0.03125;   // |a| below which the FP64 series holds
+__device__ __forceinline__ void sin_vers_series(double a, double* s, double* v) {
+  const double a2 = a * a;
+  // sin a = a (1 - a^2/3! + a^4/5! - a^6/7! + a^8/9!)
+  double ps = 1.0 / 362880.0;
+  ps = ps * a2 - 1.0 / 5040.0;
+  ps = ps * a2 + 1.0 / 120.0;
+  ps = ps * a2 - 1.0 / 6.0;
+  *s = a + a * a2 * ps;
+  // 1 - cos a = a^2/2! - a^4/4! + a^6/6! - a^8/8! + a^10/10!
+  double pc = 1.0 / 3628800.0;
+  pc = pc * a2 - 1.0 / 40320.0;
+  pc = pc * a2 + 1.0 / 720.0;
+  pc = pc * a2 - 1.0 / 24.0;
+  pc = pc * a2 + 0.5;
+  *v = a2 * pc;
+}
 __device__ __forceinline__ void sin_vers(double a, double* s, double* v) {
-  if (fabs(a) < 0.03125) {
-    const double a2 = a * a;
-    // sin a = a (1 - a^2/3! + a^4/5! - a^6/7! + a^8/9!)
-    double ps = 1.0 / 362880.0;
-    ps = ps * a2 - 1.0 / 5040.0;
-    ps = ps * a2 + 1.0 / 120.0;
-    ps = ps * a2 - 1.0 / 6.0;
-    *s = a + a * a2 * ps;
-    // 1 - cos a = a^2/2! - a^4/4! + a^6/6! - a^8/8! + a^10/10!
-    double pc = 1.0 / 3628800.0;
-    pc = pc * a2 - 1.0 / 40320.0;
-    pc = pc * a2 + 1.0 / 720.0;
-    pc = pc * a2 - 1.0 / 24.0;
-    pc = pc * a2 + 0.5;
-    *v = a2 * pc;
+  if (fabs(a) < kSinVersSeries64) {
+    sin_vers_series(a, s, v);
   } else {
     const SinVers64 r = sin_vers_large(a);
     *s = r.s;
@@ -552,6 +607,7 @@ struct MfmaK4<double> {
   __device__ static __forceinline__ void settle(acc& a, acc& b, acc& c, acc& d) {
     asm volatile("" : "+v"(a), "+v"(b), "+v"(c), "+v"(d));
   }
+  __device__ static __forceinline__ void settle(acc& a, acc& b) { asm volatile("" : "+v"(a), "+v"(b)); }
 };
 
 // The J (or node) row fed by element i of lane group g: MfmaK4::row, or in
@@ -565,14 +621,16 @@ __device__ __forceinline__ int mf_row(int g, int i) {
 // frag: [2][64 lanes][4]: block 0 A_i = T[l%16][row(l/16, i)], block 1 the
 // transpose T[row(l/16, i)][l%16]; zero outside nj (in the half-K order for
 // FP32 when KH).  KH: N_J <= kHalfKMaxNJ, two of the four K instructions.
-template <typename T, int NR, bool KH>
+// NK: K instructions of a product (four, three or the half-K two).  LARGE: angles
+// beyond the series may occur (FP64; FP32 decides per tile).
+template <typename T, int NR, int NK, bool LARGE>
 __device__ __forceinline__ void coupling_mfma_exact(cx<T>* sh, int nj, int r0,
                                                     const T* __restrict__ frag,
                                                     const T* __restrict__ x,
                                                     const T* __restrict__ mudt, T E) {
   typedef typename MfmaK4<T>::acc acc_t;
+  constexpr bool KH = NK == 2;
   constexpr int NRH = NR / fwd_split<NR, T>();
-  constexpr int NK = KH ? 2 : 4;
   const int lane = fresh_lane();
   const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) >> 6);
   const int nwaves = (blockDim.x + 63) >> 6;
@@ -611,7 +669,12 @@ __device__ __forceinline__ void coupling_mfma_exact(cx<T>* sh, int nj, int r0,
     MfmaK4<T>::settle(Pgr, Pgi, Per, Pei);
     const T md = mudt[r] * E;
     T sn[4], vs[4];
-    sin_vers_tile<NR>(md, xk, sn, vs);
+    if constexpr (LARGE) {
+      sin_vers_tile<NR>(md, xk, sn, vs);
+    } else {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) sin_vers_series(md * xk[i], &sn[i], &vs[i]);
+    }
 #pragma unroll
     for (int i = 0; i < NK; ++i) {
       const T gr = Pgr[i], gi = Pgi[i], er = Per[i], ei = Pei[i];
@@ -634,6 +697,99 @@ __device__ __forceinline__ void coupling_mfma_exact(cx<T>* sh, int nj, int r0,
       T* oe = reinterpret_cast<T*>(sh + rows.e[i] + rl);
       og[0] = cgr[i]; og[1] = cgi[i];
       oe[0] = cer[i]; oe[1] = cei[i];
+    }
+  }
+}
+
+// complex128 lines in two rounds: the contraction by parts.  With the excited
+// state held as e~ = -i e, the rotation takes (g.x, e~.x) to themselves and
+// (g.y, e~.y) to themselves by the same rule, dX = -v X - s Y, dY = s X - v Y per
+// node.  So the J <-> angle exchange takes the first parts of all lines in one
+// round and the second parts in the next, over all radial points: half the LDS
+// of a complex exchange, the tiles shared as evenly, and half the accumulators.
+// The products are those of coupling_mfma_exact; sh: the rows as doubles.
+template <int NR, int NK, bool LARGE>
+__device__ __forceinline__ void coupling_mfma_parts(double* sh, int nj, const double* __restrict__ frag,
+                                                    const double* __restrict__ x, const double* __restrict__ mudt,
+                                                    double E) {
+  typedef MfmaK4<double> MK;
+  typedef MK::acc acc_t;
+  const int lane = fresh_lane();
+  const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) >> 6);
+  const int nwaves = (blockDim.x + 63) >> 6;
+  const int col = lane & 15;
+  const int grp = lane >> 4;
+  double A[NK], At[NK], xk[NK];
+  int og[NK], oe[NK];
+  const int spare = 2 * lds_row<NR, double, 2>(2 * nj);
+#pragma unroll
+  for (int i = 0; i < NK; ++i) {
+    const int J = MK::row(grp, i);
+    A[i] = frag[(0 * 64 + lane) * 4 + i];
+    At[i] = frag[(1 * 64 + lane) * 4 + i];
+    xk[i] = J < nj ? x[J] : 0.0;
+    og[i] = J < nj ? 2 * lds_row<NR, double, 2>(J) : spare;
+    oe[i] = J < nj ? 2 * lds_row<NR, double, 2>(nj + J) : spare;
+  }
+#pragma unroll 1
+  for (int tile = wave; tile * 16 < NR; tile += nwaves) {
+    const int r = tile * 16 + col;
+    const acc_t z = {0.0, 0.0, 0.0, 0.0};
+    acc_t X = z, Y = z, P = z, Q = z;
+#pragma unroll
+    for (int i = 0; i < NK; ++i) {
+      X[i] = sh[og[i] + r];
+      Y[i] = sh[oe[i] + r];
+    }
+    const double md = mudt[r] * E;
+#pragma unroll
+    for (int i = 0; i < NK; ++i) {
+      P = MK::mma(A[i], X[i], P);
+      Q = MK::mma(A[i], Y[i], Q);
+    }
+    MK::settle(P, Q);
+#pragma unroll
+    for (int i = 0; i < NK; ++i) {
+      double sn, vs;
+      if constexpr (LARGE)
+        sin_vers(md * xk[i], &sn, &vs);
+      else
+        sin_vers_series(md * xk[i], &sn, &vs);
+      const double px = P[i], qy = Q[i];
+      P[i] = -vs * px - sn * qy;
+      Q[i] = -vs * qy + sn * px;
+    }
+#pragma unroll
+    for (int i = 0; i < NK; ++i) {
+      X = MK::mma(At[i], P[i], X);
+      Y = MK::mma(At[i], Q[i], Y);
+    }
+    MK::settle(X, Y);
+#pragma unroll
+    for (int i = 0; i < NK; ++i) {
+      sh[og[i] + r] = X[i];
+      sh[oe[i] + r] = Y[i];
+    }
+  }
+}
+
+// Both rounds of it for this lane's values.
+template <int NR, int NK, bool LARGE>
+__device__ __forceinline__ void coupling_by_parts(cx<double>* v, bool active, double* slot, int q, double* sh, int nj,
+                                                  const double* frag, const double* x, const double* mudt, double E) {
+  constexpr int R1 = FftShape<NR, double>::R1, R2 = FftShape<NR, double>::R2;
+#pragma unroll
+  for (int c = 0; c < 2; ++c) {
+    if (active) {
+#pragma unroll
+      for (int p = 0; p < R1; ++p) slot[q + R2 * p] = c == 0 ? v[p].x : v[p].y;
+    }
+    __syncthreads();
+    coupling_mfma_parts<NR, NK, LARGE>(sh, nj, frag, x, mudt, E);
+    __syncthreads();
+    if (active) {
+#pragma unroll
+      for (int p = 0; p < R1; ++p) (c == 0 ? v[p].x : v[p].y) = slot[q + R2 * p];
     }
   }
 }
@@ -692,16 +848,20 @@ __device__ __forceinline__ void absorb_point(cx<T>& v, T m, double& ab) {
 // SIMD fit in 128 VGPRs and the LDS holds more molecules than that.  The FP64
 // form is bounded by LDS (one molecule of complex128 lines per CU) and may use
 // 256 VGPRs.
-template <typename T, int NR>
-struct MolOcc { static constexpr int waves = sizeof(T) == 8 ? 2 : (NR <= 128 ? 4 : 3); };
+template <typename T, int NR, bool PARTS>
+struct MolOcc {
+  static constexpr int waves = sizeof(T) == 8 ? (PARTS && NR < 512 ? 3 : 2) : (NR <= 128 ? 4 : 3);
+};
 
 
 // coupling path: BF16 hi/lo split on 16x16x16 (mixed form) or the
 // working precision on 16x16x4 (FP32 and FP64 forms)
 // (kCpExactHalf: the working precision with N_J <= kHalfKMaxNJ, two of the
-// four K instructions; a launch picks it from N_J, so that a kernel holds
-// one contraction path)
-enum { kCpExact = 0, kCpBf16x3 = 1, kCpExactHalf = 2 };
+// four K instructions; kCpExact3: FP64 with N_J <= 12, whose row order puts the
+// rows from 12 on into the fourth; a launch picks them from N_J, so that a kernel
+// holds one contraction path)
+constexpr int kThreeKMaxNJ = 12;
+enum { kCpExact = 0, kCpBf16x3 = 1, kCpExactHalf = 2, kCpExact3 = 3 };
 
 // raised wave priority over the contraction rounds (see the step loop)
 template <typename T, int NR, int CP>
@@ -710,10 +870,16 @@ inline constexpr bool kPrioContraction = CP == kCpBf16x3 && NR >= 256;
 // ONE: the launch advances exactly one step (the coupled step's case); the
 // step loop then has no back edge, and the register allocation needs no
 // spills.
-template <typename T, int NR, int CP, bool ONE>
-__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(MolOcc<T, NR>::waves)))
+template <typename T, int NR, int CP, bool ONE, bool PARTS>
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(MolOcc<T, NR, PARTS>::waves)))
 void mol_step_kernel(MolArgs a) {
   constexpr int R1 = FftShape<NR, T>::R1, R2 = FftShape<NR, T>::R2;
+  // SP exchange rounds of NRH radial points; round h holds the registers
+  // p in [h PH, (h+1) PH), i.e. r = q + R2 p in [h NRH, (h+1) NRH)
+  // (PARTS: the dipole readout only)
+  constexpr int SP = PARTS ? 2 : fwd_split<NR, T>(), PH = R1 / SP, NRH = NR / SP;
+  constexpr int NK = CP == kCpExactHalf ? 2 : CP == kCpExact3 ? 3 : 4;
+  static_assert(!PARTS || sizeof(T) == 8, "the exchange by parts is for complex128 lines");
   static_assert(CP != kCpBf16x3 || stage_tables<NR, T>(),
                 "the BF16 contraction reads its operands from the LDS copy of the tables");
   extern __shared__ __align__(16) unsigned char smem[];
@@ -728,7 +894,7 @@ void mol_step_kernel(MolArgs a) {
   unsigned char* frag_s = smem + StagedTables<NR, T>::fft_bytes;
   float* x_s = reinterpret_cast<float*>(frag_s + StagedTables<NR, T>::frag_bytes);
   cx<T>* sh = reinterpret_cast<cx<T>*>(smem + TB);
-  double* red = reinterpret_cast<double*>(smem + TB + sizeof(cx<T>) * (lds_row<NR, T>(L) + NR / fwd_split<NR, T>()));
+  double* red = reinterpret_cast<double*>(smem + TB + sizeof(cx<T>) * (lds_row<NR, T, SP>(L) + NRH));
 
   const int mol = blockIdx.x;
   const int tid = threadIdx.x;
@@ -736,6 +902,7 @@ void mol_step_kernel(MolArgs a) {
   const int line = tid / R2;
   const int q = tid - line * R2;
   const bool active = line < L;
+  const bool exc = line >= nj;   // an excited-state line (PARTS: held as -i e)
 
   const char* ws = a.ws;
   MolTabs<T> tb;
@@ -771,18 +938,29 @@ void mol_step_kernel(MolArgs a) {
   }
   if (a.E_out != nullptr && tid == 0) a.E_out[mol] = Ed;
   const T E = static_cast<T>(Ed);
+  // FP64: whether some coupling angle mu12(r) dt x E may lie beyond the series of
+  // sin_vers (|x| < 1; also taken for a NaN).  Decided per molecule, so that the
+  // library calls and the registers that they clobber stay out of the common
+  // path (with the fourth K instruction saved: 1867 -> 1709 us per 20,000
+  // molecules at n_r = 256, N_J = 11)
+  const bool large = sizeof(T) == 8 &&
+                     !(fabs(Ed) * *reinterpret_cast<const double*>(ws + a.lay.status + 8) < kSinVersSeries64);
 
   // the contractions' spare row (rows J >= nj) holds zeros; the barrier
   // before the first contraction publishes them
-  for (int i = tid; i < NR / fwd_split<NR, T>(); i += nthr) sh[lds_row<NR, T>(L) + i] = cx<T>{T(0), T(0)};
+  for (int i = tid; i < NRH; i += nthr) sh[lds_row<NR, T, SP>(L) + i] = cx<T>{T(0), T(0)};
 
   cx<T>* psi = reinterpret_cast<cx<T>*>(a.psi) + static_cast<size_t>(mol) * L * NR;
-  cx<T>* slot = sh + lds_row<NR, T>(line);
+  cx<T>* slot = sh + lds_row<NR, T, SP>(line);
   const int loff = line * NR + q;  // this lane's first element of its line
   cx<T> v[R1];
   if (active) {
 #pragma unroll
     for (int p = 0; p < R1; ++p) v[p] = psi[loff + R2 * p];
+    if constexpr (PARTS) {
+#pragma unroll
+      for (int p = 0; p < R1; ++p) v[p] = exc ? mul_mi(v[p]) : v[p];
+    }
   }
   // the tables read at every element go to LDS (the per-element L1/L2
   // traffic and latency of these reads dominated the step otherwise)
@@ -793,9 +971,6 @@ void mol_step_kernel(MolArgs a) {
     __syncthreads();
   }
 
-  // SP exchange rounds of NRH radial points; round h holds the registers
-  // p in [h PH, (h+1) PH), i.e. r = q + R2 p in [h NRH, (h+1) NRH)
-  constexpr int SP = fwd_split<NR, T>(), PH = R1 / SP, NRH = NR / SP;
   double ab = 0.0;
   const int n_steps = ONE ? 1 : a.n_steps;
   for (int step = 0; step < n_steps; ++step) {
@@ -813,8 +988,25 @@ void mol_step_kernel(MolArgs a) {
     }
     const cx<T>* vph = opaque(tb.vph);
     if (active) kinetic_half<T, NR, false, SP, 0, tw_scaled<NR, T>()>(v, slot, q, kin, tw);
+    if constexpr (PARTS) {
+      if (active) {
 #pragma unroll
-    for (int h = 0; h < SP; ++h) {
+        for (int p = 0; p < R1; ++p) v[p] = phase_mul(v[p], vph[loff + R2 * p]);
+      }
+      const T* frag = reinterpret_cast<const T*>(ws + a.lay.tmfrag_d);
+      T* slotd = reinterpret_cast<T*>(slot);
+      T* shd = reinterpret_cast<T*>(sh);
+      if (__builtin_expect(large, 0))
+        coupling_by_parts<NR, NK, true>(v, active, slotd, q, shd, nj, frag, tb.x, tb.mudt, E);
+      else
+        coupling_by_parts<NR, NK, false>(v, active, slotd, q, shd, nj, frag, tb.x, tb.mudt, E);
+      if (active) {
+#pragma unroll
+        for (int p = 0; p < R1; ++p) v[p] = phase_mul(v[p], vph[loff + R2 * p]);
+      }
+    }
+#pragma unroll
+    for (int h = 0; h < (PARTS ? 0 : SP); ++h) {
       if (active) {
 #pragma unroll
         for (int pp = 0; pp < PH; ++pp) {
@@ -836,11 +1028,15 @@ void mol_step_kernel(MolArgs a) {
         coupling_mfma<NR>(sh, nj, h * NRH, reinterpret_cast<const unsigned short*>(frag_s),
                           reinterpret_cast<const float*>(x_s), tb.mudt, E);
       } else if constexpr (stage_tables<NR, T>()) {
-        coupling_mfma_exact<T, NR, CP == kCpExactHalf>(sh, nj, h * NRH, reinterpret_cast<const T*>(frag_s),
+        coupling_mfma_exact<T, NR, NK, true>(sh, nj, h * NRH, reinterpret_cast<const T*>(frag_s),
                                                        reinterpret_cast<const T*>(x_s), tb.mudt, E);
       } else {
         const T* frag = reinterpret_cast<const T*>(ws + (sizeof(T) == 8 ? a.lay.tmfrag_d : a.lay.tmfrag_f));
-        coupling_mfma_exact<T, NR, CP == kCpExactHalf>(sh, nj, h * NRH, frag, tb.x, tb.mudt, E);
+        if (__builtin_expect(large, 0)) {
+          coupling_mfma_exact<T, NR, NK, true>(sh, nj, h * NRH, frag, tb.x, tb.mudt, E);
+        } else {
+          coupling_mfma_exact<T, NR, NK, false>(sh, nj, h * NRH, frag, tb.x, tb.mudt, E);
+        }
       }
       if constexpr (kPrioContraction<T, NR, CP>) __builtin_amdgcn_s_setprio(0);
       __syncthreads();
@@ -894,10 +1090,12 @@ void mol_step_kernel(MolArgs a) {
       __syncthreads();
       for (int rl = tid; rl < NRH; rl += nthr) {
         T acc = T(0);
-        cx<T> g0 = sh[rl], e0 = sh[lds_row<NR, T>(nj) + rl];
+        cx<T> g0 = sh[rl], e0 = sh[lds_row<NR, T, SP>(nj) + rl];
         for (int J = 0; J + 1 < nj; ++J) {
-          const cx<T> g1 = sh[lds_row<NR, T>(J + 1) + rl], e1 = sh[lds_row<NR, T>(nj + J + 1) + rl];
-          const T t = g0.x * e1.x + g0.y * e1.y + g1.x * e0.x + g1.y * e0.y;
+          const cx<T> g1 = sh[lds_row<NR, T, SP>(J + 1) + rl], e1 = sh[lds_row<NR, T, SP>(nj + J + 1) + rl];
+          // PARTS: e = i e~
+          const T t = PARTS ? (g0.y * e1.x - g0.x * e1.y) + (g1.y * e0.x - g1.x * e0.y)
+                            : g0.x * e1.x + g0.y * e1.y + g1.x * e0.x + g1.y * e0.y;
           acc += static_cast<T>(tb.cj[J]) * t;
           g0 = g1;
           e0 = e1;
@@ -921,41 +1119,67 @@ void mol_step_kernel(MolArgs a) {
   if (active && n_steps > 0) {
     cx<T>* out = a.psi_out ? reinterpret_cast<cx<T>*>(a.psi_out) + static_cast<size_t>(mol) * L * NR : psi;
 #pragma unroll
-    for (int p = 0; p < R1; ++p) out[loff + R2 * p] = v[p];
+    for (int p = 0; p < R1; ++p) out[loff + R2 * p] = (PARTS && exc) ? mul_i(v[p]) : v[p];
   }
 }
 
-template <typename T, int NR, int CP, bool ONE>
+template <typename T, int NR, int CP, bool ONE, bool PARTS>
 int launch_mol_t1(const MolArgs& a, hipStream_t s) {
   static_assert(NR == FftShape<NR, T>::R1 * FftShape<NR, T>::R2, "FFT shape");
-  constexpr int R2 = FftShape<NR, T>::R2;
+  constexpr int R2 = FftShape<NR, T>::R2, SP = PARTS ? 2 : fwd_split<NR, T>();
   const int L = 2 * a.nj;
   int threads = ((L * R2 + 63) / 64) * 64;
   if (threads < 64) threads = 64;
   const size_t shm = lds_table_bytes<NR, T>() +
-                     sizeof(cx<T>) * (static_cast<size_t>(lds_line_start(L, fwd_line_stride<NR, T>(), sizeof(cx<T>))) +
-                                      NR / fwd_split<NR, T>()) +
+                     sizeof(cx<T>) * (static_cast<size_t>(lds_line_start(L, fwd_line_stride<NR, T, SP>(), sizeof(cx<T>))) +
+                                      NR / SP) +
                      16 * 4 * sizeof(double);
   static std::atomic<unsigned long long> lds_set{0};
   if (shm > 64 * 1024) {
-    const hipError_t e = allow_large_lds(reinterpret_cast<const void*>(&mol_step_kernel<T, NR, CP, ONE>), lds_set);
+    const hipError_t e = allow_large_lds(reinterpret_cast<const void*>(&mol_step_kernel<T, NR, CP, ONE, PARTS>), lds_set);
     if (e != hipSuccess) return static_cast<int>(e);
   }
-  hipLaunchKernelGGL((mol_step_kernel<T, NR, CP, ONE>), dim3(a.n_mol), dim3(threads), shm, s, a);
+  hipLaunchKernelGGL((mol_step_kernel<T, NR, CP, ONE, PARTS>), dim3(a.n_mol), dim3(threads), shm, s, a);
   return static_cast<int>(hipGetLastError());
 }
 
-// complex64 forms: a single-step instantiation (no spills at N_r = 256,
-// 4% faster); the FP64 form measured no gain from it
+// Where the exchange by parts (half the LDS, three waves per SIMD at n_r <= 256)
+// beats the one-round exchange in FP64, both measured (us per launch, one round /
+// by parts):
+//  n_r = 512, N_J > 1: a CU holds two workgroups instead of one (N_J = 7, 5,000
+//    molecules: 795 / 759, three steps 1235 / 837; N_J = 1: 396 / 459);
+//  n_r = 256, N_J <= 8, single steps: up to four wavefronts per workgroup, three
+//    workgroups instead of two per CU (N_J = 6, 20,000 molecules: 835 / 714).  Its
+//    multi-step loop spills (817 / 893), and from five wavefronts on a CU takes one
+//    workgroup either way (N_J = 11: 1709 / 2153);
+//  n_r = 64, N_J > 8 (30,000 molecules: 665 / 531; N_J = 6: 294 / 303).
+// At n_r = 128 the one-round exchange fits as many (N_J = 7: 614 / 653).
+template <int NR, int CP, bool ONE>
+constexpr bool mol_parts() {
+  return NR == 512 || (NR == 256 && CP == kCpExactHalf && ONE) || (NR == 64 && CP != kCpExactHalf);
+}
+
+template <typename T, int NR, int CP, bool ONE>
+int launch_mol_t2(const MolArgs& a, hipStream_t s) {
+  if constexpr (sizeof(T) == 8 && mol_parts<NR, CP, ONE>()) {
+    if (NR != 512 || a.nj > 1) return launch_mol_t1<T, NR, CP, ONE, true>(a, s);
+  }
+  if constexpr (sizeof(T) == 4 || NR == 512 || !mol_parts<NR, CP, ONE>()) return launch_mol_t1<T, NR, CP, ONE, false>(a, s);
+}
+
+// The contraction form by N_J (see kCpExact...), and a single-step instantiation:
+// in complex64 it needs no spills at n_r = 256 (4% faster), in FP64 it halves the
+// launch at n_r = 512 (1550 -> 795 us at N_J = 7, 5,000 molecules; there the step
+// loop's registers spill) and moves the others by a few percent.
 template <typename T, int NR, int CP>
 int launch_mol_t(const MolArgs& a, hipStream_t s) {
   if constexpr (CP == kCpExact) {
     if (a.nj <= kHalfKMaxNJ) return launch_mol_t<T, NR, kCpExactHalf>(a, s);
+    if constexpr (sizeof(T) == 8) {
+      if (a.nj <= kThreeKMaxNJ) return launch_mol_t<T, NR, kCpExact3>(a, s);
+    }
   }
-  if constexpr (sizeof(T) == 4) {
-    if (a.n_steps == 1) return launch_mol_t1<T, NR, CP, true>(a, s);
-  }
-  return launch_mol_t1<T, NR, CP, false>(a, s);
+  return a.n_steps == 1 ? launch_mol_t2<T, NR, CP, true>(a, s) : launch_mol_t2<T, NR, CP, false>(a, s);
 }
 
 template <typename T, int CP>

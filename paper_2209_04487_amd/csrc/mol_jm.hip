@@ -111,13 +111,16 @@ __device__ __forceinline__ void coupling_jm_point(cx<T>* g, cx<T>* e, const cx<T
 // The tables are staged in the compact layout (complex64 forms), which keeps
 // a workgroup small enough for ten molecules per CU.
 // Occupancy target: three waves per SIMD for the complex64 form (168
-// registers); the complex128 form takes what it needs.
-template <typename T>
-struct JmOcc { static constexpr int waves = sizeof(T) == 4 ? 3 : 1; };
+// registers); the complex128 form two in single-step launches (at n_r = 512,
+// whose lines take 128 registers a lane, 1267 -> 941 us per 10,000 molecules), and
+// what it needs in the others, whose step loop would spill there (969 -> 1120 us
+// per 4,000 molecules and three steps at n_r = 512).
+template <typename T, bool ONE>
+struct JmOcc { static constexpr int waves = sizeof(T) == 4 ? 3 : (ONE ? 2 : 1); };
 
 // ONE: the launch advances exactly one step (as in the m = 0 kernel).
 template <typename T, int NR, bool ONE>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(JmOcc<T>::waves))) void mol_jm_kernel(MolArgs a) {
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(JmOcc<T, ONE>::waves))) void mol_jm_kernel(MolArgs a) {
   constexpr int R1 = FftShape<NR, T>::R1, R2 = FftShape<NR, T>::R2;
   constexpr int NB = 4, L = 2 * NB;
   constexpr int SP = fwd_split<NR, T>(), PH = R1 / SP, NRH = NR / SP;
@@ -344,13 +347,10 @@ int launch_jm_t1(const MolArgs& a, hipStream_t s) {
   return static_cast<int>(hipGetLastError());
 }
 
-// complex64: a single-step instantiation for the coupled step's launches
+// a single-step instantiation for the coupled step's launches
 template <typename T, int NR>
 int launch_jm_t(const MolArgs& a, hipStream_t s) {
-  if constexpr (sizeof(T) == 4) {
-    if (a.n_steps == 1) return launch_jm_t1<T, NR, true>(a, s);
-  }
-  return launch_jm_t1<T, NR, false>(a, s);
+  return a.n_steps == 1 ? launch_jm_t1<T, NR, true>(a, s) : launch_jm_t1<T, NR, false>(a, s);
 }
 
 template <typename T>
