@@ -293,8 +293,8 @@ __global__ __launch_bounds__(512) void mol_adj_kernel(MolAdjArgs a) {
 #pragma unroll
     for (int p = 0; p < R1; ++p) lpsi[loff + R2 * p] = lam[p];
   }
-  double sums[4] = {grad, 0.0, 0.0, 0.0};
-  block_sum4(sums, red);
+  double sums[1] = {grad};
+  block_sums<1>(sums, red);
   if (tid == 0) a.lE[mol] = sums[0];
 }
 

@@ -295,6 +295,16 @@ static MolArgs make_mol_args(const qd_desc* d, const void* ws) {
   return a;
 }
 
+// the sizes of the m = 0 basis that the library takes: a molecule's lines, the
+// complex128 ones whole, within one workgroup's LDS
+static int check_mol_lds(const qd_desc* d) {
+  const size_t need = mol_lds_bytes(d->n_r, d->j_max + 1, d->prec);
+  if (need > mol_lds_limit())
+    return fail(MSQD_EUNSUP, "n_r x (j_max+1) too large for one workgroup's LDS in this precision (" +
+                                 std::to_string(need) + " > " + std::to_string(mol_lds_limit()) + " bytes)");
+  return MSQD_OK;
+}
+
 static int launch_mol(const qd_desc* d, const MolArgs& a, hipStream_t s) {
   int e = 0;
   if (a.n_mol == 0) return MSQD_OK;
@@ -304,10 +314,8 @@ static int launch_mol(const qd_desc* d, const MolArgs& a, hipStream_t s) {
     if (e != 0) return check_hip(static_cast<hipError_t>(e), "(j, m) molecule step launch");
     return MSQD_OK;
   }
-  const size_t need = mol_lds_bytes(d->n_r, d->j_max + 1, d->prec);
-  if (need > mol_lds_limit())
-    return fail(MSQD_EUNSUP, "n_r x (j_max+1) too large for one workgroup's LDS in this precision (" +
-                                 std::to_string(need) + " > " + std::to_string(mol_lds_limit()) + " bytes)");
+  const int rc = check_mol_lds(d);
+  if (rc) return rc;
   switch (d->prec) {
     case MSQD_FP64: e = launch_mol_fp64(a, d->n_r, s); break;
     case MSQD_FP32: e = launch_mol_fp32(a, d->n_r, s); break;
@@ -573,8 +581,15 @@ static int readout_impl(const qd_desc* d, const void* ws, const void* psi, const
     a.want_d = d_mol != nullptr;
     a.want_norm = norm_mol != nullptr;
     a.want_yield = yield_mol != nullptr;
-    const int rc = launch_mol(d, a, s);
-    if (rc) return rc;
+    if (d->basis == MSQD_BASIS_M0) {
+      const int rc = check_mol_lds(d);
+      if (rc) return rc;
+      const int e = launch_mol_readout(a, d->n_r, d->prec != MSQD_FP64, s);
+      if (e) return check_hip(static_cast<hipError_t>(e), "molecule readout launch");
+    } else {
+      const int rc = launch_mol(d, a, s);
+      if (rc) return rc;
+    }
   }
   if (!sums) return MSQD_OK;
   SumArgs sa{};

@@ -44,7 +44,7 @@ QdLayout qd_layout(int n_r, int nj);
 struct MolArgs {
   int n_mol;
   int nj;
-  int n_steps;          // 0: readouts only, state untouched
+  int n_steps;          // 0 ((j, m) kernels): readouts only, state untouched
   int kdiss;            // first radial index with r > r_diss
   int kmask;            // first radial index where the absorber mask is below one
   int want_d, want_norm, want_yield;
@@ -84,5 +84,7 @@ int launch_mol_fp64(const MolArgs& a, int n_r, hipStream_t s);
 int launch_mol_jm(const MolArgs& a, int n_r, bool f32, hipStream_t s);
 int launch_mol_fp32(const MolArgs& a, int n_r, hipStream_t s);
 int launch_mol_mixed(const MolArgs& a, int n_r, hipStream_t s);
+// dipole, norm and yield of the current m = 0 wavepackets (want_*)
+int launch_mol_readout(const MolArgs& a, int n_r, bool f32, hipStream_t s);
 
 }  // namespace msqd

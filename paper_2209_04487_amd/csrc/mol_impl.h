@@ -801,20 +801,21 @@ __device__ __forceinline__ double wave_sum(double v) {
   return v;
 }
 
-// Sum of four per-lane partials over the workgroup, in a fixed order.
-__device__ __forceinline__ void block_sum4(double* v, double* red) {
+// Sums of N per-lane partials over the workgroup, in a fixed order.
+template <int N>
+__device__ __forceinline__ void block_sums(double* v, double* red) {
   const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6, nw = (blockDim.x + 63) >> 6;
 #pragma unroll
-  for (int i = 0; i < 4; ++i) v[i] = wave_sum(v[i]);
+  for (int i = 0; i < N; ++i) v[i] = wave_sum(v[i]);
   if (lane == 0) {
 #pragma unroll
-    for (int i = 0; i < 4; ++i) red[wid * 4 + i] = v[i];
+    for (int i = 0; i < N; ++i) red[wid * N + i] = v[i];
   }
   __syncthreads();
   if (threadIdx.x == 0) {
-    for (int i = 0; i < 4; ++i) {
+    for (int i = 0; i < N; ++i) {
       double s = 0.0;
-      for (int w = 0; w < nw; ++w) s += red[w * 4 + i];
+      for (int w = 0; w < nw; ++w) s += red[w * N + i];
       v[i] = s;
     }
   }
@@ -924,17 +925,14 @@ void mol_step_kernel(MolArgs a) {
   tb.mu = reinterpret_cast<const double*>(ws + a.lay.mu_d);
   tb.cj = reinterpret_cast<const double*>(ws + a.lay.cj_d);
 
-  // field seen by this molecule (gathered from E_x at its cell, or given);
-  // a readout-only launch (no step) reads no field
-  double Ed = 0.0;
-  if (ONE || a.n_steps > 0) {
-    if (a.Ex != nullptr) {
-      const int c = a.cell_of_mol[mol];
-      Ed = (a.ex_is_float ? static_cast<double>(reinterpret_cast<const float*>(a.Ex)[c])
-                          : reinterpret_cast<const double*>(a.Ex)[c]) * a.inv_eau;
-    } else {
-      Ed = a.E_mol[mol];
-    }
+  // field seen by this molecule (gathered from E_x at its cell, or given)
+  double Ed;
+  if (a.Ex != nullptr) {
+    const int c = a.cell_of_mol[mol];
+    Ed = (a.ex_is_float ? static_cast<double>(reinterpret_cast<const float*>(a.Ex)[c])
+                        : reinterpret_cast<const double*>(a.Ex)[c]) * a.inv_eau;
+  } else {
+    Ed = a.E_mol[mol];
   }
   if (a.E_out != nullptr && tid == 0) a.E_out[mol] = Ed;
   const T E = static_cast<T>(Ed);
@@ -1063,18 +1061,12 @@ void mol_step_kernel(MolArgs a) {
     }
   }
 
-  // readouts of the final state (the norm also when no dipole is asked
-  // for, as the finiteness check)
-  double nrm = 0.0, yld = 0.0, dd = 0.0;
-  const bool want_n = a.want_norm || !a.want_d;
-  if (active && (want_n || a.want_yield)) {
+  // the dipole of the final state, or (none asked for) its norm as the
+  // finiteness check
+  double nrm = 0.0, dd = 0.0;
+  if (active && !a.want_d) {
 #pragma unroll
-    for (int p = 0; p < R1; ++p) {
-      const int r = q + R2 * p;
-      const double n2 = static_cast<double>(norm2(v[p]));
-      nrm += n2;
-      if (r >= a.kdiss) yld += n2;
-    }
+    for (int p = 0; p < R1; ++p) nrm += static_cast<double>(norm2(v[p]));
   }
   if (a.want_d) {
     // d = 2 dr sum_r mu(r) sum_J c_J Re[conj(g_J) e_{J+1} + conj(g_{J+1}) e_J],
@@ -1104,19 +1096,17 @@ void mol_step_kernel(MolArgs a) {
       }
     }
   }
-  double sums[4] = {ab, nrm, yld, dd};
-  block_sum4(sums, red);
+  double sums[3] = {ab, nrm, dd};
+  block_sums<3>(sums, red);
   if (tid == 0) {
     const double dr = a.dr;
     const double absorbed = a.absorbed[mol] + sums[0] * dr;
-    if (n_steps > 0) a.absorbed[mol] = absorbed;
-    const double d = 2.0 * dr * sums[3];
-    if (a.want_d && a.d_mol) a.d_mol[mol] = d;
-    if (a.want_norm && a.norm_mol) a.norm_mol[mol] = sums[1] * dr;
-    if (a.want_yield && a.yield_mol) a.yield_mol[mol] = sums[2] * dr + absorbed;
+    a.absorbed[mol] = absorbed;
+    const double d = 2.0 * dr * sums[2];
+    if (a.want_d) a.d_mol[mol] = d;
     if (!isfinite(d) || !isfinite(sums[1]) || !isfinite(absorbed)) atomicOr(a.status, 1);
   }
-  if (active && n_steps > 0) {
+  if (active) {
     cx<T>* out = a.psi_out ? reinterpret_cast<cx<T>*>(a.psi_out) + static_cast<size_t>(mol) * L * NR : psi;
 #pragma unroll
     for (int p = 0; p < R1; ++p) out[loff + R2 * p] = (PARTS && exc) ? mul_i(v[p]) : v[p];
