@@ -366,7 +366,8 @@ typedef struct {
                                 rebuilds it from J_mol, so J_mol and P_c
                                 alone carry the state (checkpoints need not
                                 hold it).  An occupied cell outside the held
-                                planes sets its E components to NaN. */
+                                planes sets its E components to NaN (the library
+                                marks such planes in fd_ws). */
 } cpl_state;
 
 /* n_steps coupled steps from step n0 (section on molecular mapping, with

@@ -103,6 +103,7 @@ FdLayout fd_layout(const fdtd_desc* d) {
   L.aHf = take(4 * nz);
   L.kHf = take(4 * nz);
   L.freqs = take(8 * static_cast<size_t>(d->n_freq > 0 ? d->n_freq : 1));
+  L.outside = take(4 * nz);
   L.total = o;
   return L;
 }
@@ -259,6 +260,7 @@ static FdArgs make_fd_args(const fdtd_desc* d, const fdtd_fields* f, const void*
   a.mat = f->mat;
   a.ws = static_cast<const char*>(ws);
   a.lay = fd_layout(d);
+  a.stage_k[0] = a.stage_k[1] = -1;
   return a;
 }
 
@@ -827,15 +829,34 @@ static MonArgs mon_args(const fdtd_desc* d, const fdtd_fields* f, const void* ws
   return m;
 }
 
-// the monitor part of step n of a call whose last step is n_last
-static int fd_monitor(const fdtd_desc* d, const fdtd_fields* f, const void* ws, int64_t n, int64_t n_last,
-                      MonBatch& b, hipStream_t s) {
-  if (d->n_freq <= 0 || (n + 1) % d->mon_every != 0) return MSQD_OK;
-  const bool f32 = d->prec != MSQD_FP64;
+// what the monitor does at step n of a call whose last step is n_last
+enum MonPlan { kMonNone, kMonDirect, kMonStage };
+static MonPlan mon_plan(const fdtd_desc* d, int64_t n, int64_t n_last, const MonBatch& b) {
+  if (d->n_freq <= 0 || (n + 1) % d->mon_every != 0) return kMonNone;
   const bool last = n + d->mon_every > n_last;   // no further sample in this call
+  return b.ns == 0 && last ? kMonDirect : kMonStage;
+}
+
+// let the E update of step n stage its sample itself
+static void mon_stage_in_e(const fdtd_desc* d, const fdtd_fields* f, const void* ws, const MonBatch& b, FdArgs& fa) {
+  for (int pl = 0; pl < fd_planes(d); ++pl) {
+    const MonArgs m = mon_args(d, f, ws, pl);
+    fa.stage_k[pl] = m.mon_k;
+    fa.stage[pl] = m.ring + static_cast<size_t>(b.ns) * 4 * d->ny * d->nx;
+  }
+}
+
+// the monitor part of step n after its E update (staged: the E update took the
+// sample into the ring)
+static int fd_monitor(const fdtd_desc* d, const fdtd_fields* f, const void* ws, int64_t n, int64_t n_last,
+                      MonBatch& b, bool staged, hipStream_t s) {
+  const MonPlan plan = mon_plan(d, n, n_last, b);
+  if (plan == kMonNone) return MSQD_OK;
+  const bool f32 = d->prec != MSQD_FP64;
+  const bool last = n + d->mon_every > n_last;
   const double tE = static_cast<double>(n + 1) * d->dt, tH = (static_cast<double>(n) + 0.5) * d->dt;
   const int planes = fd_planes(d);
-  if (b.ns == 0 && last) {
+  if (plan == kMonDirect) {
     for (int pl = 0; pl < planes; ++pl) {
       MonArgs m = mon_args(d, f, ws, pl);
       m.tE = tE;
@@ -845,7 +866,7 @@ static int fd_monitor(const fdtd_desc* d, const fdtd_fields* f, const void* ws, 
     }
     return MSQD_OK;
   }
-  for (int pl = 0; pl < planes; ++pl) {
+  for (int pl = 0; !staged && pl < planes; ++pl) {
     MonArgs m = mon_args(d, f, ws, pl);
     m.slot = b.ns;
     const int e = launch_monitor_stage(m, f32, s);
@@ -887,7 +908,7 @@ int fdtd_step(const fdtd_desc* d, const fdtd_fields* f, const void* ws, int64_t 
   e = launch_yee_e(a, f32, s);
   if (e) return check_hip(static_cast<hipError_t>(e), "E update launch");
   MonBatch mb;
-  return fd_monitor(d, f, ws, n, n, mb, s);
+  return fd_monitor(d, f, ws, n, n, mb, false, s);
 }
 
 int flux_readout(const fdtd_desc* d, const fdtd_fields* f, double* flux, void* stream) {
@@ -952,6 +973,14 @@ int map_planes(int32_t n_occ, const int32_t* occ_cell, int32_t nx, int32_t ny, i
   *held_k0 = static_cast<int32_t>(lo);
   *held_nk = static_cast<int32_t>(hi - lo + 1);
   return MSQD_OK;
+}
+
+// a number for each deposit that marks planes (DepArgs::outside), so that marks
+// left by another step are never taken for this one's
+static uint32_t next_tag() {
+  static std::atomic<uint32_t> last{0};
+  const uint32_t t = last.fetch_add(1, std::memory_order_relaxed) + 1;
+  return t ? t : last.fetch_add(1, std::memory_order_relaxed) + 1;   // zero is the empty mark
 }
 
 int coupled_step(const cpl_desc* d, const cpl_state* st, const double* src_values, int64_t n0,
@@ -1048,36 +1077,51 @@ int coupled_step(const cpl_desc* d, const cpl_state* st, const double* src_value
     const int e = launch_deposit(da, f32, s);
     if (e) return check_hip(static_cast<hipError_t>(e), "held current launch");
   }
+  // With a held array the new current goes there, and the E update subtracts it:
+  // the deposit then depends on the molecules alone and shares the H update's
+  // launch, and E is final after its update, which stages the monitor's sample.
   MonBatch mb;
+  const int64_t n_last = n0 + n_steps - 1;
   for (int32_t t = 0; t < n_steps; ++t) {
     const int64_t n = n0 + t;
     const bool mol_now = (n % M) == 0;
+    const bool dep_now = held && mol_now && da.n_occ > 0;
     fa.src_term = -2.0 * src_values[t] / (kEta0 * d->fd.dx);
-    int e = launch_yee_h(fa, f32, s);
-    if (e) return check_hip(static_cast<hipError_t>(e), "H update launch");
+    int e = 0;
+    if (!dep_now) {
+      e = launch_yee_h(fa, f32, s);
+      if (e) return check_hip(static_cast<hipError_t>(e), "H update launch");
+    }
     if (mol_now) {
       timing_mark(true, s);
       rc = launch_mol(&d->qd, ma, s);
       if (rc) return rc;
       timing_mark(false, s);
     }
-    if (held) {
-      // the new current goes into the held array; the E update subtracts it
-      if (mol_now) {
-        da.update = 1;
-        e = launch_deposit(da, f32, s);
-        if (e) return check_hip(static_cast<hipError_t>(e), "deposit launch");
-      }
-      e = launch_yee_e(fa, f32, s);
-      if (e) return check_hip(static_cast<hipError_t>(e), "E update launch");
-    } else {
-      e = launch_yee_e(fa, f32, s);
-      if (e) return check_hip(static_cast<hipError_t>(e), "E update launch");
+    fa.outside = nullptr;
+    if (dep_now) {
+      da.update = 1;
+      da.outside = reinterpret_cast<uint32_t*>(static_cast<char*>(const_cast<void*>(st->fd_ws)) + fa.lay.outside);
+      da.tag = next_tag();
+      e = launch_yee_h_deposit(fa, da, f32, s);
+      if (e) return check_hip(static_cast<hipError_t>(e), "H update and deposit launch");
+      fa.outside = da.outside;
+      fa.tag = da.tag;
+      fa.n_occ = da.n_occ;
+      fa.occ_cell = da.occ_cell;
+    }
+    const bool e_final = held || da.n_occ == 0;
+    const bool staged = e_final && mon_plan(&d->fd, n, n_last, mb) == kMonStage;
+    if (staged) mon_stage_in_e(&d->fd, &st->f, st->fd_ws, mb, fa);
+    e = launch_yee_e(fa, f32, s);
+    if (e) return check_hip(static_cast<hipError_t>(e), "E update launch");
+    fa.stage_k[0] = fa.stage_k[1] = -1;
+    if (!held) {
       da.update = mol_now ? 1 : 0;
       e = launch_deposit(da, f32, s);
       if (e) return check_hip(static_cast<hipError_t>(e), "deposit launch");
     }
-    rc = fd_monitor(&d->fd, &st->f, st->fd_ws, n, n0 + n_steps - 1, mb, s);
+    rc = fd_monitor(&d->fd, &st->f, st->fd_ws, n, n_last, mb, staged, s);
     if (rc) return rc;
   }
   return MSQD_OK;
@@ -1185,15 +1229,13 @@ int coupled_bloch_step(const cpl_bloch_desc* d, const cpl_bloch_state* st, const
     const int64_t n = n0 + t;
     if (!std::isfinite(src_values[t])) return fail(MSQD_EINVAL, "source value not finite");
     fa.src_term = -2.0 * src_values[t] / (kEta0 * d->fd.dx);
-    int e = launch_yee_h(fa, f32, s);
-    if (e) return check_hip(static_cast<hipError_t>(e), "H update launch");
-    e = launch_bloch(ba, f32, s);
-    if (e) return check_hip(static_cast<hipError_t>(e), "Bloch step launch");
+    int e = launch_yee_h_bloch(fa, ba, f32, s);
+    if (e) return check_hip(static_cast<hipError_t>(e), "H update and Bloch step launch");
     e = launch_yee_e(fa, f32, s);
     if (e) return check_hip(static_cast<hipError_t>(e), "E update launch");
     e = launch_deposit(da, f32, s);
     if (e) return check_hip(static_cast<hipError_t>(e), "deposit launch");
-    rc = fd_monitor(&d->fd, &st->f, st->fd_ws, n, n0 + n_steps - 1, mb, s);
+    rc = fd_monitor(&d->fd, &st->f, st->fd_ws, n, n0 + n_steps - 1, mb, false, s);
     if (rc) return rc;
   }
   return MSQD_OK;

@@ -9,6 +9,7 @@ struct FdLayout {
   size_t bE, aE, kE, bH, aH, kH;      // double [nz] CPML profiles (kE, kH hold 1/kappa)
   size_t bEf, aEf, kEf, bHf, aHf, kHf; // float [nz]
   size_t freqs;                        // double [n_freq]
+  size_t outside;                      // uint32 [nz] (DepArgs::outside)
   size_t total;
 };
 FdLayout fd_layout(const fdtd_desc* d);
@@ -27,10 +28,27 @@ struct FdArgs {
   // planes held_k0 .. held_k0 + held_nk - 1 for components c < held_nc
   const void* held;
   int held_k0, held_nk, held_nc;       // held_nc = 0: none
+  // monitor samples the E update stages itself: plane stage_k[i] (-1: none)
+  // into the ring slot stage[i] ([4][ny][nx])
+  int stage_k[2];
+  double* stage[2];
+  // planes that the deposit beside this step's H update marked with `tag`
+  // (DepArgs::outside), or nullptr; their occupied cells, of which held_nc
+  // components turn to NaN
+  const uint32_t* outside;
+  uint32_t tag;
+  int n_occ;
+  const int* occ_cell;
 };
 
+struct DepArgs;
+struct BlochArgs;
 int launch_yee_h(const FdArgs& a, bool f32, hipStream_t s);
 int launch_yee_e(const FdArgs& a, bool f32, hipStream_t s);
+// the H update together with a part of the step that is independent of it: the
+// deposit into the held array, or the emitters' step
+int launch_yee_h_deposit(const FdArgs& a, const DepArgs& dep, bool f32, hipStream_t s);
+int launch_yee_h_bloch(const FdArgs& a, const BlochArgs& bl, bool f32, hipStream_t s);
 
 // samples staged behind the accumulators before one pass folds them in
 constexpr int kMonRing = 8;
@@ -77,6 +95,11 @@ struct DepArgs {
   void* held;
   int held_k0, held_nk;
   long plane;                          // nx ny
+  // a cell outside the held planes: nullptr: its E components are set to NaN
+  // here; else (beside the H update, which reads E) its plane's entry is set to
+  // `tag`, and the E update sets them
+  uint32_t* outside;
+  uint32_t tag;
 };
 int launch_deposit(const DepArgs& a, bool f32, hipStream_t s);
 

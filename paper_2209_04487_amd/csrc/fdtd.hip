@@ -5,6 +5,7 @@
 // Each update is a bandwidth-bound stencil: one lane per cell, x fastest so
 // that neighbouring lanes touch neighbouring addresses; the +-1 neighbours in
 // y and z come from cache.
+#include "bloch.h"
 #include "fdtd.h"
 
 namespace msqd {
@@ -37,7 +38,7 @@ __device__ __forceinline__ const T* prof(const FdArgs& a, size_t off_d, size_t o
     return reinterpret_cast<const T*>(a.ws + off_f);
 }
 
-// Launch geometry of both updates: blockIdx.y is the z plane, blockIdx.x a
+// Launch geometry of both updates: blockIdx.y gives the z plane, blockIdx.x a
 // run of 256 cells of that plane in x-fastest order, and the in-plane (i, j)
 // come from 32-bit arithmetic.
 //
@@ -48,7 +49,7 @@ __device__ __forceinline__ const T* prof(const FdArgs& a, size_t off_d, size_t o
 // eighth of every plane's runs (a strip of y rows, the same in all planes, the
 // number of runs padded to a multiple of eight): all XCDs still sweep the
 // planes together, and the neighbours of a strip hit the XCD's own L2.  The E
-// update takes the planes in descending order (REV), so that it begins with
+// update takes the planes in descending order, so that it begins with
 // the planes that the H update before it finished with, and the next H update
 // with the E update's last ones.  H + E pair, before -> strips -> both:
 // 60.6 -> 54.7 -> 50.3 us at 192x192x120 FP32 (6.6 TB/s of the two kernels'
@@ -65,14 +66,13 @@ struct CellIdx {
   unsigned p;   // index in the plane
   int i, j, k;
 };
-template <bool REV>
-__device__ __forceinline__ bool cell_of_thread(const FdArgs& a, CellIdx& c) {
+__device__ __forceinline__ bool cell_of_thread(const FdArgs& a, int k, CellIdx& c) {
   const int plane = a.nx * a.ny;
   int run = static_cast<int>(blockIdx.x);
   if (gridDim.x >= kStripRuns) run = (run & 7) * static_cast<int>(gridDim.x >> 3) + (run >> 3);
   const int p = run * static_cast<int>(blockDim.x) + static_cast<int>(threadIdx.x);
   if (p >= plane) return false;
-  c.k = REV ? a.nz - 1 - static_cast<int>(blockIdx.y) : static_cast<int>(blockIdx.y);
+  c.k = k;
   c.j = p / a.nx;
   c.i = p - c.j * a.nx;
   c.p = static_cast<unsigned>(p);
@@ -108,14 +108,71 @@ struct MolTerm<double> {
   __device__ static __forceinline__ double apply(double e, double ce, double h) { return fma(-ce, h, e); }
 };
 
+// ------------------------------------------------- polarisation current
+// Per occupied cell: P^{n+1} = (w e a0 / dx^3) sum_{i in cell} d_i in CSR
+// order, J = (P^{n+1} - P^n)/dt_mol, and E_x at the cell loses
+// dt/(eps0 eps_r) J.  Between molecular updates (multi-rate coupling) only
+// the held J is applied.  With a held array the term (MolTerm) is stored
+// there for the E update to apply (update = 0 then rebuilds the array from
+// J_mol), and a cell outside the held planes sets its E component to NaN.
+template <typename T>
+__device__ __forceinline__ void deposit_cell(const DepArgs& a, int c) {
+  const int nc = a.ncomp;
+  const int cell = a.occ_cell[c];
+  void* fld[3] = {a.Ex, a.Ey, a.Ez};
+  // the cell's loads before its first store: the material bytes may alias
+  // any array, so a load after a store would wait on it
+  int mk[3];
+  double pj[3];   // P_c before the update, or the held J_mol
+  T e_old[3];
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    if (k >= nc) break;
+    mk[k] = a.mat[static_cast<size_t>(k) * a.ncells + cell] & 3;
+    pj[k] = a.update ? a.P_c[static_cast<size_t>(c) * nc + k] : a.J_mol[static_cast<size_t>(c) * nc + k];
+    e_old[k] = a.held ? T(0) : static_cast<const T*>(fld[k])[cell];
+  }
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    if (k >= nc) break;
+    double J;
+    if (a.update) {
+      double s = 0.0;
+      const int b = a.occ_ptr[c], e = a.occ_ptr[c + 1];
+      for (int t = b; t < e; ++t) s += a.d_mol[static_cast<size_t>(a.mol_perm[t]) * nc + k];
+      const double p_new = s * a.pfac;
+      J = (p_new - pj[k]) * a.inv_dt;
+      a.P_c[static_cast<size_t>(c) * nc + k] = p_new;
+      a.J_mol[static_cast<size_t>(c) * nc + k] = J;
+    } else {
+      J = pj[k];
+    }
+    const int m = mk[k];
+    T* E = static_cast<T*>(fld[k]);
+    const T h = MolTerm<T>::held(a.ce[m], J);
+    if (a.held) {
+      const long kc = cell / a.plane;
+      if (kc >= a.held_k0 && kc < a.held_k0 + a.held_nk)
+        static_cast<T*>(a.held)[(static_cast<long>(k) * a.held_nk + kc - a.held_k0) * a.plane +
+                                (cell - kc * a.plane)] = h;
+      else if (a.outside)
+        a.outside[kc] = a.tag;
+      else
+        E[cell] = __builtin_nan("");
+    } else {
+      E[cell] = MolTerm<T>::apply(e_old[k], static_cast<T>(a.ce[m]), h);
+    }
+  }
+}
+
 // H^{n+1/2} = H^{n-1/2} - (dt/mu0) curl E^n, with the CPML stretching of the
 // z derivatives: d/dz -> (1/kappa) d/dz + psi, psi <- b psi + a d/dz.
 // Every load is issued before the first store (the arrays are distinct), so
 // the loads of a cell overlap instead of waiting behind the stores.
 template <typename T>
-__global__ __launch_bounds__(256) void yee_h_kernel(FdArgs a) {
+__device__ __forceinline__ void yee_h_block(const FdArgs& a, int plane_k) {
   CellIdx cl;
-  if (!cell_of_thread<false>(a, cl)) return;
+  if (!cell_of_thread(a, plane_k, cl)) return;
   const int nx = a.nx, ny = a.ny, nz = a.nz;
   const int k = cl.k;
   const unsigned p = cl.p;
@@ -166,6 +223,59 @@ __global__ __launch_bounds__(256) void yee_h_kernel(FdArgs a) {
   Hz[p] = hz - cH * (dEy_dx - dEx_dy);
 }
 
+template <typename T>
+__global__ __launch_bounds__(256) void yee_h_kernel(FdArgs a) {
+  yee_h_block<T>(a, static_cast<int>(blockIdx.y));
+}
+
+// The H update with a second, independent part of the coupled step in the first
+// `rows` rows of its grid, which spares that part its launch and its tail: H^{n+1/2}
+// reads E^n and writes H only.
+//  - the deposit into the held array, one occupied cell per thread, after the
+//    molecular step (3 launches per coupled step instead of 4; the deposit alone
+//    took 4 us at 64 molecules and 7 us at 100,000, most of it latency);
+//  - the step of the two-level emitters, one emitter per thread (10 us at 691,200).
+__device__ __forceinline__ int extra_index() {
+  return static_cast<int>((blockIdx.y * gridDim.x + blockIdx.x) * blockDim.x + threadIdx.x);
+}
+template <typename T>
+__global__ __launch_bounds__(256) void yee_h_deposit_kernel(FdArgs a, DepArgs dep, int rows) {
+  if (static_cast<int>(blockIdx.y) < rows) {
+    const int c = extra_index();
+    if (c < dep.n_occ) deposit_cell<T>(dep, c);
+    return;
+  }
+  yee_h_block<T>(a, static_cast<int>(blockIdx.y) - rows);
+}
+template <typename T>
+__global__ __launch_bounds__(256) void yee_h_bloch_kernel(FdArgs a, BlochArgs bl, int rows) {
+  if (static_cast<int>(blockIdx.y) < rows) {
+    const int i = extra_index();
+    if (i < bl.n) bloch_emitter<T>(bl, i);
+    return;
+  }
+  yee_h_block<T>(a, static_cast<int>(blockIdx.y) - rows);
+}
+
+template <typename T>
+__global__ __launch_bounds__(256) void deposit_kernel(DepArgs a) {
+  const int c = blockIdx.x * blockDim.x + threadIdx.x;
+  if (c < a.n_occ) deposit_cell<T>(a, c);
+}
+
+// whether a cell is occupied (occ is increasing)
+__device__ __forceinline__ bool occupied(const int* occ, int n_occ, long cell) {
+  int lo = 0, hi = n_occ;
+  while (lo < hi) {
+    const int mid = lo + (hi - lo) / 2;
+    if (occ[mid] < cell)
+      lo = mid + 1;
+    else
+      hi = mid;
+  }
+  return lo < n_occ && occ[lo] == cell;
+}
+
 // Drude current (centred form of Eq. (2)) and
 // E^{n+1} = E^n + dt/(eps0 eps_r) [curl H^{n+1/2} - J_D^{n+1/2} - J_src].
 // E_x, E_y at k = 0 stay zero (the grid ends on tangential E = 0).
@@ -173,7 +283,7 @@ __global__ __launch_bounds__(256) void yee_h_kernel(FdArgs a) {
 template <typename T>
 __global__ __launch_bounds__(256) void yee_e_kernel(FdArgs a) {
   CellIdx cl;
-  if (!cell_of_thread<true>(a, cl)) return;
+  if (!cell_of_thread(a, a.nz - 1 - static_cast<int>(blockIdx.y), cl)) return;
   const int nx = a.nx, ny = a.ny, nz = a.nz;
   const int k = cl.k;
   const unsigned p = cl.p;
@@ -200,6 +310,9 @@ __global__ __launch_bounds__(256) void yee_e_kernel(FdArgs a) {
   // the held molecular current, on the planes that hold occupied cells (k is
   // uniform over the workgroup)
   const bool in_held = k >= a.held_k0 && k < a.held_k0 + a.held_nk;
+  // occupied cells outside the held planes turn to NaN (marked planes only)
+  const bool poison = !in_held && a.outside != nullptr && a.outside[k] == a.tag &&
+                      occupied(a.occ_cell, a.n_occ, base + p);
   const long hn = static_cast<long>(a.held_nk) * sz;
 #pragma unroll
   for (int c = 0; c < 3; ++c)
@@ -245,7 +358,20 @@ __global__ __launch_bounds__(256) void yee_e_kernel(FdArgs a) {
     if (c < 2 && k == 0) e1 = T(0);
     // the molecular current after the update, as the separate pass applies it
     if (in_held && c < a.held_nc) e1 = MolTerm<T>::apply(e1, ce, hv[c]);
+    if (poison && c < a.held_nc) e1 = __builtin_nan("");
     E[c][p] = e1;
+    e0[c] = e1;
+  }
+  // the monitor's sample of this step, staged from the registers (as mon_values)
+#pragma unroll
+  for (int pl = 0; pl < 2; ++pl) {
+    if (k == a.stage_k[pl]) {
+      double* ring = a.stage[pl];
+      ring[p] = static_cast<double>(e0[0]);
+      ring[sz + p] = static_cast<double>(e0[1]);
+      ring[2 * sz + p] = 0.5 * (static_cast<double>(hx_km) + hx);
+      ring[3 * sz + p] = 0.5 * (static_cast<double>(hy_km) + hy);
+    }
   }
 }
 
@@ -261,6 +387,53 @@ int launch_yee_h(const FdArgs& a, bool f32, hipStream_t s) {
     hipLaunchKernelGGL(yee_h_kernel<float>, yee_grid(a), dim3(256), 0, s, a);
   else
     hipLaunchKernelGGL(yee_h_kernel<double>, yee_grid(a), dim3(256), 0, s, a);
+  return static_cast<int>(hipGetLastError());
+}
+
+// rows of the H update's grid that n extra threads take, or 0 where the grid has
+// no room for them (65,535 rows)
+static int extra_rows(const dim3& g, int n) {
+  const long per = 256L * g.x, rows = (n + per - 1) / per;
+  return rows + g.y <= 65535 ? static_cast<int>(rows) : 0;
+}
+
+int launch_deposit(const DepArgs& a, bool f32, hipStream_t s) {
+  if (a.n_occ <= 0) return 0;
+  const int blocks = (a.n_occ + 255) / 256;
+  if (f32)
+    hipLaunchKernelGGL(deposit_kernel<float>, dim3(blocks), dim3(256), 0, s, a);
+  else
+    hipLaunchKernelGGL(deposit_kernel<double>, dim3(blocks), dim3(256), 0, s, a);
+  return static_cast<int>(hipGetLastError());
+}
+
+int launch_yee_h_deposit(const FdArgs& a, const DepArgs& dep, bool f32, hipStream_t s) {
+  dim3 g = yee_grid(a);
+  const int rows = dep.n_occ > 0 ? extra_rows(g, dep.n_occ) : 0;
+  if (rows == 0) {
+    const int e = launch_deposit(dep, f32, s);
+    return e ? e : launch_yee_h(a, f32, s);
+  }
+  g.y += rows;
+  if (f32)
+    hipLaunchKernelGGL(yee_h_deposit_kernel<float>, g, dim3(256), 0, s, a, dep, rows);
+  else
+    hipLaunchKernelGGL(yee_h_deposit_kernel<double>, g, dim3(256), 0, s, a, dep, rows);
+  return static_cast<int>(hipGetLastError());
+}
+
+int launch_yee_h_bloch(const FdArgs& a, const BlochArgs& bl, bool f32, hipStream_t s) {
+  dim3 g = yee_grid(a);
+  const int rows = bl.n > 0 ? extra_rows(g, bl.n) : 0;
+  if (rows == 0) {
+    const int e = launch_bloch(bl, f32, s);
+    return e ? e : launch_yee_h(a, f32, s);
+  }
+  g.y += rows;
+  if (f32)
+    hipLaunchKernelGGL(yee_h_bloch_kernel<float>, g, dim3(256), 0, s, a, bl, rows);
+  else
+    hipLaunchKernelGGL(yee_h_bloch_kernel<double>, g, dim3(256), 0, s, a, bl, rows);
   return static_cast<int>(hipGetLastError());
 }
 
@@ -465,73 +638,6 @@ __global__ __launch_bounds__(256) void flux_kernel(int plane, int n_freq, const 
 int launch_flux(int nx, int ny, int n_freq, const double* dft, double* flux, hipStream_t s) {
   hipLaunchKernelGGL(flux_kernel, dim3(n_freq), dim3(256), 0, s, nx * ny, n_freq,
                      reinterpret_cast<const double2*>(dft), flux);
-  return static_cast<int>(hipGetLastError());
-}
-
-// ------------------------------------------------- polarisation current
-// Per occupied cell: P^{n+1} = (w e a0 / dx^3) sum_{i in cell} d_i in CSR
-// order, J = (P^{n+1} - P^n)/dt_mol, and E_x at the cell loses
-// dt/(eps0 eps_r) J.  Between molecular updates (multi-rate coupling) only
-// the held J is applied.  With a held array the term (MolTerm) is stored
-// there for the E update to apply (update = 0 then rebuilds the array from
-// J_mol), and a cell outside the held planes sets its E component to NaN.
-template <typename T>
-__global__ __launch_bounds__(256) void deposit_kernel(DepArgs a) {
-  const int c = blockIdx.x * blockDim.x + threadIdx.x;
-  if (c >= a.n_occ) return;
-  const int nc = a.ncomp;
-  const int cell = a.occ_cell[c];
-  void* fld[3] = {a.Ex, a.Ey, a.Ez};
-  // the cell's loads before its first store: the material bytes may alias
-  // any array, so a load after a store would wait on it
-  int mk[3];
-  double pj[3];   // P_c before the update, or the held J_mol
-  T e_old[3];
-#pragma unroll
-  for (int k = 0; k < 3; ++k) {
-    if (k >= nc) break;
-    mk[k] = a.mat[static_cast<size_t>(k) * a.ncells + cell] & 3;
-    pj[k] = a.update ? a.P_c[static_cast<size_t>(c) * nc + k] : a.J_mol[static_cast<size_t>(c) * nc + k];
-    e_old[k] = a.held ? T(0) : static_cast<const T*>(fld[k])[cell];
-  }
-#pragma unroll
-  for (int k = 0; k < 3; ++k) {
-    if (k >= nc) break;
-    double J;
-    if (a.update) {
-      double s = 0.0;
-      const int b = a.occ_ptr[c], e = a.occ_ptr[c + 1];
-      for (int t = b; t < e; ++t) s += a.d_mol[static_cast<size_t>(a.mol_perm[t]) * nc + k];
-      const double p_new = s * a.pfac;
-      J = (p_new - pj[k]) * a.inv_dt;
-      a.P_c[static_cast<size_t>(c) * nc + k] = p_new;
-      a.J_mol[static_cast<size_t>(c) * nc + k] = J;
-    } else {
-      J = pj[k];
-    }
-    const int m = mk[k];
-    T* E = static_cast<T*>(fld[k]);
-    const T h = MolTerm<T>::held(a.ce[m], J);
-    if (a.held) {
-      const long kc = cell / a.plane;
-      if (kc >= a.held_k0 && kc < a.held_k0 + a.held_nk)
-        static_cast<T*>(a.held)[(static_cast<long>(k) * a.held_nk + kc - a.held_k0) * a.plane +
-                                (cell - kc * a.plane)] = h;
-      else
-        E[cell] = __builtin_nan("");
-    } else {
-      E[cell] = MolTerm<T>::apply(e_old[k], static_cast<T>(a.ce[m]), h);
-    }
-  }
-}
-
-int launch_deposit(const DepArgs& a, bool f32, hipStream_t s) {
-  if (a.n_occ <= 0) return 0;
-  const int blocks = (a.n_occ + 255) / 256;
-  if (f32)
-    hipLaunchKernelGGL(deposit_kernel<float>, dim3(blocks), dim3(256), 0, s, a);
-  else
-    hipLaunchKernelGGL(deposit_kernel<double>, dim3(blocks), dim3(256), 0, s, a);
   return static_cast<int>(hipGetLastError());
 }
 
