@@ -133,32 +133,26 @@ __device__ __forceinline__ double coupling_adj_mfma(const cx<T>* A, cx<T>* B, in
   return grad;
 }
 
-// chi, the coupling's input, through device memory (over psi^{n+1}, which
-// the reverse sweep no longer needs) instead of a second LDS buffer
-template <typename T>
-constexpr bool adj_chi_in_device_memory(bool next) { return next && sizeof(T) == 8; }
-
 // NEXT: the state after the step (psi^{n+1} = m psi_pre) is given, so the
 // recompute stops at chi = V K psi; otherwise the whole forward step is
 // recomputed to obtain psi_pre.
 // KH: N_J <= kHalfKMaxNJ (two of the four K instructions per product),
 // chosen at launch so that a kernel holds one contraction path.
-template <typename T, int NR, bool NEXT, bool KH>
+template <int NR, bool NEXT, bool KH>
 __global__ __launch_bounds__(512) void mol_adj_kernel(MolAdjArgs a) {
+  typedef double T;
   constexpr int R1 = FftShape<NR, T>::R1, R2 = FftShape<NR, T>::R2;
   constexpr int LS = line_stride<NR, T>();
   extern __shared__ __align__(16) unsigned char smem[];
   const int nj = a.nj;
   const int L = 2 * nj;
-  // LDS: B (the lines) and A (chi).  complex128 with psi^{n+1} given keeps
-  // chi in device memory instead (below): a molecule then needs half the LDS
-  // and four instead of two share a CU, 18% faster for the FP64 gradient; in
-  // complex64 the device-memory round trip of chi measured 4% slower than the
-  // LDS copy, so chi stays in LDS there.
-  constexpr bool CHI_DEV = adj_chi_in_device_memory<T>(NEXT);
+  // LDS: B (the lines) and A (chi).  With psi^{n+1} given chi goes through
+  // device memory instead (over psi^{n+1}, which the reverse sweep no longer
+  // needs): a molecule then needs half the LDS and four instead of two share a
+  // CU, 18% faster.
   cx<T>* B = reinterpret_cast<cx<T>*>(smem);
   cx<T>* A = B + L * LS;
-  double* red = reinterpret_cast<double*>(smem + (CHI_DEV ? 1 : 2) * sizeof(cx<T>) * L * LS);
+  double* red = reinterpret_cast<double*>(smem + (NEXT ? 1 : 2) * sizeof(cx<T>) * L * LS);
   const int mol = blockIdx.x;
   const int tid = threadIdx.x;
   const int nthr = blockDim.x;
@@ -169,14 +163,13 @@ __global__ __launch_bounds__(512) void mol_adj_kernel(MolAdjArgs a) {
   const int J_of_line = line - s_of_line * nj;
 
   const char* ws = a.ws;
-  const bool dbl = sizeof(T) == 8;
-  const cx<T>* kin = reinterpret_cast<const cx<T>*>(ws + (dbl ? a.lay.kin_d : a.lay.kin_f));
-  const cx<T>* tw = reinterpret_cast<const cx<T>*>(ws + (dbl ? a.lay.tw_d : a.lay.tw_f));
-  const cx<T>* vph = reinterpret_cast<const cx<T>*>(ws + (dbl ? a.lay.vph_d : a.lay.vph_f));
-  const T* frag = reinterpret_cast<const T*>(ws + (dbl ? a.lay.tmfrag_d : a.lay.tmfrag_f));
-  const T* xk = reinterpret_cast<const T*>(ws + (dbl ? a.lay.x_d : a.lay.x_f));
-  const T* mudt = reinterpret_cast<const T*>(ws + (dbl ? a.lay.mudt_d : a.lay.mudt_f));
-  const T* mask = reinterpret_cast<const T*>(ws + (dbl ? a.lay.mask_d : a.lay.mask_f));
+  const cx<T>* kin = reinterpret_cast<const cx<T>*>(ws + a.lay.kin_d);
+  const cx<T>* tw = reinterpret_cast<const cx<T>*>(ws + a.lay.tw_d);
+  const cx<T>* vph = reinterpret_cast<const cx<T>*>(ws + a.lay.vph_d);
+  const T* frag = reinterpret_cast<const T*>(ws + a.lay.tmfrag_d);
+  const T* xk = reinterpret_cast<const T*>(ws + a.lay.x_d);
+  const T* mudt = reinterpret_cast<const T*>(ws + a.lay.mudt_d);
+  const T* mask = reinterpret_cast<const T*>(ws + a.lay.mask_d);
   const double* mu = reinterpret_cast<const double*>(ws + a.lay.mu_d);
   const double* cj = reinterpret_cast<const double*>(ws + a.lay.cj_d);
 
@@ -190,19 +183,19 @@ __global__ __launch_bounds__(512) void mol_adj_kernel(MolAdjArgs a) {
   // ---- forward recompute: chi = V K psi; psi_pre = K V C(chi), or
   // psi^{n+1} = m psi_pre read back (v then holds psi^{n+1})
   cx<T> v[R1];
-  cx<T>* chi_g = reinterpret_cast<cx<T>*>(a.psi_np1) + base;   // CHI_DEV: chi replaces psi^{n+1} here
+  cx<T>* chi_g = reinterpret_cast<cx<T>*>(a.psi_np1) + base;   // NEXT: chi replaces psi^{n+1} here
   if (active) {
 #pragma unroll
     for (int p = 0; p < R1; ++p) v[p] = psi[loff + R2 * p];
     kinetic_half<T, NR>(v, slot, q, kin, tw);
 #pragma unroll
     for (int p = 0; p < R1; ++p) v[p] = phase_mul(v[p], vph[loff + R2 * p]);
-    if constexpr (!CHI_DEV) {
+    if constexpr (!NEXT) {
 #pragma unroll
       for (int p = 0; p < R1; ++p) A[line * LS + q + R2 * p] = v[p];
     }
   }
-  if constexpr (CHI_DEV) {
+  if constexpr (NEXT) {
     // psi^{n+1} into this line's LDS row (the transform above is done with
     // it), then chi over psi^{n+1} in device memory: each lane reads an
     // element before it writes it, and only this workgroup touches this
@@ -214,16 +207,6 @@ __global__ __launch_bounds__(512) void mol_adj_kernel(MolAdjArgs a) {
       for (int p = 0; p < R1; ++p) chi_g[loff + R2 * p] = v[p];
 #pragma unroll
       for (int p = 0; p < R1; ++p) v[p] = B[line * LS + q + R2 * p];
-    }
-    __syncthreads();
-  } else if constexpr (NEXT) {
-    const cx<T>* nxt = chi_g;
-    if (active) {
-#pragma unroll
-      for (int p = 0; p < R1; ++p) {
-        v[p] = nxt[loff + R2 * p];
-        B[line * LS + q + R2 * p] = v[p];
-      }
     }
     __syncthreads();
   } else {
@@ -278,7 +261,7 @@ __global__ __launch_bounds__(512) void mol_adj_kernel(MolAdjArgs a) {
   }
   __syncthreads();
   double grad;
-  if constexpr (CHI_DEV)
+  if constexpr (NEXT)
     grad = coupling_adj_mfma<T, NR, true, NR, KH>(chi_g, B, LS, nj, frag, xk, mudt, E);
   else
     grad = coupling_adj_mfma<T, NR, true, LS, KH>(A, B, LS, nj, frag, xk, mudt, E);
@@ -298,30 +281,340 @@ __global__ __launch_bounds__(512) void mol_adj_kernel(MolAdjArgs a) {
   if (tid == 0) a.lE[mol] = sums[0];
 }
 
-// LDS per workgroup: two line buffers, or one where chi goes through device
-// memory
-static size_t adj_lds_bytes(int n_r, int nj, bool f32, bool next) {
+// ---------------------------------------------------- molecules, complex64
+// The same for complex64 lines, in the exchange rounds of the forward step (half
+// the radial points at a time where fwd_split is two).  What bounds it is the
+// latency of its phases (loads, transforms, contraction) with few wavefronts to
+// hide it: two whole-line LDS buffers (30 KB at n_r = 128, J <= 6) left a CU 2.5
+// wavefronts per execution unit, and at n_r = 256 the kernel spilled.  Here a
+// round's chi and lambda are in LDS and the other round's in registers, the
+// tables are staged, and the node rotation is taken on its two independent pairs
+// of parts in turn (coupling_adj_pairs), which halves a tile's registers.  Reverse
+// step with psi^{n+1} given, whole-line form -> this one: 503 -> 394 us (20,000
+// molecules, n_r = 128, J <= 6; the three reads and one write of 287 MB are 221 us
+// at a copy's rate), 505 -> 447 (12,000, J <= 10), 1027 -> 553 (10,000, n_r = 256,
+// J <= 6), 1155 -> 637 (6,000, J <= 10), 1002 -> 703 (8,000, n_r = 512, J <= 3),
+// 363 -> 307 (30,000, n_r = 64, J <= 7).
+
+// One round of the coupling's adjoint (ADJ) or of the coupling (segment
+// recompute).  The rotation takes (g re, e im) and (e re, g im) to themselves:
+//   Q_x = c P_x - s P_y, Q_y = c P_y + s P_x;
+//   dY/dE share -(L_x Q_y - L_y Q_x); O_x = c L_x + s L_y, O_y = c L_y - s L_x.
+// A: chi; B: the adjoint at the coupling's output, on return at its input (the
+// recompute: C(E) chi).  Rows as in the forward step; rows J >= nj read row
+// nj - 1, whose column of T is zero.
+template <int NR, bool ADJ, bool KH>
+__device__ __forceinline__ double coupling_adj_pairs(const cx<float>* A, cx<float>* B, int nj, int r0,
+                                                     const float* __restrict__ frag, const float* __restrict__ x,
+                                                     const float* __restrict__ mudt, float E) {
+  typedef MfmaK4<float> MK;
+  typedef MK::acc acc_t;
+  constexpr int NK = KH ? 2 : 4, NRH = NR / fwd_split<NR, float>();
+  const int lane = fresh_lane();
+  const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) >> 6);
+  const int nwaves = (blockDim.x + 63) >> 6;
+  const int col = lane & 15;
+  const int grp = lane >> 4;
+  float Tf[NK], Tt[NK], xk[4];
+  int og[NK], oe[NK];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int J = mf_row<float, KH>(grp, i);
+    xk[i] = (i < NK && J < nj) ? x[J] : 0.0f;
+    if (i < NK) {
+      Tf[i < NK ? i : 0] = frag[(0 * 64 + lane) * 4 + i];
+      Tt[i < NK ? i : 0] = frag[(1 * 64 + lane) * 4 + i];
+      const int Jc = J < nj ? J : nj - 1;
+      og[i < NK ? i : 0] = lds_row<NR, float>(Jc);
+      oe[i < NK ? i : 0] = lds_row<NR, float>(nj + Jc);
+    }
+  }
+  double grad = 0.0;
+  const acc_t z = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+  for (int tile = wave; tile * 16 < NRH; tile += nwaves) {
+    const int rl = tile * 16 + col;
+    const int r = r0 + rl;
+    cx<float> ag[NK], ae[NK], bg[NK], be[NK];
+#pragma unroll
+    for (int i = 0; i < NK; ++i) {
+      ag[i] = A[og[i] + rl];
+      ae[i] = A[oe[i] + rl];
+      if constexpr (ADJ) {
+        bg[i] = B[og[i] + rl];
+        be[i] = B[oe[i] + rl];
+      }
+    }
+    const float mr = mudt[r];
+    float sn[4], vs[4];
+    sin_vers_tile<NR>(mr * E, xk, sn, vs);
+    double gl = 0.0;
+    acc_t out[2][2];
+#pragma unroll
+    for (int pr = 0; pr < 2; ++pr) {
+      acc_t P = z, Q = z, L = z, M = z;
+#pragma unroll
+      for (int i = 0; i < NK; ++i) {
+        P = MK::mma(Tf[i], pr == 0 ? ag[i].x : ae[i].x, P);
+        Q = MK::mma(Tf[i], pr == 0 ? ae[i].y : ag[i].y, Q);
+        if constexpr (ADJ) {
+          L = MK::mma(Tf[i], pr == 0 ? bg[i].x : be[i].x, L);
+          M = MK::mma(Tf[i], pr == 0 ? be[i].y : bg[i].y, M);
+        }
+      }
+#pragma unroll
+      for (int i = 0; i < NK; ++i) {
+        const float c = 1.0f - vs[i];
+        const float qx = c * P[i] - sn[i] * Q[i], qy = c * Q[i] + sn[i] * P[i];
+        if constexpr (ADJ) {
+          gl -= static_cast<double>(xk[i]) * static_cast<double>(L[i] * qy - M[i] * qx);
+          P[i] = c * L[i] + sn[i] * M[i];
+          Q[i] = c * M[i] - sn[i] * L[i];
+        } else {
+          P[i] = qx;
+          Q[i] = qy;
+        }
+      }
+      out[pr][0] = z;
+      out[pr][1] = z;
+#pragma unroll
+      for (int i = 0; i < NK; ++i) {
+        out[pr][0] = MK::mma(Tt[i], P[i], out[pr][0]);
+        out[pr][1] = MK::mma(Tt[i], Q[i], out[pr][1]);
+      }
+    }
+    if constexpr (ADJ) grad += static_cast<double>(mr) * gl;
+#pragma unroll
+    for (int i = 0; i < NK; ++i) {
+      if (mf_row<float, KH>(grp, i) < nj) {
+        B[og[i] + rl] = {out[0][0][i], out[1][1][i]};
+        B[oe[i] + rl] = {out[1][0][i], out[0][1][i]};
+      }
+    }
+  }
+  return grad;
+}
+
+// LDS of the complex64 form: transform tables (compact twiddles), the round's
+// lambda rows and chi rows, the reduction scratch
+template <int NR>
+struct Adj32Shape {
+  typedef StagedTables<NR, float, true, false> TBL;
+  static constexpr int SP = fwd_split<NR, float>();
+  static size_t buf_bytes(int nj) {
+    return (sizeof(cx<float>) * static_cast<size_t>(lds_line_start(2 * nj, fwd_line_stride<NR, float>(), 8)) + 15) / 16 * 16;
+  }
+  static size_t bytes(int nj) { return TBL::bytes + 2 * buf_bytes(nj) + 16 * sizeof(double); }
+};
+
+// Wavefronts per execution unit: four where the lines' 16 points per lane (twice:
+// chi and lambda) and a half-K tile fit 128 registers, three with the full-K tile,
+// two at 32 points per lane (more spilled 54 to 141 registers: 553 -> 725 us for
+// 10,000 molecules at n_r = 256, J <= 6; 394 -> 435 us at three instead of four
+// for 20,000 at n_r = 128).
+template <int NR, bool KH>
+constexpr int adj32_waves() { return FftShape<NR, float>::R1 > 16 ? 2 : (KH ? 4 : 3); }
+
+template <int NR, bool NEXT, bool KH>
+__global__ __launch_bounds__(512)
+__attribute__((amdgpu_waves_per_eu(adj32_waves<NR, KH>()))) void mol_adj32_kernel(MolAdjArgs a) {
+  typedef Adj32Shape<NR> S;
+  typedef typename S::TBL TBL;
+  constexpr int R1 = FftShape<NR, float>::R1, R2 = FftShape<NR, float>::R2;
+  constexpr int SP = S::SP, PH = R1 / SP, NRH = NR / SP, TWC = TBL::TWC;
+  extern __shared__ __align__(16) unsigned char smem[];
+  const int nj = a.nj;
+  const int L = 2 * nj;
+  const int buf = (lds_row<NR, float>(L) + 1) / 2 * 2;
+  cx<float>* kin = reinterpret_cast<cx<float>*>(smem);
+  cx<float>* tw = kin + NR;
+  float* mask = reinterpret_cast<float*>(tw + TBL::tw_elems);
+  cx<float>* B = reinterpret_cast<cx<float>*>(smem + TBL::bytes);
+  cx<float>* A = B + buf;
+  double* red = reinterpret_cast<double*>(A + buf);
+  const int mol = blockIdx.x;
+  const int tid = threadIdx.x;
+  const int line = tid / R2;
+  const int q = tid - line * R2;
+  const bool active = line < L;
+  const int s_of_line = line >= nj ? 1 : 0;
+  const int J_of_line = line - s_of_line * nj;
+
+  const char* ws = a.ws;
+  const cx<float>* vph = reinterpret_cast<const cx<float>*>(ws + a.lay.vph_f);
+  const float* frag = reinterpret_cast<const float*>(ws + a.lay.tmfrag_f);
+  const float* xk = reinterpret_cast<const float*>(ws + a.lay.x_f);
+  const float* mudt = reinterpret_cast<const float*>(ws + a.lay.mudt_f);
+  const double* mu = reinterpret_cast<const double*>(ws + a.lay.mu_d);
+  const double* cj = reinterpret_cast<const double*>(ws + a.lay.cj_d);
+
+  const float E = static_cast<float>(a.E_mol[mol]);
+  const size_t base = static_cast<size_t>(mol) * L * NR;
+  const cx<float>* psi = static_cast<const cx<float>*>(a.psi_n) + base;
+  const cx<float>* nxt = static_cast<const cx<float>*>(a.psi_np1) + base;
+  cx<float>* lpsi = static_cast<cx<float>*>(a.lpsi) + base;
+  cx<float>* slot = B + lds_row<NR, float>(line);    // this line's row of the round
+  cx<float>* aslot = A + lds_row<NR, float>(line);
+  const int loff = line * NR + q;
+
+  // ---- chi = V K psi, and psi_pre = K V C(chi) or psi^{n+1} = m psi_pre (v)
+  cx<float> ch[R1], v[R1];
+  if (active) {
+#pragma unroll
+    for (int p = 0; p < R1; ++p) ch[p] = psi[loff + R2 * p];
+  }
+  stage_tables_to_lds<NR, float, true>(kin, tw, mask, reinterpret_cast<const cx<float>*>(ws + a.lay.kin_f),
+                                       reinterpret_cast<const cx<float>*>(ws + a.lay.tw_f),
+                                       reinterpret_cast<const float*>(ws + a.lay.mask_f));
+  __syncthreads();
+  if (active) {
+    kinetic_half<float, NR, false, SP, TWC>(ch, slot, q, kin, tw);
+#pragma unroll
+    for (int p = 0; p < R1; ++p) ch[p] = phase_mul(ch[p], vph[loff + R2 * p]);
+  }
+  if constexpr (NEXT) {
+    if (active) {
+#pragma unroll
+      for (int p = 0; p < R1; ++p) v[p] = nxt[loff + R2 * p];
+    }
+  } else {
+#pragma unroll
+    for (int h = 0; h < SP; ++h) {
+      if (active) {
+#pragma unroll
+        for (int pp = 0; pp < PH; ++pp) aslot[q + R2 * pp] = ch[h * PH + pp];
+      }
+      __syncthreads();
+      coupling_adj_pairs<NR, false, KH>(A, B, nj, h * NRH, frag, xk, mudt, E);
+      __syncthreads();
+      if (active) {
+#pragma unroll
+        for (int pp = 0; pp < PH; ++pp) {
+          const int p = h * PH + pp;
+          v[p] = phase_mul(slot[q + R2 * pp], vph[loff + R2 * p]);
+        }
+      }
+    }
+    if (active) kinetic_half<float, NR, false, SP, TWC>(v, slot, q, kin, tw);   // psi_pre (before the absorber)
+  }
+
+  // ---- reverse: dipole and absorber terms (lambda replaces v), then K^H V^H
+  const double ld = a.ld ? a.ld[mol] : 0.0;
+  const double lab = a.labs[mol];
+  const float cjm = (active && J_of_line > 0) ? static_cast<float>(cj[J_of_line - 1]) : 0.0f;
+  const float cjp = (active && J_of_line + 1 < nj) ? static_cast<float>(cj[J_of_line]) : 0.0f;
+  const float fd = static_cast<float>(2.0 * a.dr * ld);
+  const float fa = static_cast<float>(2.0 * a.dr * lab);
+  // rows of the other state's neighbours J - 1 and J + 1 (their own line where
+  // there is none: its factor is zero)
+  const int sb = (1 - s_of_line) * nj;
+  const cx<float>* rowm = B + lds_row<NR, float>(J_of_line > 0 ? sb + J_of_line - 1 : line);
+  const cx<float>* rowp = B + lds_row<NR, float>(J_of_line + 1 < nj ? sb + J_of_line + 1 : line);
+#pragma unroll
+  for (int h = 0; h < SP; ++h) {
+    if (h > 0) __syncthreads();
+    if (active) {
+#pragma unroll
+      for (int pp = 0; pp < PH; ++pp) {
+        const cx<float> w = v[h * PH + pp];
+        slot[q + R2 * pp] = NEXT ? w : cscale(w, mask[q + R2 * (h * PH + pp)]);
+      }
+    }
+    __syncthreads();
+    if (active) {
+#pragma unroll
+      for (int pp = 0; pp < PH; ++pp) {
+        const int p = h * PH + pp, r = q + R2 * p, rl = q + R2 * pp;
+        cx<float> l = lpsi[loff + R2 * p];
+        // D psi' with D = mu12(r) <J|cos|J'> sigma_x
+        const cx<float> dpsi = cscale(rowm[rl], cjm) + cscale(rowp[rl], cjp);
+        l = l + cscale(dpsi, fd * static_cast<float>(mu[r]));
+        const float m = mask[r];
+        // absorber term 2 dr labs (1 - m^2) psi_pre, with psi_pre = psi^{n+1} / m
+        // when the state after the step was given (m > 0 on the periodic grid)
+        const float wa = NEXT ? (1.0f - m * m) / m : (1.0f - m * m);
+        v[p] = cscale(l, m) + cscale(v[p], fa * wa);
+      }
+    }
+  }
+  __syncthreads();
+  if (active) {
+    kinetic_half<float, NR, true, SP, TWC>(v, slot, q, kin, tw);
+#pragma unroll
+    for (int p = 0; p < R1; ++p) v[p] = phase_mul_conj(v[p], vph[loff + R2 * p]);
+  }
+  double grad = 0.0;
+#pragma unroll
+  for (int h = 0; h < SP; ++h) {
+    if (active) {
+#pragma unroll
+      for (int pp = 0; pp < PH; ++pp) {
+        aslot[q + R2 * pp] = ch[h * PH + pp];
+        slot[q + R2 * pp] = v[h * PH + pp];
+      }
+    }
+    __syncthreads();
+    grad += coupling_adj_pairs<NR, true, KH>(A, B, nj, h * NRH, frag, xk, mudt, E);
+    __syncthreads();
+    if (active) {
+#pragma unroll
+      for (int pp = 0; pp < PH; ++pp) {
+        const int p = h * PH + pp;
+        v[p] = phase_mul_conj(slot[q + R2 * pp], vph[loff + R2 * p]);
+      }
+    }
+  }
+  if (active) {
+    kinetic_half<float, NR, true, SP, TWC>(v, slot, q, kin, tw);
+#pragma unroll
+    for (int p = 0; p < R1; ++p) lpsi[loff + R2 * p] = v[p];
+  }
+  double sums[1] = {grad};
+  block_sums<1>(sums, red);
+  if (tid == 0) a.lE[mol] = sums[0];
+}
+
+template <int NR, bool NEXT, bool KH>
+static int launch_mol_adj32(const MolAdjArgs& a, hipStream_t s) {
+  const int threads = (2 * a.nj * FftShape<NR, float>::R2 + 63) / 64 * 64;
+  const size_t shm = Adj32Shape<NR>::bytes(a.nj);
+  static std::atomic<unsigned long long> lds_set{0};
+  if (shm > 64 * 1024) {
+    const hipError_t e = allow_large_lds(reinterpret_cast<const void*>(&mol_adj32_kernel<NR, NEXT, KH>), lds_set);
+    if (e != hipSuccess) return static_cast<int>(e);
+  }
+  hipLaunchKernelGGL((mol_adj32_kernel<NR, NEXT, KH>), dim3(a.n_mol), dim3(threads), shm, s, a);
+  return static_cast<int>(hipGetLastError());
+}
+
+// LDS that a molecule's two line buffers take: the limit on what is accepted (the
+// complex64 form needs about half of it)
+size_t mol_adj_lds_bytes(int n_r, int nj, bool f32) {
   const size_t el = f32 ? 8 : 16;
   const int r2 = n_r / fft_r1(n_r, static_cast<int>(el / 2));
-  const bool one = f32 ? adj_chi_in_device_memory<float>(next) : adj_chi_in_device_memory<double>(next);
-  return (one ? 1 : 2) * el * static_cast<size_t>(2 * nj) * (n_r + r2) + 16 * 4 * sizeof(double);
+  return 2 * el * static_cast<size_t>(2 * nj) * (n_r + r2) + 16 * 4 * sizeof(double);
 }
-size_t mol_adj_lds_bytes(int n_r, int nj, bool f32) { return adj_lds_bytes(n_r, nj, f32, false); }
+
+template <int NR, bool NEXT, bool KH>
+static int launch_mol_adj64(const MolAdjArgs& a, hipStream_t s) {
+  const int threads = (2 * a.nj * FftShape<NR, double>::R2 + 63) / 64 * 64;
+  const size_t line = sizeof(cx<double>) * line_stride<NR, double>();
+  const size_t shm = (NEXT ? 1 : 2) * line * 2 * a.nj + 16 * 4 * sizeof(double);
+  static std::atomic<unsigned long long> lds_set{0};
+  if (shm > 64 * 1024) {
+    const hipError_t e = allow_large_lds(reinterpret_cast<const void*>(&mol_adj_kernel<NR, NEXT, KH>), lds_set);
+    if (e != hipSuccess) return static_cast<int>(e);
+  }
+  hipLaunchKernelGGL((mol_adj_kernel<NR, NEXT, KH>), dim3(a.n_mol), dim3(threads), shm, s, a);
+  return static_cast<int>(hipGetLastError());
+}
 
 template <typename T, int NR, bool NEXT, bool KH>
 static int launch_mol_adj_n(const MolAdjArgs& a, hipStream_t s) {
-  constexpr int R2 = FftShape<NR, T>::R2;
-  const int L = 2 * a.nj;
-  int threads = ((L * R2 + 63) / 64) * 64;
-  if (threads < 64) threads = 64;
-  const size_t shm = adj_lds_bytes(NR, a.nj, sizeof(T) == 4, NEXT);
-  static std::atomic<unsigned long long> lds_set{0};
-  if (shm > 64 * 1024) {
-    const hipError_t e = allow_large_lds(reinterpret_cast<const void*>(&mol_adj_kernel<T, NR, NEXT, KH>), lds_set);
-    if (e != hipSuccess) return static_cast<int>(e);
-  }
-  hipLaunchKernelGGL((mol_adj_kernel<T, NR, NEXT, KH>), dim3(a.n_mol), dim3(threads), shm, s, a);
-  return static_cast<int>(hipGetLastError());
+  if constexpr (sizeof(T) == 4)
+    return launch_mol_adj32<NR, NEXT, KH>(a, s);
+  else
+    return launch_mol_adj64<NR, NEXT, KH>(a, s);
 }
 
 template <typename T, int NR>
