@@ -10,7 +10,8 @@
 // diagonalised once on the host, D_z|m' = Q diag(x) Q^T, so that the coupling
 // at a radial point is: rotate to the field frame (U^H), transform each m'
 // block to the eigenbasis of cos(theta) (Q^T), rotate the (g, e) pair of every
-// eigenvector by the angle mu12(r) dt e x_k, and transform back.  The Wigner
+// eigenvector by the angle mu12(r) dt e x_k, and transform back (the kernel forms
+// the product U Q per molecule and uses the pairs +-x_k).  The Wigner
 // matrices d^j(beta) are formed per molecule from the eigenvectors of J_x:
 // exp(-i beta J_y) = exp(-i pi/2 J_z) exp(-i beta J_x) exp(i pi/2 J_z), so
 //   d^j_{m m'}(beta) = sum_k O_{m k} O_{m' k} cos(pi/2 (m' - m) - beta mu_k),

@@ -1,21 +1,23 @@
 // The molecular step in the rotational basis |j, m>, 2 <= j_max <= 5, with
 // all three field components: one workgroup per molecule, (j_max + 1)^2
 // lines per electronic state.  The coupling is the exact exponential on the
-// truncated basis, applied as a rotation to the field frame, per-m' Gauss
-// transforms of cos(theta), the 2x2 rotation of every eigenvector's (g, e)
-// pair, and the way back (the construction and the tables are described in
-// mol_jmg.h).
+// truncated basis, applied as a rotation of the (g, e) parts of pairs of
+// eigenvectors of the direction cosine along the field (the construction is
+// described at jmg_couple, the tables in mol_jmg.h).
 //
 // Work decomposition: the line layout and the kinetic half-steps are those
 // of the m = 0 step (R2 lanes per line, R1 values per lane, in-wave
-// four-step FFT).  The lines go through LDS in SP rounds of radial points;
-// in each round the coupling runs as three stages over the LDS rows:
-//   A: per (state, j, r): y_m' = sum_m d^j_{m m'}(beta) e^{i m alpha} psi_m,
-//   B: per (m', r): chi = Q^T y for both states, the increment of the
-//      rotation, back with Q (the increments replace y in LDS),
-//   C: per (state, j, r): dpsi_m = e^{-i m alpha} sum_m' d^j_{m m'} dy_m',
-// and every lane adds the increments to the values it kept in registers
-// (the increment form: rounding errors scale with the change, not with psi).
+// four-step FFT).  The lines, times e^{i m alpha}, go through LDS in SP rounds of
+// radial points; in each round the coupling replaces them by their increments
+// (matrix cores), and every lane adds those, times e^{-i m alpha}, to the values it
+// kept in registers (the increment form: rounding errors scale with the change,
+// not with psi).
+//
+// What bounds it: the latency of the phases of a molecule in a row, with one
+// workgroup per CU at j_max >= 4 (registers).  At n_r = 256, j_max = 5, complex64,
+// of 51 us per molecule and CU the transforms take 12, the dipole 9.5, the coupling
+// about 8 and the wavepacket's loads and stores 8 (30,000 molecules: 8.85 GB, 1.8 ms
+// at a copy's rate).
 #pragma once
 
 #include "mol_impl.h"
@@ -23,19 +25,47 @@
 
 namespace msqd {
 
-// LDS of the per-molecule coupling tables: the phases e^{i m alpha}; d^j(beta)
-// twice (row-major and transposed, rows padded to 16 bytes); Q and the
+// Even and odd states of the basis and the pairs of eigenvectors (see below):
+// NE states with even j, NO with odd j, P pairs.  A set of up to 16 rows takes
+// steps(n) K instructions; row 4 i + kk belongs to lane group kk, element i (the
+// four rows that an instruction reads are neighbouring lines, on distinct banks).
+// The odd states of j_max = 5 (21) take a second set of rows.
+template <int JM>
+struct JmgPairs {
+  static constexpr int count(int parity) {
+    int n = 0;
+    for (int j = parity; j <= JM; j += 2) n += 2 * j + 1;
+    return n;
+  }
+  static constexpr int pairs_of(int a) { return (JM + 1 - a) / 2; }   // of the block |m'| = a
+  static constexpr int count_pairs() {
+    int n = pairs_of(0);
+    for (int a = 1; a <= JM; ++a) n += 2 * pairs_of(a);
+    return n;
+  }
+  static constexpr int steps(int n) { return (n + 3) / 4; }
+  static constexpr int NE = count(0), NO = count(1), P = count_pairs();
+  static constexpr int NO1 = NO < 16 ? NO : 16, NO2 = NO - NO1;
+  static constexpr int SE = steps(NE), S1 = steps(NO1), S2 = steps(NO2), SP = steps(P);
+  static constexpr int PST = P | 1;   // row stride of W in LDS
+  static_assert(NE <= 16 && NO2 <= 16 && P <= 16, "rows of one matrix-core tile");
+  // The state j^2 + m + j of row r of the even or the odd states, and its j
+  __device__ static __forceinline__ int even_j(int r) { return r < 1 ? 0 : (r < 6 ? 2 : 4); }
+  __device__ static __forceinline__ int even_b(int r) { return r < 1 ? 0 : (r < 6 ? r + 3 : r + 10); }
+  __device__ static __forceinline__ int odd_j(int r) { return r < 3 ? 1 : (r < 10 ? 3 : 5); }
+  __device__ static __forceinline__ int odd_b(int r) { return r < 3 ? r + 1 : (r < 10 ? r + 6 : r + 15); }
+};
+
+// LDS of the per-molecule coupling tables: the phases e^{i m alpha}; W and the
 // scaled nodes; and the workgroup reduction scratch.
 template <typename T, int JM>
 struct JmgTabShape {
   static constexpr size_t a16(size_t b) { return (b + 15) / 16 * 16; }
   static constexpr JmgTab tab = jmg_tab(JM);
-  static constexpr int PADE = 16 / static_cast<int>(sizeof(T));
-  static constexpr int prow(int j) { return (2 * j + 1 + PADE - 1) / PADE * PADE; }
-  static constexpr int poff(int j) { return j == 0 ? 0 : poff(j - 1) + (2 * j - 1) * prow(j - 1); }
-  static constexpr int n_pad = poff(JM + 1);
+  typedef JmgPairs<JM> PR;
+  static constexpr int n_w = (PR::NE + PR::NO) * PR::PST;
   static constexpr size_t ph_bytes = a16(sizeof(cx<T>) * (2 * JM + 1));
-  static constexpr size_t mt_bytes = a16(sizeof(T) * static_cast<size_t>(2 * n_pad + tab.n_q + tab.n_x));
+  static constexpr size_t mt_bytes = a16(sizeof(T) * static_cast<size_t>(n_w + 16));
   static constexpr size_t red_bytes = 6 * 16 * sizeof(double);
   static constexpr size_t bytes = ph_bytes + mt_bytes + red_bytes;
 };
@@ -76,218 +106,159 @@ __device__ __forceinline__ int jmg_row(int line) {
   return lds_line_start(line, JmgShape<T, NR, JM>::LS, static_cast<int>(sizeof(cx<T>)));
 }
 
-// ---------------------------------------------------------------- stages
-// Task t of pass p for thread tid: the passes alternate direction, so that
-// with tasks ordered from the heaviest down, a thread that drew a heavy task
-// in one pass draws a light one in the next.  Only for workgroups of whole
-// wavefronts: otherwise the reversed passes would split the tasks of one
-// block over two wavefronts.
-template <int NTHR>
-__device__ __forceinline__ int zigzag_task(int pass, int tid) {
-  return pass * NTHR + ((NTHR % 64 == 0 && (pass & 1)) ? NTHR - 1 - tid : tid);
-}
-
-// Workgroups of more than four whole wavefronts (nine at j_max = 5) put more
-// of them on some SIMDs than on others, and with a fixed share of the tasks
-// per wavefront those SIMDs set the pace of every stage.  Their stages
-// therefore hand out the tasks dynamically: each wavefront takes the next 64
-// (heaviest first) from an LDS counter, so the wavefronts that share a SIMD
-// take fewer.  Every task writes only its own outputs, so the results do not
-// depend on which wavefront takes it.
-template <int NTHR>
-inline constexpr bool kDynStages = NTHR % 64 == 0 && NTHR > 4 * 64;
-
-// Run body(t) for t in [0, nt): dynamically (ctr: an LDS counter that is zero
-// on entry) or in the zigzag passes.
-template <int NTHR, typename F>
-__device__ __forceinline__ void stage_tasks(int* ctr, int nt, int tid, F&& body) {
-  if constexpr (kDynStages<NTHR>) {
-    const int lane = tid & 63;
-    for (;;) {
-      int c = 0;
-      if (lane == 0) c = atomicAdd(ctr, 1);
-      c = __builtin_amdgcn_readfirstlane(c);
-      if (c * 64 >= nt) break;
-      const int t = c * 64 + lane;
-      if (t < nt) body(t);
-    }
-  } else {
-    for (int pass = 0; pass * NTHR < nt; ++pass) {
-      const int t = zigzag_task<NTHR>(pass, tid);
-      if (t < nt) body(t);
-    }
-  }
-}
-
-// Rotation of the j block of state s at radial point rl: to the field frame
-// (BACK = false) or back (BACK = true).  dmr holds d^j(beta) row-major
-// [m + j][m' + j] and dmt its transpose, each row padded to 16 bytes at
-// JmgShape::poff(j), so that a row is read with 16-byte loads;
-// ph[m + JM] = e^{i m alpha}.
+// ------------------------------------------------------------- coupling
+// The coupling's increments in LDS, in place: psi_b -> sum over the pairs p of
+// W_bp dchi_p, both states, all radial points of a round.
+//
+// In the field frame cos(theta) only joins states of neighbouring j, so that its
+// eigenvalues come in pairs +-x (or are zero, with no increment) and the two
+// eigenvectors of a pair share their even-j part and, but for the sign, their
+// odd-j part.  With W_bp = sqrt(2) d^j_{m m'}(beta) Q^{|m'|}_{j k} (p: m' and an
+// eigenvalue x_k > 0) and u_b = e^{i m alpha} psi_b, the coupling acts on
+//   a_p = sum_{even b} W_bp u_b and b_p = sum_{odd b} W_bp u_b
+// of the two electronic states s, s' as
+//   da_s = -vers a_s + i sin b_s',   db_s' = -vers b_s' + i sin a_s,
+// vers = 1 - cos, of the angle mu12 dt |E| x_p: 15 angles and 15 x 36
+// coefficients at j_max = 5 for 36 states, where the rotation to the field frame
+// and the transforms of every m' block take 34 angles and 286 + 144, in three
+// stages with a barrier after each.  One step, those stages on the vector units ->
+// this, complex64: 7.18 -> 6.00 ms (30,000 molecules, n_r = 256, j_max = 5), 5.91 ->
+// 4.69 (j_max = 4), 1.91 -> 1.84 (j_max = 3), 1.83 -> 1.83 (40,000, j_max = 2), 3.78
+// -> 3.23 (30,000, n_r = 128, j_max = 5), 2.28 -> 1.92 (10,000, n_r = 512, j_max =
+// 3); three steps at n_r = 256, j_max = 3: 6.08 -> 4.40.  complex128: 2.00 -> 1.47
+// (10,000, n_r = 256, j_max = 3), 1.61 -> 1.04 (j_max = 2), 1.95 -> 1.30 (n_r = 128,
+// j_max = 4), 2.94 -> 2.81 (j_max = 5), 2.88 -> 1.90 (20,000, n_r = 64, j_max = 5).
+//
+// A task is 16 radial points with the even states of one electronic state and the
+// odd states of the other; its four products are chains of 16x16x4 matrix-core
+// instructions whose output rows are the next one's operand rows (MfmaK4), so
+// nothing passes between lanes.  (a re, b im) and (a im, b re) are taken in turn.
+// Every task reads and writes its own elements only.
 template <typename T>
-__device__ __forceinline__ void load_row16(T* dst, const T* src, int n) {
-  if constexpr (sizeof(T) == 4) {
-    for (int c = 0; c < n; c += 4) {
-      const float4 w = *reinterpret_cast<const float4*>(src + c);
-      dst[c] = w.x;
-      dst[c + 1] = w.y;
-      dst[c + 2] = w.z;
-      dst[c + 3] = w.w;
-    }
-  } else {
-    for (int c = 0; c < n; c += 2) {
-      const double2 w = *reinterpret_cast<const double2*>(src + c);
-      dst[c] = w.x;
-      dst[c + 1] = w.y;
-    }
-  }
+__device__ __forceinline__ int jmg_slot_row(int slot, int S) {
+  // the row whose product comes out in row `slot` of a tile; -1: none
+  const int kk = sizeof(T) == 4 ? slot >> 2 : slot & 3, i = sizeof(T) == 4 ? slot & 3 : slot >> 2;
+  return i < S ? 4 * i + kk : -1;
 }
 
-template <typename T, int NR, int JM, int J, bool BACK>
-__device__ __forceinline__ void jmg_rot_block(cx<T>* sh, const T* dmr, const T* dmt, const cx<T>* ph, int s,
-                                              int rl) {
-  typedef JmgShape<T, NR, JM> S;
-  constexpr int N = 2 * J + 1, NB = (JM + 1) * (JM + 1), P = S::prow(J);
-  const T* d = (BACK ? dmr : dmt) + S::poff(J);
-  cx<T>* row0 = sh + rl;
-  const int l0 = s * NB + J * J;
-  // the inputs stay in registers; each output goes to LDS as it is formed
-  // (in place: the inputs were read before the first store)
-  cx<T> u[N];
-#pragma unroll
-  for (int i = 0; i < N; ++i) u[i] = row0[jmg_row<T, NR, JM>(l0 + i)];
-  if constexpr (!BACK) {
-#pragma unroll
-    for (int i = 0; i < N; ++i) u[i] = cmul(ph[JM - J + i], u[i]);
-  }
-#pragma unroll 1
-  for (int o = 0; o < N; ++o) {
-    // y_o = sum_i d[i][o] u_i (to the field frame, row o of the transpose)
-    // or sum_i d[o][i] u_i (back, row o)
-    T dv[P];
-#pragma unroll
-    for (int c = 0; c < P; c += S::PADE) load_row16(dv + c, d + o * P + c, S::PADE);
-    cx<T> acc = cscale(u[0], dv[0]);
-#pragma unroll
-    for (int i = 1; i < N; ++i) acc = acc + cscale(u[i], dv[i]);
-    if constexpr (BACK) acc = cmul_conj(acc, ph[JM - J + o]);
-    row0[jmg_row<T, NR, JM>(l0 + o)] = acc;
-  }
-}
-
-template <typename T, int NR, int JM, int J, bool BACK>
-__device__ __forceinline__ void jmg_rot_dispatch(int j, cx<T>* sh, const T* dmr, const T* dmt, const cx<T>* ph,
-                                                 int s, int rl) {
-  if (j == J)
-    jmg_rot_block<T, NR, JM, J, BACK>(sh, dmr, dmt, ph, s, rl);
-  else if constexpr (J > 1)
-    jmg_rot_dispatch<T, NR, JM, J - 1, BACK>(j, sh, dmr, dmt, ph, s, rl);
-}
-
-// All (state, j >= 1, r) tasks of a round; the j = 0 block is unchanged by
-// the rotation.  Tasks are ordered by decreasing j so that the heavy blocks
-// spread over the workgroup.
-template <typename T, int NR, int JM, bool BACK>
-__device__ __forceinline__ void jmg_rotate(cx<T>* sh, const T* dmr, const T* dmt, const cx<T>* ph, int tid,
-                                           int* ctr) {
-  constexpr int NRH = JmgShape<T, NR, JM>::NRH;
-  constexpr int NT = 2 * JM * NRH;
-  stage_tasks<JmgShape<T, NR, JM>::threads>(ctr, NT, tid, [&](int t) {
-    const int jr = t / (2 * NRH);
-    const int rem = t - jr * 2 * NRH;
-    const int s = rem / NRH;
-    jmg_rot_dispatch<T, NR, JM, JM, BACK>(JM - jr, sh, dmr, dmt, ph, s, rem - s * NRH);
-  });
-}
-
-// Stage B on the block m' (|m'| = A) at radial point rl: the states
-// j = A..JM of both electronic states.  The block |m'| = JM has the single
-// state j = JM, on which cos(theta) vanishes: its increment is zero.
-template <typename T, int NR, int JM, int A>
-__device__ __forceinline__ void jmg_couple_block(cx<T>* sh, const T* qm, const T* xe, int mp, T md, int rl) {
-  constexpr int N = JM + 1 - A, NB = (JM + 1) * (JM + 1);
-  if constexpr (A == JM) {
-    const int b = JM * JM + mp + JM;
-    sh[jmg_row<T, NR, JM>(b) + rl] = {T(0), T(0)};
-    sh[jmg_row<T, NR, JM>(NB + b) + rl] = {T(0), T(0)};
-  } else {
-    // Two passes, so that inputs and outputs are never live together.
-    // (1) per eigenvector k: chi_k = sum_i Q[i][k] y_i for both states and
-    //     its rotation increment dchi_k, stored at once over the block's LDS
-    //     slots (all inputs are in registers by then; qm holds Q
-    //     column-major, so column k is contiguous);
-    // (2) per row i: dy_i = sum_k Q[i][k] dchi_k, read back from those slots.
-    const T* Qc = qm + jmg_q_off(JM, A);
-    const T* x = xe + jmg_x_off(JM, A);
-    // the rotation angles' sine and versine first, while little else is
-    // live (the large-angle path is an out-of-line call)
-    T sn[N], vs[N];
-#pragma unroll
-    for (int k = 0; k < N; ++k) sin_vers(md * x[k], &sn[k], &vs[k]);
-    cx<T> g[N], e[N];
-#pragma unroll
-    for (int i = 0; i < N; ++i) {
-      const int j = A + i, b = j * j + mp + j;
-      g[i] = sh[jmg_row<T, NR, JM>(b) + rl];
-      e[i] = sh[jmg_row<T, NR, JM>(NB + b) + rl];
-    }
-#pragma unroll
-    for (int k = 0; k < N; ++k) {
-      const T* qk = Qc + k * N;
-      cx<T> ag = cscale(g[0], qk[0]), ae = cscale(e[0], qk[0]);
-#pragma unroll
-      for (int i = 1; i < N; ++i) {
-        ag = ag + cscale(g[i], qk[i]);
-        ae = ae + cscale(e[i], qk[i]);
-      }
-      // exp(i th sigma_x) - 1 on (g, e): (-vers g + i sin e, i sin g - vers e)
-      const int j = A + k, b = j * j + mp + j;   // slot k of the block
-      sh[jmg_row<T, NR, JM>(b) + rl] = {-vs[k] * ag.x - sn[k] * ae.y, -vs[k] * ag.y + sn[k] * ae.x};
-      sh[jmg_row<T, NR, JM>(NB + b) + rl] = {-vs[k] * ae.x - sn[k] * ag.y, -vs[k] * ae.y + sn[k] * ag.x};
-    }
-#pragma unroll
-    for (int k = 0; k < N; ++k) {
-      const int j = A + k, b = j * j + mp + j;
-      g[k] = sh[jmg_row<T, NR, JM>(b) + rl];
-      e[k] = sh[jmg_row<T, NR, JM>(NB + b) + rl];
-    }
-#pragma unroll
-    for (int i = 0; i < N; ++i) {
-      cx<T> ag = cscale(g[0], Qc[i]), ae = cscale(e[0], Qc[i]);
-#pragma unroll
-      for (int k = 1; k < N; ++k) {
-        ag = ag + cscale(g[k], Qc[k * N + i]);
-        ae = ae + cscale(e[k], Qc[k * N + i]);
-      }
-      const int j = A + i, b = j * j + mp + j;
-      sh[jmg_row<T, NR, JM>(b) + rl] = ag;
-      sh[jmg_row<T, NR, JM>(NB + b) + rl] = ae;
-    }
-  }
-}
-
-template <typename T, int NR, int JM, int A>
-__device__ __forceinline__ void jmg_couple_dispatch(int a, cx<T>* sh, const T* qm, const T* xe, int mp, T md,
-                                                    int rl) {
-  if (a == A)
-    jmg_couple_block<T, NR, JM, A>(sh, qm, xe, mp, md, rl);
-  else if constexpr (A > 0)
-    jmg_couple_dispatch<T, NR, JM, A - 1>(a, sh, qm, xe, mp, md, rl);
-}
-
-// All (m', r) tasks of a round, m' in the order 0, 1, -1, 2, -2, ...
+// A lane's part of the coupling in every task: its states' LDS rows (of the two
+// electronic states, 16 bits each), the operands of
+// W^T (fw: row = pair, K = state) and of W (row = state, K = pair), its pairs' nodes.
 template <typename T, int NR, int JM>
-__device__ __forceinline__ void jmg_couple(cx<T>* sh, const T* qm, const T* xe, const T* mudt_h, int tid,
-                                           int* ctr) {
-  constexpr int NRH = JmgShape<T, NR, JM>::NRH;
-  constexpr int NT = (2 * JM + 1) * NRH;
-  stage_tasks<JmgShape<T, NR, JM>::threads>(ctr, NT, tid, [&](int t) {
-    const int u = t / NRH;
-    const int rl = t - u * NRH;
-    const int a = (u + 1) >> 1;
-    const int mp = (u & 1) ? a : -a;
-    jmg_couple_dispatch<T, NR, JM, JM>(a, sh, qm, xe, mp, mudt_h[rl], rl);
-  });
+struct JmgOps {
+  typedef JmgPairs<JM> PR;
+  static constexpr int SE = PR::SE, S1 = PR::S1, S2 = PR::S2, SP = PR::SP, NI = SE + S1 + S2;
+  unsigned row[NI];
+  bool in[NI];   // whether there is such a state
+  T fw[NI], be[SP], bo[SP], b2[SP], xk[4];
+
+  __device__ __forceinline__ JmgOps(const T* W, const T* xe) {
+    constexpr int NE = PR::NE, NO1 = PR::NO1, NO = PR::NO, P = PR::P, PST = PR::PST;
+    const int lane = fresh_lane();
+    const int col = lane & 15, kk = lane >> 4;
+    const int pr = jmg_slot_row<T>(col, SP);
+#pragma unroll
+    for (int i = 0; i < NI; ++i) {
+      const bool even = i < SE;
+      int r = even ? 4 * i + kk : (i < SE + S1 ? 4 * (i - SE) + kk : NO1 + 4 * (i - SE - S1) + kk);
+      in[i] = r < (even ? NE : (i < SE + S1 ? NO1 : NO));
+      r = in[i] ? r : 0;   // W is zero for the rows past the last; any state will do
+      const int b = even ? PR::even_b(r) : PR::odd_b(r);
+      static_assert(JmgShape<T, NR, JM>::rows_bytes / sizeof(cx<T>) < 65536, "16-bit rows");
+      row[i] = jmg_row<T, NR, JM>(b) | jmg_row<T, NR, JM>(JmgShape<T, NR, JM>::NB + b) << 16;
+      const bool ok = in[i] && pr >= 0 && pr < P;
+      const T w = W[ok ? (even ? r : NE + r) * PST + pr : 0];
+      fw[i] = ok ? w : T(0);
+    }
+    const int re = jmg_slot_row<T>(col, SE), r1 = jmg_slot_row<T>(col, S1), r2 = jmg_slot_row<T>(col, S2);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int p = 4 * i + kk;
+      const bool ok = i < SP && p < P;
+      xk[i] = ok ? xe[p] : T(0);
+      if (i < SP) {
+        const bool oke = ok && re >= 0 && re < NE, ok1 = ok && r1 >= 0 && r1 < NO1;
+        const bool ok2 = S2 > 0 && ok && r2 >= 0 && NO1 + r2 < NO;
+        const T we = W[oke ? re * PST + p : 0], w1 = W[ok1 ? (NE + r1) * PST + p : 0];
+        be[i < SP ? i : 0] = oke ? we : T(0);
+        bo[i < SP ? i : 0] = ok1 ? w1 : T(0);
+        if constexpr (S2 > 0) {
+          const T w2 = W[ok2 ? (NE + NO1 + r2) * PST + p : 0];
+          b2[i < SP ? i : 0] = ok2 ? w2 : T(0);
+        }
+      }
+    }
+  }
+};
+
+template <typename T, int NR, int JM>
+__device__ __forceinline__ void jmg_couple(cx<T>* sh, const JmgOps<T, NR, JM>& o, const T* mudt_h, int* ctr) {
+  typedef JmgShape<T, NR, JM> S;
+  typedef JmgOps<T, NR, JM> O;
+  typedef MfmaK4<T> MK;
+  typedef typename MK::acc acc_t;
+  constexpr int SE = O::SE, S1 = O::S1, S2 = O::S2, SP = O::SP, NI = O::NI;
+  constexpr int NT = 2 * S::NRH / 16, NW = S::threads / 64;   // tasks; whole wavefronts
+  const int lane = fresh_lane();
+  const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) >> 6);
+  if (wave >= NW) return;
+  const int col = lane & 15;
+  const acc_t z = {T(0), T(0), T(0), T(0)};
+  auto task = [&](int t) {
+    const int s = t & 1, rl = (t >> 1) * 16 + col;
+    T sn[4], vs[4];
+    sin_vers_tile<NR>(mudt_h[rl], o.xk, sn, vs);
+    T* at[NI];
+#pragma unroll
+    for (int i = 0; i < NI; ++i)
+      at[i] = reinterpret_cast<T*>(sh + ((o.row[i] >> (((i < SE) == (s == 0)) ? 0 : 16)) & 0xffffu) + rl);
+#pragma unroll
+    for (int c = 0; c < 2; ++c) {
+      // c = 0: (a re, b im); c = 1: (a im, b re)
+      acc_t A = z, B = z;
+#pragma unroll
+      for (int i = 0; i < SE; ++i) A = MK::mma(o.fw[i], at[i][c], A);
+#pragma unroll
+      for (int i = SE; i < NI; ++i) B = MK::mma(o.fw[i], at[i][1 - c], B);
+      if constexpr (sizeof(T) == 8) MK::settle(A, B);
+#pragma unroll
+      for (int i = 0; i < SP; ++i) {
+        const T sg = c == 0 ? sn[i] : -sn[i];
+        const T a = A[i], b = B[i];
+        A[i] = -vs[i] * a - sg * b;
+        B[i] = -vs[i] * b + sg * a;
+      }
+      acc_t oe = z, o1 = z, o2 = z;
+#pragma unroll
+      for (int i = 0; i < SP; ++i) {
+        oe = MK::mma(o.be[i], A[i], oe);
+        o1 = MK::mma(o.bo[i], B[i], o1);
+        if constexpr (S2 > 0) o2 = MK::mma(o.b2[i], B[i], o2);
+      }
+      if constexpr (sizeof(T) == 8) {
+        MK::settle(oe, o1);
+        if constexpr (S2 > 0) MK::settle(o2, o2);
+      }
+#pragma unroll
+      for (int i = 0; i < NI; ++i)
+        if (o.in[i]) at[i][i < SE ? c : 1 - c] = i < SE ? oe[i & 3] : (i < SE + S1 ? o1[(i - SE) & 3] : o2[(i - SE - S1) & 3]);
+    }
+  };
+  // Workgroups of more than four wavefronts put more of them on some execution
+  // units than on others, and with a fixed share of the tasks those would set the
+  // pace: their wavefronts take the next task from an LDS counter (zero on entry).
+  if constexpr (NW > 4) {
+    for (;;) {
+      int t = 0;
+      if (lane == 0) t = atomicAdd(ctr, 1);
+      t = __builtin_amdgcn_readfirstlane(t);
+      if (t >= NT) break;
+      task(t);
+    }
+  } else {
+#pragma unroll 1
+    for (int t = wave; t < NT; t += NW) task(t);
+  }
 }
 
 // The terms of the dipole vector at radial point rl from the basis states of
@@ -355,13 +326,11 @@ void mol_jmg_kernel(MolArgs a) {
   T* mask_s = reinterpret_cast<T*>(tw_s + TBL::tw_elems);
   cx<T>* sh = reinterpret_cast<cx<T>*>(smem + TBL::bytes);
   cx<T>* ph = reinterpret_cast<cx<T>*>(smem + TBL::bytes + S::rows_bytes);
-  T* dmr = reinterpret_cast<T*>(smem + TBL::bytes + S::rows_bytes + S::ph_bytes);
-  T* dmt = dmr + S::n_pad;
-  T* qm = dmt + S::n_pad;
-  T* xe = qm + TB.n_q;
+  T* W = reinterpret_cast<T*>(smem + TBL::bytes + S::rows_bytes + S::ph_bytes);
+  T* xe = W + S::n_w;
   double* red = reinterpret_cast<double*>(smem + TBL::bytes + S::rows_bytes + S::ph_bytes + S::mt_bytes);
-  // the stages' task counters live in the reduction area, which is used
-  // only after the last stage
+  // the coupling's task counter lives in the reduction area, which is used
+  // only after the last round
   int* ctr = reinterpret_cast<int*>(red);
 
   const int mol = blockIdx.x;
@@ -382,6 +351,12 @@ void mol_jmg_kernel(MolArgs a) {
   const T* mask_g = reinterpret_cast<const T*>(ws + (dbl ? a.lay.mask_d : a.lay.mask_f));
   const double* mu = reinterpret_cast<const double*>(ws + a.lay.mu_d);
   const double* tg = reinterpret_cast<const double*>(ws + a.lay.total);
+
+  // the coupling's host tables, one entry per thread, ahead of the wavepacket's
+  // loads: what is formed from them is formed while those are in flight
+  constexpr int NTAB = TB.n_jx + TB.n_q + TB.n_x;
+  static_assert(NTAB <= nthr && TB.jx == 0 && TB.q == TB.n_jx && TB.x == TB.n_jx + TB.n_q, "one entry per thread");
+  const double tab_e = tg[tid < NTAB ? tid : 0];
 
   // field at the molecule (each component at its own edge of the cell);
   // a readout-only launch (no step) reads no field
@@ -409,11 +384,25 @@ void mol_jmg_kernel(MolArgs a) {
   const int loff = line * NR + q;
   const int voff = (st * a.nj + jl) * NR + q;   // potential phases depend on (state, j)
   cx<T> vv[R1];
+  if constexpr (stage_tables<NR, T>()) stage_tables_to_lds<NR, T, true>(kin_s, tw_s, mask_s, kin_g, tw_g, mask_g);
+  // The wavepacket's loads: ahead of the coupling tables' arithmetic, which other
+  // workgroups' loads would otherwise wait behind; after it for the complex64 forms
+  // of one exchange round, which have a CU or nearly so to themselves (6.00 ms
+  // instead of 6.41 for 30,000 molecules at n_r = 256, j_max = 5; 1.84 instead of
+  // 2.02 the other way round at j_max = 3).
+  constexpr bool LATE = sizeof(T) == 4 && SP == 1;
+  if constexpr (!LATE) {
 #pragma unroll
-  for (int p = 0; p < R1; ++p) vv[p] = psi[loff + R2 * p];
+    for (int p = 0; p < R1; ++p) vv[p] = psi[loff + R2 * p];
+  }
 
-  // per-molecule coupling tables: the field frame (alpha, beta) and |E|
+  // per-molecule coupling tables: the field frame (alpha, beta) and |E|; the LDS
+  // rows, which are not in use yet, hold the host tables and d^j(beta)
   {
+    double* tl = reinterpret_cast<double*>(sh);
+    double* dj = tl + NTAB;
+    static_assert((NTAB + TB.n_jx) * sizeof(double) <= S::rows_bytes, "scratch in the rows");
+    if (tid < NTAB) tl[tid] = tab_e;
     const double en = sqrt(E3[0] * E3[0] + E3[1] * E3[1] + E3[2] * E3[2]);
     const double rho = sqrt(E3[0] * E3[0] + E3[1] * E3[1]);
     const double ca = rho > 0.0 ? E3[0] / rho : 1.0, sa = rho > 0.0 ? E3[1] / rho : 0.0;
@@ -432,7 +421,7 @@ void mol_jmg_kernel(MolArgs a) {
     // mu_k = k - j: ra, rc are the rows of m and m' in O
     auto wigner_d = [&](int j, int ra, int rc) {
       const int n = 2 * j + 1;
-      const double* O = tg + TB.jx + jmg_jx_off(j);
+      const double* O = tl + TB.jx + jmg_jx_off(j);
       // cos(pi/2 (m' - m) - beta mu) = cA cos(mu beta) + sA sin(mu beta)
       const int dq = (rc - ra) & 3;
       const double cA = dq == 0 ? 1.0 : (dq == 2 ? -1.0 : 0.0);
@@ -448,28 +437,43 @@ void mol_jmg_kernel(MolArgs a) {
       }
       return acc;
     };
-    // both padded layouts: entry (row r, column c) of block j is d[r][c]
-    // in dmr and d[c][r] in dmt; the padding columns are zero
-    for (int t = tid; t < S::n_pad; t += nthr) {
+    __syncthreads();
+    for (int t = tid; t < TB.n_jx; t += nthr) {
       int j = 0;
-      while (t >= S::poff(j + 1)) ++j;
-      const int P = S::prow(j), o = t - S::poff(j), r = o / P, c = o - r * P;
-      const bool in = c < 2 * j + 1;
-      dmr[t] = in ? static_cast<T>(wigner_d(j, r, c)) : T(0);
-      dmt[t] = in ? static_cast<T>(wigner_d(j, c, r)) : T(0);
+      while (t >= jmg_jx_off(j + 1)) ++j;
+      const int n = 2 * j + 1, o = t - jmg_jx_off(j), r = o / n;
+      dj[t] = wigner_d(j, r, o - r * n);
     }
-    // Q^(a) column-major in LDS (the workspace holds it row-major)
-    for (int t = tid; t < TB.n_q; t += nthr) {
-      int am = 0;
-      while (t >= jmg_q_off(JM, am + 1)) ++am;
-      const int n = JM + 1 - am, o = t - jmg_q_off(JM, am), i = o / n, k = o - i * n;
-      qm[jmg_q_off(JM, am) + k * n + i] = static_cast<T>(tg[TB.q + t]);
+    __syncthreads();
+    typedef JmgPairs<JM> PR;
+    for (int t = tid; t < (PR::NE + PR::NO) * PR::P; t += nthr) {
+      const int r = t / PR::P;
+      int p = t - r * PR::P;
+      const bool even = r < PR::NE;
+      const int j = even ? PR::even_j(r) : PR::odd_j(r - PR::NE);
+      const int b = even ? PR::even_b(r) : PR::odd_b(r - PR::NE);
+      const int m = b - j * j - j;
+      // pair p: m' = 0, 1, -1, 2, -2, ..., the positive eigenvalues of each in order
+      const int pw = r * PR::PST + p;
+      int u = 0;
+      while (p >= PR::pairs_of((u + 1) >> 1)) p -= PR::pairs_of((u++ + 1) >> 1);
+      const int am = (u + 1) >> 1, mp = (u & 1) ? am : -am;
+      const int n = JM + 1 - am, k = (n + 1) / 2 + p;
+      double w = 0.0;
+      if (am <= j)
+        w = 1.4142135623730950488 * dj[jmg_jx_off(j) + (m + j) * (2 * j + 1) + mp + j] *
+            tl[TB.q + jmg_q_off(JM, am) + (j - am) * n + k];
+      W[pw] = static_cast<T>(w);
+      if (r == 0) xe[pw] = static_cast<T>(en * tl[TB.x + jmg_x_off(JM, am) + k]);
     }
-    for (int t = tid; t < TB.n_x; t += nthr) xe[t] = static_cast<T>(en * tg[TB.x + t]);
   }
-  if constexpr (stage_tables<NR, T>()) stage_tables_to_lds<NR, T, true>(kin_s, tw_s, mask_s, kin_g, tw_g, mask_g);
+  if constexpr (LATE) {
+#pragma unroll
+    for (int p = 0; p < R1; ++p) vv[p] = psi[loff + R2 * p];
+  }
   __syncthreads();
 
+  const cx<T> eim = ph[b - jl * jl - jl + JM];   // this line's e^{i m alpha}
   double ab = 0.0;
   const int n_steps = ONE ? 1 : a.n_steps;
   for (int step = 0; step < n_steps; ++step) {
@@ -487,27 +491,25 @@ void mol_jmg_kernel(MolArgs a) {
     }
     const cx<T>* vph = opaque(vph_g);
     kinetic_half<T, NR, false, SP, TBL::TWC>(vv, slot, q, kin, tw);
+    const JmgOps<T, NR, JM> ops(W, xe);
 #pragma unroll
     for (int h = 0; h < SP; ++h) {
 #pragma unroll
       for (int pp = 0; pp < PH; ++pp) {
         const int p = h * PH + pp;
         vv[p] = phase_mul(vv[p], vph[voff + R2 * p]);
-        slot[q + R2 * pp] = vv[p];
+        slot[q + R2 * pp] = cmul(eim, vv[p]);
       }
-      // the previous round's stages ended at a barrier: reset their counters
-      if (kDynStages<nthr> && tid == 0) ctr[0] = ctr[1] = ctr[2] = 0;
+      // the previous round's coupling ended at a barrier: reset its counter
+      if (tid == 0) *ctr = 0;
       __syncthreads();
-      jmg_rotate<T, NR, JM, false>(sh, dmr, dmt, ph, tid, ctr);
+      jmg_couple<T, NR, JM>(sh, ops, mudt + h * NRH, ctr);
       __syncthreads();
-      jmg_couple<T, NR, JM>(sh, qm, xe, mudt + h * NRH, tid, ctr + 1);
-      __syncthreads();
-      jmg_rotate<T, NR, JM, true>(sh, dmr, dmt, ph, tid, ctr + 2);
-      __syncthreads();
+      vph = opaque(vph_g);   // read again rather than kept across the coupling
 #pragma unroll
       for (int pp = 0; pp < PH; ++pp) {
         const int p = h * PH + pp;
-        vv[p] = phase_mul(vv[p] + slot[q + R2 * pp], vph[voff + R2 * p]);
+        vv[p] = phase_mul(vv[p] + cmul_conj(slot[q + R2 * pp], eim), vph[voff + R2 * p]);
       }
     }
     kinetic_half<T, NR, false, SP, TBL::TWC>(vv, slot, q, kin, tw);
@@ -539,7 +541,8 @@ void mol_jmg_kernel(MolArgs a) {
       for (int pp = 0; pp < PH; ++pp) slot[q + R2 * pp] = vv[h * PH + pp];
       __syncthreads();
       for (int pass = 0; pass * nthr < NRH * (JM + 1); ++pass) {
-        const int t = zigzag_task<JmgShape<T, NR, JM>::threads>(pass, tid);
+        // alternate directions: a thread with a heavy task in one pass draws a light one in the next
+        const int t = pass * nthr + ((nthr % 64 == 0 && (pass & 1)) ? nthr - 1 - tid : tid);
         if (t >= NRH * (JM + 1)) continue;
         const int j = JM - t / NRH, rl = t - (JM - j) * NRH;   // heaviest j first
         double tx, ty, tz;
