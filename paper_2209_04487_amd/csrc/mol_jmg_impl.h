@@ -15,7 +15,7 @@
 //
 // What bounds it: the latency of the phases of a molecule in a row, with one
 // workgroup per CU at j_max >= 4 (registers).  At n_r = 256, j_max = 5, complex64,
-// of 51 us per molecule and CU the transforms take 12, the dipole 9.5, the coupling
+// of 49 us per molecule and CU the transforms take 12, the dipole 7, the coupling
 // about 8 and the wavepacket's loads and stores 8 (30,000 molecules: 8.85 GB, 1.8 ms
 // at a copy's rate).
 #pragma once
@@ -191,6 +191,29 @@ struct JmgOps {
   }
 };
 
+// Run task(t), t < nt, on the workgroup's whole wavefronts.  Workgroups of more than
+// four wavefronts put more of them on some execution units than on others, and with a
+// fixed share of the tasks those would set the pace: their wavefronts take the next
+// task from an LDS counter (zero on entry).  The tasks' outputs are their own.
+template <typename T, int NR, int JM, typename F>
+__device__ __forceinline__ void jmg_tasks(int nt, int* ctr, F&& task) {
+  constexpr int NW = JmgShape<T, NR, JM>::threads / 64;
+  const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) >> 6);
+  if (wave >= NW) return;
+  if constexpr (NW > 4) {
+    for (;;) {
+      int t = 0;
+      if (fresh_lane() == 0) t = atomicAdd(ctr, 1);
+      t = __builtin_amdgcn_readfirstlane(t);
+      if (t >= nt) break;
+      task(t);
+    }
+  } else {
+#pragma unroll 1
+    for (int t = wave; t < nt; t += NW) task(t);
+  }
+}
+
 template <typename T, int NR, int JM>
 __device__ __forceinline__ void jmg_couple(cx<T>* sh, const JmgOps<T, NR, JM>& o, const T* mudt_h, int* ctr) {
   typedef JmgShape<T, NR, JM> S;
@@ -198,11 +221,8 @@ __device__ __forceinline__ void jmg_couple(cx<T>* sh, const JmgOps<T, NR, JM>& o
   typedef MfmaK4<T> MK;
   typedef typename MK::acc acc_t;
   constexpr int SE = O::SE, S1 = O::S1, S2 = O::S2, SP = O::SP, NI = O::NI;
-  constexpr int NT = 2 * S::NRH / 16, NW = S::threads / 64;   // tasks; whole wavefronts
-  const int lane = fresh_lane();
-  const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) >> 6);
-  if (wave >= NW) return;
-  const int col = lane & 15;
+  constexpr int NT = 2 * S::NRH / 16;   // tasks
+  const int col = fresh_lane() & 15;
   const acc_t z = {T(0), T(0), T(0), T(0)};
   auto task = [&](int t) {
     const int s = t & 1, rl = (t >> 1) * 16 + col;
@@ -244,21 +264,7 @@ __device__ __forceinline__ void jmg_couple(cx<T>* sh, const JmgOps<T, NR, JM>& o
         if (o.in[i]) at[i][i < SE ? c : 1 - c] = i < SE ? oe[i & 3] : (i < SE + S1 ? o1[(i - SE) & 3] : o2[(i - SE - S1) & 3]);
     }
   };
-  // Workgroups of more than four wavefronts put more of them on some execution
-  // units than on others, and with a fixed share of the tasks those would set the
-  // pace: their wavefronts take the next task from an LDS counter (zero on entry).
-  if constexpr (NW > 4) {
-    for (;;) {
-      int t = 0;
-      if (lane == 0) t = atomicAdd(ctr, 1);
-      t = __builtin_amdgcn_readfirstlane(t);
-      if (t >= NT) break;
-      task(t);
-    }
-  } else {
-#pragma unroll 1
-    for (int t = wave; t < NT; t += NW) task(t);
-  }
+  jmg_tasks<T, NR, JM>(NT, ctr, task);
 }
 
 // The terms of the dipole vector at radial point rl from the basis states of
@@ -274,7 +280,8 @@ __device__ __forceinline__ void jmg_dipole_point(const cx<T>* sh, const double* 
     return cx<double>{static_cast<double>(v.x), static_cast<double>(v.y)};
   };
   double z = 0.0, pr = 0.0, pi = 0.0;
-#pragma unroll 1
+  constexpr int kUnroll = sizeof(T) == 4 ? 2 : 1;   // complex128 spilled with two
+#pragma unroll kUnroll
   for (int m = -j; m <= j; ++m) {
     const int b = j * j + m + j;
     const cx<double> gb = ld(b), eb = ld(NB + b);
@@ -540,11 +547,19 @@ void mol_jmg_kernel(MolArgs a) {
 #pragma unroll
       for (int pp = 0; pp < PH; ++pp) slot[q + R2 * pp] = vv[h * PH + pp];
       __syncthreads();
-      for (int pass = 0; pass * nthr < NRH * (JM + 1); ++pass) {
-        // alternate directions: a thread with a heavy task in one pass draws a light one in the next
-        const int t = pass * nthr + ((nthr % 64 == 0 && (pass & 1)) ? nthr - 1 - tid : tid);
-        if (t >= NRH * (JM + 1)) continue;
-        const int j = JM - t / NRH, rl = t - (JM - j) * NRH;   // heaviest j first
+      // Tasks of one j and 64 radial points, the heaviest first (j = JM has terms with
+      // j - 1 only), given out to and fro over the whole wavefronts: fixed, so that the
+      // sums are the same in every run.  With two or more wavefronts for each 64 points,
+      // an equal number of them, which the execution units share alike (9 wavefronts
+      // -> 8 at j_max = 5; 6.04 -> 5.70 ms for 30,000 molecules at n_r = 256).
+      constexpr int NC = NRH / 64, NW = nthr / 64, NWD = NW >= 2 * NC ? NW / NC * NC : NW;
+      const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+      for (int pass = 0; pass * NWD < NC * (JM + 1); ++pass) {
+        const int t = pass * NWD + ((pass & 1) ? NWD - 1 - wave : wave);
+        if (wave >= NWD || t >= NC * (JM + 1)) continue;
+        constexpr int top = (JM + 1) / 2;   // tasks with a larger sum than j = JM's
+        const int u = t / NC, rl = (t - u * NC) * 64 + (tid & 63);
+        const int j = u == top ? JM : JM - 1 - u + (u > top ? 1 : 0);
         double tx, ty, tz;
         jmg_dipole_point<T, NR, JM>(sh, dip, j, rl, &tx, &ty, &tz);
         const double m = mu[h * NRH + rl];
