@@ -27,9 +27,11 @@ namespace msqd {
 // The split is the host's fft_r1(n_r, element bytes): complex64 lines use
 // longer in-register DFTs (fewer lanes and waves per molecule, more
 // molecules per CU); complex128 keeps R1 <= 16 within the register file.
-template <int NR, typename T>
+// W: wide lines, R1 / W values on W times the lanes, where R2 <= R1 still holds
+// (complex64 at n_r = 256: 16 x 16; see kWideMaxNJ).
+template <int NR, typename T, int W = 1>
 struct FftShape {
-  static constexpr int R1 = fft_r1(NR, static_cast<int>(sizeof(T)));
+  static constexpr int R1 = fft_r1(NR, static_cast<int>(sizeof(T))) / W;
   static constexpr int R2 = NR / R1;
 };
 
@@ -43,17 +45,17 @@ constexpr int line_stride() { return NR + FftShape<NR, T>::R2; }
 // points; the shortest complex64 grids use one.  complex128 lines take one
 // round, or two by parts (mol_step_kernel's PARTS): the real and the imaginary
 // parts in turn, as their lanes hold a single column at n_r = 256.
-template <int NR, typename T>
+template <int NR, typename T, int W = 1>
 constexpr int fwd_split() {
-  return (sizeof(T) == 4 && (FftShape<NR, T>::R1 / FftShape<NR, T>::R2) % 2 == 0) ? 2 : 1;
+  return (sizeof(T) == 4 && (FftShape<NR, T, W>::R1 / FftShape<NR, T, W>::R2) % 2 == 0) ? 2 : 1;
 }
 // Elements between the LDS rows of lines in SP rounds: NR/SP points, at least
 // the padded rows of R1 + 1 of the transposes.  By parts a line needs
 // R2 (R1 + 1) doubles, half as many elements; that stride puts the lines of a
 // half-wavefront on distinct banks in the row and the column accesses.
-template <int NR, typename T, int SP = fwd_split<NR, T>()>
+template <int NR, typename T, int SP = fwd_split<NR, T>(), int W = 1>
 constexpr int fwd_line_stride() {
-  return NR / SP + FftShape<NR, T>::R2 / ((sizeof(T) == 8 && SP == 2) ? 2 : 1);
+  return NR / SP + FftShape<NR, T, W>::R2 / ((sizeof(T) == 8 && SP == 2) ? 2 : 1);
 }
 
 // The per-workgroup LDS copy of the transform tables (kinetic factors,
@@ -68,9 +70,9 @@ constexpr int fwd_line_stride() {
 // With CPOPS the copy also holds the operands of the J <-> angle contraction
 // (the matrix-core fragments of T and T^T, 2 KB, and the angle nodes padded
 // with zeros to 16), which every exchange round of every step reads.
-template <int NR, typename T, bool COMPACT = false, bool CPOPS = true>
+template <int NR, typename T, bool COMPACT = false, bool CPOPS = true, int W = 1>
 struct StagedTables {
-  static constexpr int R1 = FftShape<NR, T>::R1, R2 = FftShape<NR, T>::R2;
+  static constexpr int R1 = FftShape<NR, T, W>::R1, R2 = FftShape<NR, T, W>::R2;
   static constexpr bool on = sizeof(T) == 4;
   static constexpr int TWC = (on && COMPACT) ? R1 + 1 : 0;   // compact row stride (0: full layout)
   static constexpr size_t tw_elems =
@@ -83,8 +85,8 @@ struct StagedTables {
 };
 template <int NR, typename T>
 constexpr bool stage_tables() { return StagedTables<NR, T>::on; }
-template <int NR, typename T>
-constexpr size_t lds_table_bytes() { return StagedTables<NR, T>::bytes; }
+template <int NR, typename T, int W = 1>
+constexpr size_t lds_table_bytes() { return StagedTables<NR, T, false, true, W>::bytes; }
 
 // Cooperative copy of a table into LDS in 16-byte pieces.
 __device__ __forceinline__ void lds_stage(void* dst, const void* src, size_t bytes) {
@@ -96,22 +98,25 @@ __device__ __forceinline__ void lds_stage(void* dst, const void* src, size_t byt
 // Stage the tables: kin [NR], the twiddles of the R1 x R1 table tw_g (all,
 // or the rows x < R2 in the compact layout), and mask [NR]; the caller
 // synchronises the workgroup afterwards.
-template <int NR, typename T, bool COMPACT = false>
+template <int NR, typename T, bool COMPACT = false, int W = 1>
 __device__ __forceinline__ void stage_tables_to_lds(cx<T>* kin_s, cx<T>* tw_s, T* mask_s, const cx<T>* kin_g,
                                                     const cx<T>* tw_g, const T* mask_g) {
-  typedef StagedTables<NR, T, COMPACT, false> ST;
+  typedef StagedTables<NR, T, COMPACT, false, W> ST;
   lds_stage(kin_s, kin_g, NR * sizeof(cx<T>));
   if constexpr (COMPACT) {
-    for (int t = threadIdx.x; t < ST::R2 * ST::R1; t += blockDim.x) tw_s[(t / ST::R1) * ST::TWC + t % ST::R1] = tw_g[t];
+    for (int t = threadIdx.x; t < ST::R2 * ST::R1; t += blockDim.x)
+      tw_s[(t / ST::R1) * ST::TWC + t % ST::R1] = tw_g[t / ST::R1 * (W * ST::R1) + t % ST::R1];
+  } else if constexpr (W > 1) {
+    for (int t = threadIdx.x; t < ST::R1 * ST::R1; t += blockDim.x) tw_s[t] = tw_g[t / ST::R1 * (W * ST::R1) + t % ST::R1];
   } else {
     lds_stage(tw_s, tw_g, ST::tw_elems * sizeof(cx<T>));
   }
   lds_stage(mask_s, mask_g, NR * sizeof(T));
 }
 
-template <int NR, typename T, int SP = fwd_split<NR, T>()>
+template <int NR, typename T, int SP = fwd_split<NR, T>(), int W = 1>
 __device__ __forceinline__ int lds_row(int line) {
-  return lds_line_start(line, fwd_line_stride<NR, T, SP>(), static_cast<int>(sizeof(cx<T>)));
+  return lds_line_start(line, fwd_line_stride<NR, T, SP, W>(), static_cast<int>(sizeof(cx<T>)));
 }
 
 __device__ __forceinline__ void wave_lds_sync() {
@@ -232,10 +237,10 @@ __device__ __forceinline__ void transpose_by_parts(cx<double>* v, cx<double>* sl
   }
 }
 
-template <typename T, int NR, bool CONJ = false, int SP = 1, int TWC = 0, bool TWS = false>
+template <typename T, int NR, bool CONJ = false, int SP = 1, int TWC = 0, bool TWS = false, int W = 1>
 __device__ __forceinline__ void kinetic_half(cx<T>* v, cx<T>* slot, int q, const cx<T>* __restrict__ kin,
                                              const cx<T>* __restrict__ tw2) {
-  constexpr int R1 = FftShape<NR, T>::R1, R2 = FftShape<NR, T>::R2, U = R1 / R2;
+  constexpr int R1 = FftShape<NR, T, W>::R1, R2 = FftShape<NR, T, W>::R2, U = R1 / R2;
   // complex128 in two rounds: the transposes go by parts
   constexpr bool PARTS = sizeof(T) == 8 && SP == 2;
   // SP rounds of RH = R1/SP columns each; the slot holds R2 rows of RH + 1
@@ -474,29 +479,30 @@ __device__ __forceinline__ mf_float4 mma3(mf_short4 ahi, mf_short4 alo, mf_short
 // once: the operand T is zero in the columns J >= nj, so the update writes
 // back the zero it loaded, and neither the loads nor the stores of a tile
 // branch on J.
-template <int NR, typename T>
+template <int NR, typename T, int W = 1>
 struct CpRows {
   int g[4], e[4];
   __device__ __forceinline__ CpRows(int nj, int j0, int step) {
-    const int spare = lds_row<NR, T>(2 * nj);
+    constexpr int SP = fwd_split<NR, T, W>();
+    const int spare = lds_row<NR, T, SP, W>(2 * nj);
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const int J = j0 + step * i;
-      g[i] = J < nj ? lds_row<NR, T>(J) : spare;
-      e[i] = J < nj ? lds_row<NR, T>(nj + J) : spare;
+      g[i] = J < nj ? lds_row<NR, T, SP, W>(J) : spare;
+      e[i] = J < nj ? lds_row<NR, T, SP, W>(nj + J) : spare;
     }
   }
 };
 
 // frag: 4 operand blocks [A_hi, A_lo, At_hi, At_lo] x 64 lanes x 4 bf16;
 // x: the angle nodes padded with zeros to 16
-template <int NR>
+template <int NR, int W>
 __device__ __forceinline__ void coupling_mfma(cx<float>* sh, int nj, int r0,
                                            const unsigned short* __restrict__ frag,
                                            const float* __restrict__ x,
                                            const float* __restrict__ mudt, float E) {
   using T = float;
-  constexpr int NRH = NR / fwd_split<NR, float>();   // radial points of this round
+  constexpr int NRH = NR / fwd_split<NR, float, W>();   // radial points of this round
   const int lane = fresh_lane();
   const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) >> 6);
   const int nwaves = (blockDim.x + 63) >> 6;
@@ -513,7 +519,7 @@ __device__ __forceinline__ void coupling_mfma(cx<float>* sh, int nj, int r0,
   float xk[4];
 #pragma unroll
   for (int i = 0; i < 4; ++i) xk[i] = x[rb + i];   // x holds 16 nodes, zero beyond nj
-  const CpRows<NR, T> rows(nj, rb, 1);
+  const CpRows<NR, T, W> rows(nj, rb, 1);
 #pragma unroll 1
   for (int tile = wave; tile * 16 < NRH; tile += nwaves) {
     const int rl = tile * 16 + col;   // radial point within the round (LDS)
@@ -538,7 +544,7 @@ __device__ __forceinline__ void coupling_mfma(cx<float>* sh, int nj, int r0,
     mf_float4 Pei = mma3(Ahi, Alo, h3, l3, z);
     // (R - I) Phi per node: dg = -v Phi_g + i s Phi_e, de = i s Phi_g - v Phi_e
     float sn[4], vs[4];
-    sin_vers_tile<NR>(mudt[r] * E, xk, sn, vs);
+    sin_vers_tile<(W > 1 ? 128 : NR)>(mudt[r] * E, xk, sn, vs);
     float dgr[4], dgi[4], der[4], dei[4];
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
@@ -623,14 +629,14 @@ __device__ __forceinline__ int mf_row(int g, int i) {
 // FP32 when KH).  KH: N_J <= kHalfKMaxNJ, two of the four K instructions.
 // NK: K instructions of a product (four, three or the half-K two).  LARGE: angles
 // beyond the series may occur (FP64; FP32 decides per tile).
-template <typename T, int NR, int NK, bool LARGE>
+template <typename T, int NR, int NK, bool LARGE, int W>
 __device__ __forceinline__ void coupling_mfma_exact(cx<T>* sh, int nj, int r0,
                                                     const T* __restrict__ frag,
                                                     const T* __restrict__ x,
                                                     const T* __restrict__ mudt, T E) {
   typedef typename MfmaK4<T>::acc acc_t;
   constexpr bool KH = NK == 2;
-  constexpr int NRH = NR / fwd_split<NR, T>();
+  constexpr int NRH = NR / fwd_split<NR, T, W>();
   const int lane = fresh_lane();
   const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) >> 6);
   const int nwaves = (blockDim.x + 63) >> 6;
@@ -646,7 +652,7 @@ __device__ __forceinline__ void coupling_mfma_exact(cx<T>* sh, int nj, int r0,
   }
   // this lane's rows: 4 grp + i (FP32 instruction) or 4 i + grp (FP64);
   // 2 grp + i in the FP32 half-K order
-  const CpRows<NR, T> rows(nj, mf_row<T, KH>(grp, 0), mf_row<T, KH>(0, 1) - mf_row<T, KH>(0, 0));
+  const CpRows<NR, T, W> rows(nj, mf_row<T, KH>(grp, 0), mf_row<T, KH>(0, 1) - mf_row<T, KH>(0, 0));
 #pragma unroll 1
   for (int tile = wave; tile * 16 < NRH; tile += nwaves) {
     const int rl = tile * 16 + col;   // radial point within the round (LDS)
@@ -670,7 +676,7 @@ __device__ __forceinline__ void coupling_mfma_exact(cx<T>* sh, int nj, int r0,
     const T md = mudt[r] * E;
     T sn[4], vs[4];
     if constexpr (LARGE) {
-      sin_vers_tile<NR>(md, xk, sn, vs);
+      sin_vers_tile<(W > 1 ? 128 : NR)>(md, xk, sn, vs);
     } else {
 #pragma unroll
       for (int i = 0; i < 4; ++i) sin_vers_series(md * xk[i], &sn[i], &vs[i]);
@@ -846,12 +852,13 @@ __device__ __forceinline__ void absorb_point(cx<T>& v, T m, double& ab) {
 // at n_r = 256 and 512 (three waves per molecule at J_max = 10, n_r = 256)
 // run four molecules per CU within 168 VGPRs, which the LDS copy of a
 // molecule also allows; at n_r <= 128 (16 values per lane) four waves per
-// SIMD fit in 128 VGPRs and the LDS holds more molecules than that.  The FP64
+// SIMD fit in 128 VGPRs and the LDS holds more molecules than that, and so with
+// wide lines (W) at n_r = 256.  The FP64
 // form is bounded by LDS (one molecule of complex128 lines per CU) and may use
 // 256 VGPRs.
-template <typename T, int NR, bool PARTS>
+template <typename T, int NR, bool PARTS, int W>
 struct MolOcc {
-  static constexpr int waves = sizeof(T) == 8 ? (PARTS && NR < 512 ? 3 : 2) : (NR <= 128 ? 4 : 3);
+  static constexpr int waves = sizeof(T) == 8 ? (PARTS && NR < 512 ? 3 : 2) : (NR <= 128 || W > 1 ? 4 : 3);
 };
 
 
@@ -871,14 +878,14 @@ inline constexpr bool kPrioContraction = CP == kCpBf16x3 && NR >= 256;
 // ONE: the launch advances exactly one step (the coupled step's case); the
 // step loop then has no back edge, and the register allocation needs no
 // spills.
-template <typename T, int NR, int CP, bool ONE, bool PARTS>
-__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(MolOcc<T, NR, PARTS>::waves)))
+template <typename T, int NR, int CP, bool ONE, bool PARTS, int W>
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(MolOcc<T, NR, PARTS, W>::waves)))
 void mol_step_kernel(MolArgs a) {
-  constexpr int R1 = FftShape<NR, T>::R1, R2 = FftShape<NR, T>::R2;
+  constexpr int R1 = FftShape<NR, T, W>::R1, R2 = FftShape<NR, T, W>::R2;
   // SP exchange rounds of NRH radial points; round h holds the registers
   // p in [h PH, (h+1) PH), i.e. r = q + R2 p in [h NRH, (h+1) NRH)
   // (PARTS: the dipole readout only)
-  constexpr int SP = PARTS ? 2 : fwd_split<NR, T>(), PH = R1 / SP, NRH = NR / SP;
+  constexpr int SP = PARTS ? 2 : fwd_split<NR, T, W>(), PH = R1 / SP, NRH = NR / SP;
   constexpr int NK = CP == kCpExactHalf ? 2 : CP == kCpExact3 ? 3 : 4;
   static_assert(!PARTS || sizeof(T) == 8, "the exchange by parts is for complex128 lines");
   static_assert(CP != kCpBf16x3 || stage_tables<NR, T>(),
@@ -888,14 +895,14 @@ void mol_step_kernel(MolArgs a) {
   const int L = 2 * nj;
   // LDS: transform tables | lines | spare row (the contractions' rows
   // J >= nj) | reduction scratch
-  constexpr size_t TB = lds_table_bytes<NR, T>();
+  constexpr size_t TB = lds_table_bytes<NR, T, W>();
   cx<T>* kin_s = reinterpret_cast<cx<T>*>(smem);
   cx<T>* tw_s = kin_s + NR;
-  T* mask_s = reinterpret_cast<T*>(tw_s + StagedTables<NR, T>::tw_elems);
-  unsigned char* frag_s = smem + StagedTables<NR, T>::fft_bytes;
-  float* x_s = reinterpret_cast<float*>(frag_s + StagedTables<NR, T>::frag_bytes);
+  T* mask_s = reinterpret_cast<T*>(tw_s + StagedTables<NR, T, false, true, W>::tw_elems);
+  unsigned char* frag_s = smem + StagedTables<NR, T, false, true, W>::fft_bytes;
+  float* x_s = reinterpret_cast<float*>(frag_s + StagedTables<NR, T, false, true, W>::frag_bytes);
   cx<T>* sh = reinterpret_cast<cx<T>*>(smem + TB);
-  double* red = reinterpret_cast<double*>(smem + TB + sizeof(cx<T>) * (lds_row<NR, T, SP>(L) + NRH));
+  double* red = reinterpret_cast<double*>(smem + TB + sizeof(cx<T>) * (lds_row<NR, T, SP, W>(L) + NRH));
 
   const int mol = blockIdx.x;
   const int tid = threadIdx.x;
@@ -946,10 +953,10 @@ void mol_step_kernel(MolArgs a) {
 
   // the contractions' spare row (rows J >= nj) holds zeros; the barrier
   // before the first contraction publishes them
-  for (int i = tid; i < NRH; i += nthr) sh[lds_row<NR, T, SP>(L) + i] = cx<T>{T(0), T(0)};
+  for (int i = tid; i < NRH; i += nthr) sh[lds_row<NR, T, SP, W>(L) + i] = cx<T>{T(0), T(0)};
 
   cx<T>* psi = reinterpret_cast<cx<T>*>(a.psi) + static_cast<size_t>(mol) * L * NR;
-  cx<T>* slot = sh + lds_row<NR, T, SP>(line);
+  cx<T>* slot = sh + lds_row<NR, T, SP, W>(line);
   const int loff = line * NR + q;  // this lane's first element of its line
   cx<T> v[R1];
   if (active) {
@@ -963,9 +970,9 @@ void mol_step_kernel(MolArgs a) {
   // the tables read at every element go to LDS (the per-element L1/L2
   // traffic and latency of these reads dominated the step otherwise)
   if constexpr (stage_tables<NR, T>()) {
-    stage_tables_to_lds<NR, T>(kin_s, tw_s, mask_s, tb.kin, tb.tw, tb.mask);
-    lds_stage(frag_s, ws + (CP == kCpBf16x3 ? a.lay.tmfrag : a.lay.tmfrag_f), StagedTables<NR, T>::frag_bytes);
-    if (tid < StagedTables<NR, T>::x_pad) x_s[tid] = tid < nj ? static_cast<float>(tb.x[tid]) : 0.0f;
+    stage_tables_to_lds<NR, T, false, W>(kin_s, tw_s, mask_s, tb.kin, tb.tw, tb.mask);
+    lds_stage(frag_s, ws + (CP == kCpBf16x3 ? a.lay.tmfrag : a.lay.tmfrag_f), StagedTables<NR, T, false, true, W>::frag_bytes);
+    if (tid < StagedTables<NR, T, false, true, W>::x_pad) x_s[tid] = tid < nj ? static_cast<float>(tb.x[tid]) : 0.0f;
     __syncthreads();
   }
 
@@ -985,7 +992,7 @@ void mol_step_kernel(MolArgs a) {
       mask = opaque(tb.mask);
     }
     const cx<T>* vph = opaque(tb.vph);
-    if (active) kinetic_half<T, NR, false, SP, 0, tw_scaled<NR, T>()>(v, slot, q, kin, tw);
+    if (active) kinetic_half<T, NR, false, SP, 0, tw_scaled<NR, T>(), W>(v, slot, q, kin, tw);
     if constexpr (PARTS) {
       if (active) {
 #pragma unroll
@@ -1023,17 +1030,17 @@ void mol_step_kernel(MolArgs a) {
       if constexpr (kPrioContraction<T, NR, CP>) __builtin_amdgcn_s_setprio(1);
       // contraction operands: from the LDS copy (complex64 forms) or the workspace
       if constexpr (CP == kCpBf16x3) {
-        coupling_mfma<NR>(sh, nj, h * NRH, reinterpret_cast<const unsigned short*>(frag_s),
+        coupling_mfma<NR, W>(sh, nj, h * NRH, reinterpret_cast<const unsigned short*>(frag_s),
                           reinterpret_cast<const float*>(x_s), tb.mudt, E);
       } else if constexpr (stage_tables<NR, T>()) {
-        coupling_mfma_exact<T, NR, NK, true>(sh, nj, h * NRH, reinterpret_cast<const T*>(frag_s),
+        coupling_mfma_exact<T, NR, NK, true, W>(sh, nj, h * NRH, reinterpret_cast<const T*>(frag_s),
                                                        reinterpret_cast<const T*>(x_s), tb.mudt, E);
       } else {
         const T* frag = reinterpret_cast<const T*>(ws + (sizeof(T) == 8 ? a.lay.tmfrag_d : a.lay.tmfrag_f));
         if (__builtin_expect(large, 0)) {
-          coupling_mfma_exact<T, NR, NK, true>(sh, nj, h * NRH, frag, tb.x, tb.mudt, E);
+          coupling_mfma_exact<T, NR, NK, true, W>(sh, nj, h * NRH, frag, tb.x, tb.mudt, E);
         } else {
-          coupling_mfma_exact<T, NR, NK, false>(sh, nj, h * NRH, frag, tb.x, tb.mudt, E);
+          coupling_mfma_exact<T, NR, NK, false, W>(sh, nj, h * NRH, frag, tb.x, tb.mudt, E);
         }
       }
       if constexpr (kPrioContraction<T, NR, CP>) __builtin_amdgcn_s_setprio(0);
@@ -1047,7 +1054,7 @@ void mol_step_kernel(MolArgs a) {
       }
     }
     if (active) {
-      kinetic_half<T, NR, false, SP, 0, tw_scaled<NR, T>()>(v, slot, q, kin, tw);
+      kinetic_half<T, NR, false, SP, 0, tw_scaled<NR, T>(), W>(v, slot, q, kin, tw);
       // absorber: when it lies within the last quarter of the grid only
       // those registers are tested (one uniform branch), otherwise all
       constexpr int P0 = (3 * R1) / 4;
@@ -1082,9 +1089,9 @@ void mol_step_kernel(MolArgs a) {
       __syncthreads();
       for (int rl = tid; rl < NRH; rl += nthr) {
         T acc = T(0);
-        cx<T> g0 = sh[rl], e0 = sh[lds_row<NR, T, SP>(nj) + rl];
+        cx<T> g0 = sh[rl], e0 = sh[lds_row<NR, T, SP, W>(nj) + rl];
         for (int J = 0; J + 1 < nj; ++J) {
-          const cx<T> g1 = sh[lds_row<NR, T, SP>(J + 1) + rl], e1 = sh[lds_row<NR, T, SP>(nj + J + 1) + rl];
+          const cx<T> g1 = sh[lds_row<NR, T, SP, W>(J + 1) + rl], e1 = sh[lds_row<NR, T, SP, W>(nj + J + 1) + rl];
           // PARTS: e = i e~
           const T t = PARTS ? (g0.y * e1.x - g0.x * e1.y) + (g1.y * e0.x - g1.x * e0.y)
                             : g0.x * e1.x + g0.y * e1.y + g1.x * e0.x + g1.y * e0.y;
@@ -1113,23 +1120,23 @@ void mol_step_kernel(MolArgs a) {
   }
 }
 
-template <typename T, int NR, int CP, bool ONE, bool PARTS>
+template <typename T, int NR, int CP, bool ONE, bool PARTS, int W>
 int launch_mol_t1(const MolArgs& a, hipStream_t s) {
-  static_assert(NR == FftShape<NR, T>::R1 * FftShape<NR, T>::R2, "FFT shape");
-  constexpr int R2 = FftShape<NR, T>::R2, SP = PARTS ? 2 : fwd_split<NR, T>();
+  static_assert(NR == FftShape<NR, T, W>::R1 * FftShape<NR, T, W>::R2, "FFT shape");
+  constexpr int R2 = FftShape<NR, T, W>::R2, SP = PARTS ? 2 : fwd_split<NR, T, W>();
   const int L = 2 * a.nj;
   int threads = ((L * R2 + 63) / 64) * 64;
   if (threads < 64) threads = 64;
-  const size_t shm = lds_table_bytes<NR, T>() +
-                     sizeof(cx<T>) * (static_cast<size_t>(lds_line_start(L, fwd_line_stride<NR, T, SP>(), sizeof(cx<T>))) +
+  const size_t shm = lds_table_bytes<NR, T, W>() +
+                     sizeof(cx<T>) * (static_cast<size_t>(lds_line_start(L, fwd_line_stride<NR, T, SP, W>(), sizeof(cx<T>))) +
                                       NR / SP) +
                      16 * 4 * sizeof(double);
   static std::atomic<unsigned long long> lds_set{0};
   if (shm > 64 * 1024) {
-    const hipError_t e = allow_large_lds(reinterpret_cast<const void*>(&mol_step_kernel<T, NR, CP, ONE, PARTS>), lds_set);
+    const hipError_t e = allow_large_lds(reinterpret_cast<const void*>(&mol_step_kernel<T, NR, CP, ONE, PARTS, W>), lds_set);
     if (e != hipSuccess) return static_cast<int>(e);
   }
-  hipLaunchKernelGGL((mol_step_kernel<T, NR, CP, ONE, PARTS>), dim3(a.n_mol), dim3(threads), shm, s, a);
+  hipLaunchKernelGGL((mol_step_kernel<T, NR, CP, ONE, PARTS, W>), dim3(a.n_mol), dim3(threads), shm, s, a);
   return static_cast<int>(hipGetLastError());
 }
 
@@ -1149,12 +1156,35 @@ constexpr bool mol_parts() {
   return NR == 512 || (NR == 256 && CP == kCpExactHalf && ONE) || (NR == 64 && CP != kCpExactHalf);
 }
 
+// Where wide lines (complex64, n_r = 256: 16 values on 16 lanes, one exchange round,
+// 128 registers) beat 32 values on 8 lanes, both measured (us per launch, 8 lanes / 16
+// lanes, FP32 form unless said):
+//  N_J <= 8: up to four wavefronts per workgroup, four per execution unit instead of
+//    three (30,000 molecules, N_J = 1: 428 / 316; 3: 558 / 406; 4: 636 / 512; 7: 724 /
+//    676; 8: 846 / 727; mixed form 423 / 342, 556 / 430, 634 / 538, 731 / 712, 827 /
+//    795).  From N_J = 9 a workgroup has five to eight wavefronts, of which a CU takes
+//    two instead of four of half as many (N_J = 9: 1030 / 1425; 11: 1068 / 1431);
+//  any N_J up to 512 molecules, where two workgroups per CU hold all of them and the
+//    serial work of a wavefront is what a launch takes (N_J = 11, 64 molecules: 26.8 /
+//    19.9, mixed 24.8 / 18.8; 512: 37.4 / 31.8, 32.2 / 28.2; 700: 46.5 / 43.9, 39.2 /
+//    41.6; N_J = 16, 512: 40.0 / 35.3).
+constexpr int kWideMaxNJ = 8, kWideMaxMol = 512;
+template <typename T, int NR>
+constexpr bool wide_lines() { return sizeof(T) == 4 && NR == 256; }
+
 template <typename T, int NR, int CP, bool ONE>
 int launch_mol_t2(const MolArgs& a, hipStream_t s) {
   if constexpr (sizeof(T) == 8 && mol_parts<NR, CP, ONE>()) {
-    if (NR != 512 || a.nj > 1) return launch_mol_t1<T, NR, CP, ONE, true>(a, s);
+    if (NR != 512 || a.nj > 1) return launch_mol_t1<T, NR, CP, ONE, true, 1>(a, s);
   }
-  if constexpr (sizeof(T) == 4 || NR == 512 || !mol_parts<NR, CP, ONE>()) return launch_mol_t1<T, NR, CP, ONE, false>(a, s);
+  static_assert(kHalfKMaxNJ == kWideMaxNJ, "the half-K form at n_r = 256 has wide lines only");
+  if constexpr (wide_lines<T, NR>()) {
+    if (CP == kCpExactHalf || a.nj <= kWideMaxNJ || a.n_mol <= kWideMaxMol)
+      return launch_mol_t1<T, NR, CP, ONE, false, 2>(a, s);
+  }
+  if constexpr (wide_lines<T, NR>() ? CP != kCpExactHalf
+                                    : (sizeof(T) == 4 || NR == 512 || !mol_parts<NR, CP, ONE>()))
+    return launch_mol_t1<T, NR, CP, ONE, false, 1>(a, s);
 }
 
 // The contraction form by N_J (see kCpExact...), and a single-step instantiation:
