@@ -111,27 +111,27 @@ __device__ __forceinline__ void coupling_jm_point(cx<T>* g, cx<T>* e, const cx<T
 // The tables are staged in the compact layout (complex64 forms), which keeps
 // a workgroup small enough for ten molecules per CU.
 // Occupancy target: three waves per SIMD for the complex64 form (168
-// registers); the complex128 form two in single-step launches (at n_r = 512,
-// whose lines take 128 registers a lane, 1267 -> 941 us per 10,000 molecules), and
-// what it needs in the others, whose step loop would spill there (969 -> 1120 us
-// per 4,000 molecules and three steps at n_r = 512).
-template <typename T, bool ONE>
-struct JmOcc { static constexpr int waves = sizeof(T) == 4 ? 3 : (ONE ? 2 : 1); };
+// registers; four with wide lines); the complex128 form two in single-step
+// launches (at n_r = 512, whose lines take 128 registers a lane, 1267 -> 941 us per
+// 10,000 molecules), and what it needs in the others, whose step loop would spill
+// there (969 -> 1120 us per 4,000 molecules and three steps at n_r = 512).
+template <typename T, bool ONE, int W>
+struct JmOcc { static constexpr int waves = sizeof(T) == 4 ? (W > 1 ? 4 : 3) : (ONE ? 2 : 1); };
 
 // ONE: the launch advances exactly one step (as in the m = 0 kernel).
-template <typename T, int NR, bool ONE>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(JmOcc<T, ONE>::waves))) void mol_jm_kernel(MolArgs a) {
-  constexpr int R1 = FftShape<NR, T>::R1, R2 = FftShape<NR, T>::R2;
+template <typename T, int NR, bool ONE, int W>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(JmOcc<T, ONE, W>::waves))) void mol_jm_kernel(MolArgs a) {
+  constexpr int R1 = FftShape<NR, T, W>::R1, R2 = FftShape<NR, T, W>::R2;
   constexpr int NB = 4, L = 2 * NB;
-  constexpr int SP = fwd_split<NR, T>(), PH = R1 / SP, NRH = NR / SP;
-  typedef StagedTables<NR, T, true, false> TBL;
+  constexpr int SP = fwd_split<NR, T, W>(), PH = R1 / SP, NRH = NR / SP;
+  typedef StagedTables<NR, T, true, false, W> TBL;
   constexpr size_t TB = TBL::bytes;
   extern __shared__ __align__(16) unsigned char smem[];
   cx<T>* kin_s = reinterpret_cast<cx<T>*>(smem);
   cx<T>* tw_s = kin_s + NR;
   T* mask_s = reinterpret_cast<T*>(tw_s + TBL::tw_elems);
   cx<T>* sh = reinterpret_cast<cx<T>*>(smem + TB);
-  double* red = reinterpret_cast<double*>(smem + TB + sizeof(cx<T>) * lds_row<NR, T>(L));
+  double* red = reinterpret_cast<double*>(smem + TB + sizeof(cx<T>) * lds_row<NR, T, SP, W>(L));
 
   const int mol = blockIdx.x;
   const int tid = threadIdx.x;
@@ -143,7 +143,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(JmOcc<T, ON
   const char* ws = a.ws;
   const bool dbl = sizeof(T) == 8;
   const cx<T>* kin_g = reinterpret_cast<const cx<T>*>(ws + (dbl ? a.lay.kin_d : a.lay.kin_f));
-  const cx<T>* tw_g = reinterpret_cast<const cx<T>*>(ws + (dbl ? a.lay.tw_d : a.lay.tw_f));
+  const cx<T>* tw_g = reinterpret_cast<const cx<T>*>(ws + (dbl ? a.lay.tw_d : tw_scaled<NR, T>() ? a.lay.tw_fs : a.lay.tw_f));
   const cx<T>* vph_g = reinterpret_cast<const cx<T>*>(ws + (dbl ? a.lay.vph_d : a.lay.vph_f));
   const T* mudt = reinterpret_cast<const T*>(ws + (dbl ? a.lay.mudt_d : a.lay.mudt_f));
   const T* mask_g = reinterpret_cast<const T*>(ws + (dbl ? a.lay.mask_d : a.lay.mask_f));
@@ -179,14 +179,14 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(JmOcc<T, ON
   const T inv_a2 = a2d > 0.0 ? static_cast<T>(1.0 / a2d) : T(0);
 
   cx<T>* psi = reinterpret_cast<cx<T>*>(a.psi) + static_cast<size_t>(mol) * L * NR;
-  cx<T>* slot = sh + lds_row<NR, T>(line);
+  cx<T>* slot = sh + lds_row<NR, T, SP, W>(line);
   const int loff = line * NR + q;
   const int voff = (st * a.nj + jl) * NR + q;   // potential phases depend on (state, j)
   cx<T> vv[R1];
 #pragma unroll
   for (int p = 0; p < R1; ++p) vv[p] = psi[loff + R2 * p];
   if constexpr (stage_tables<NR, T>()) {
-    stage_tables_to_lds<NR, T, true>(kin_s, tw_s, mask_s, kin_g, tw_g, mask_g);
+    stage_tables_to_lds<NR, T, true, W>(kin_s, tw_s, mask_s, kin_g, tw_g, mask_g);
     __syncthreads();
   }
 
@@ -206,7 +206,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(JmOcc<T, ON
       mask = opaque(mask_g);
     }
     const cx<T>* vph = opaque(vph_g);
-    kinetic_half<T, NR, false, SP, TBL::TWC>(vv, slot, q, kin, tw);
+    kinetic_half<T, NR, false, SP, TBL::TWC, tw_scaled<NR, T>(), W>(vv, slot, q, kin, tw);
 #pragma unroll
     for (int h = 0; h < SP; ++h) {
 #pragma unroll
@@ -219,14 +219,14 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(JmOcc<T, ON
         cx<T> g[NB], e[NB];
 #pragma unroll
         for (int k = 0; k < NB; ++k) {
-          g[k] = sh[lds_row<NR, T>(k) + rl];
-          e[k] = sh[lds_row<NR, T>(NB + k) + rl];
+          g[k] = sh[lds_row<NR, T, SP, W>(k) + rl];
+          e[k] = sh[lds_row<NR, T, SP, W>(NB + k) + rl];
         }
         coupling_jm_point(g, e, v, aa, inv_a, inv_a2, mudt[h * NRH + rl]);
 #pragma unroll
         for (int k = 0; k < NB; ++k) {
-          sh[lds_row<NR, T>(k) + rl] = g[k];
-          sh[lds_row<NR, T>(NB + k) + rl] = e[k];
+          sh[lds_row<NR, T, SP, W>(k) + rl] = g[k];
+          sh[lds_row<NR, T, SP, W>(NB + k) + rl] = e[k];
         }
       }
       __syncthreads();
@@ -236,7 +236,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(JmOcc<T, ON
         vv[p] = phase_mul(slot[q + R2 * pp], vph[voff + R2 * p]);
       }
     }
-    kinetic_half<T, NR, false, SP, TBL::TWC>(vv, slot, q, kin, tw);
+    kinetic_half<T, NR, false, SP, TBL::TWC, tw_scaled<NR, T>(), W>(vv, slot, q, kin, tw);
     // absorber: when it lies within the last quarter of the grid only those
     // registers are tested (one uniform branch), otherwise all
     constexpr int P0 = (3 * R1) / 4;
@@ -269,7 +269,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(JmOcc<T, ON
       cx<double> g[NB], e[NB];
 #pragma unroll
       for (int k = 0; k < NB; ++k) {
-        const cx<T> gt = sh[lds_row<NR, T>(k) + rl], et = sh[lds_row<NR, T>(NB + k) + rl];
+        const cx<T> gt = sh[lds_row<NR, T, SP, W>(k) + rl], et = sh[lds_row<NR, T, SP, W>(NB + k) + rl];
         g[k] = {static_cast<double>(gt.x), static_cast<double>(gt.y)};
         e[k] = {static_cast<double>(et.x), static_cast<double>(et.y)};
       }
@@ -325,32 +325,42 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(JmOcc<T, ON
 
 // LDS bytes of one (j, m) workgroup: staged tables, the eight line slots,
 // and the reduction scratch
-template <typename T, int NR>
+template <typename T, int NR, int W>
 constexpr size_t jm_lds_bytes() {
-  return StagedTables<NR, T, true, false>::bytes +
-         sizeof(cx<T>) * static_cast<size_t>(lds_line_start(8, fwd_line_stride<NR, T>(), sizeof(cx<T>))) +
+  constexpr int SP = fwd_split<NR, T, W>();
+  return StagedTables<NR, T, true, false, W>::bytes +
+         sizeof(cx<T>) * static_cast<size_t>(lds_line_start(8, fwd_line_stride<NR, T, SP, W>(), sizeof(cx<T>))) +
          6 * 16 * sizeof(double);
 }
 
-template <typename T, int NR, bool ONE>
+template <typename T, int NR, bool ONE, int W>
 int launch_jm_t1(const MolArgs& a, hipStream_t s) {
-  constexpr int R2 = FftShape<NR, T>::R2;
+  constexpr int R2 = FftShape<NR, T, W>::R2;
   const int threads = 8 * R2;
-  const size_t shm = jm_lds_bytes<T, NR>();
+  const size_t shm = jm_lds_bytes<T, NR, W>();
   if (shm > mol_lds_limit()) return static_cast<int>(hipErrorInvalidValue);
   static std::atomic<unsigned long long> lds_set{0};
   if (shm > 64 * 1024) {
-    const hipError_t e = allow_large_lds(reinterpret_cast<const void*>(&mol_jm_kernel<T, NR, ONE>), lds_set);
+    const hipError_t e = allow_large_lds(reinterpret_cast<const void*>(&mol_jm_kernel<T, NR, ONE, W>), lds_set);
     if (e != hipSuccess) return static_cast<int>(e);
   }
-  hipLaunchKernelGGL((mol_jm_kernel<T, NR, ONE>), dim3(a.n_mol), dim3(threads), shm, s, a);
+  hipLaunchKernelGGL((mol_jm_kernel<T, NR, ONE, W>), dim3(a.n_mol), dim3(threads), shm, s, a);
   return static_cast<int>(hipGetLastError());
 }
+
+// Wide lines (mol_impl.h) while the launch is bound by the serial work of a
+// wavefront: us per step, 8 lanes per line / 16: 1 molecule 18.6 / 13.1, 333 20.9 /
+// 16.0, 1,500 29.1 / 26.9, 5,000 72.4 / 70.7, 30,000 360 / 370, 200,000 2106 / 2200.
+constexpr int kJmWideMaxMol = 2048;
 
 // a single-step instantiation for the coupled step's launches
 template <typename T, int NR>
 int launch_jm_t(const MolArgs& a, hipStream_t s) {
-  return a.n_steps == 1 ? launch_jm_t1<T, NR, true>(a, s) : launch_jm_t1<T, NR, false>(a, s);
+  if constexpr (wide_lines<T, NR>()) {
+    if (a.n_mol <= kJmWideMaxMol)
+      return a.n_steps == 1 ? launch_jm_t1<T, NR, true, 2>(a, s) : launch_jm_t1<T, NR, false, 2>(a, s);
+  }
+  return a.n_steps == 1 ? launch_jm_t1<T, NR, true, 1>(a, s) : launch_jm_t1<T, NR, false, 1>(a, s);
 }
 
 template <typename T>
