@@ -289,12 +289,15 @@ __global__ __launch_bounds__(512) void mol_adj_kernel(MolAdjArgs a) {
 // wavefronts per execution unit, and at n_r = 256 the kernel spilled.  Here a
 // round's chi and lambda are in LDS and the other round's in registers, the
 // tables are staged, and the node rotation is taken on its two independent pairs
-// of parts in turn (coupling_adj_pairs), which halves a tile's registers.  Reverse
-// step with psi^{n+1} given, whole-line form -> this one: 503 -> 394 us (20,000
-// molecules, n_r = 128, J <= 6; the three reads and one write of 287 MB are 221 us
-// at a copy's rate), 505 -> 447 (12,000, J <= 10), 1027 -> 553 (10,000, n_r = 256,
-// J <= 6), 1155 -> 637 (6,000, J <= 10), 1002 -> 703 (8,000, n_r = 512, J <= 3),
-// 363 -> 307 (30,000, n_r = 64, J <= 7).
+// of parts in turn (coupling_adj_pairs), which halves a tile's registers.  At n_r =
+// 256 the lines are wide (mol_impl.h), in one round: 64 registers of values instead
+// of 128.  Reverse step with psi^{n+1} given, whole-line form -> this one: 503 -> 394
+// us (20,000 molecules, n_r = 128, J <= 6; the three reads and one write of 287 MB are
+// 221 us at a copy's rate), 505 -> 447 (12,000, J <= 10), 1002 -> 703 (8,000, n_r =
+// 512, J <= 3), 363 -> 307 (30,000, n_r = 64, J <= 7); at n_r = 256, with 8 lanes per
+// line in between: 1027 -> 553 -> 495 (10,000, J <= 6), 1155 -> 637 -> 619 (6,000,
+// J <= 10), J <= 3, 20,000: 723 -> 597, J = 0, 30,000: 779 -> 464, 300 molecules, J <=
+// 6: 42 -> 26.
 
 // One round of the coupling's adjoint (ADJ) or of the coupling (segment
 // recompute).  The rotation takes (g re, e im) and (e re, g im) to themselves:
@@ -303,13 +306,13 @@ __global__ __launch_bounds__(512) void mol_adj_kernel(MolAdjArgs a) {
 // A: chi; B: the adjoint at the coupling's output, on return at its input (the
 // recompute: C(E) chi).  Rows as in the forward step; rows J >= nj read row
 // nj - 1, whose column of T is zero.
-template <int NR, bool ADJ, bool KH>
+template <int NR, bool ADJ, bool KH, int W>
 __device__ __forceinline__ double coupling_adj_pairs(const cx<float>* A, cx<float>* B, int nj, int r0,
                                                      const float* __restrict__ frag, const float* __restrict__ x,
                                                      const float* __restrict__ mudt, float E) {
   typedef MfmaK4<float> MK;
   typedef MK::acc acc_t;
-  constexpr int NK = KH ? 2 : 4, NRH = NR / fwd_split<NR, float>();
+  constexpr int NK = KH ? 2 : 4, NRH = NR / fwd_split<NR, float, W>();
   const int lane = fresh_lane();
   const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) >> 6);
   const int nwaves = (blockDim.x + 63) >> 6;
@@ -325,8 +328,8 @@ __device__ __forceinline__ double coupling_adj_pairs(const cx<float>* A, cx<floa
       Tf[i < NK ? i : 0] = frag[(0 * 64 + lane) * 4 + i];
       Tt[i < NK ? i : 0] = frag[(1 * 64 + lane) * 4 + i];
       const int Jc = J < nj ? J : nj - 1;
-      og[i < NK ? i : 0] = lds_row<NR, float>(Jc);
-      oe[i < NK ? i : 0] = lds_row<NR, float>(nj + Jc);
+      og[i < NK ? i : 0] = lds_row<NR, float, fwd_split<NR, float, W>(), W>(Jc);
+      oe[i < NK ? i : 0] = lds_row<NR, float, fwd_split<NR, float, W>(), W>(nj + Jc);
     }
   }
   double grad = 0.0;
@@ -347,7 +350,7 @@ __device__ __forceinline__ double coupling_adj_pairs(const cx<float>* A, cx<floa
     }
     const float mr = mudt[r];
     float sn[4], vs[4];
-    sin_vers_tile<NR>(mr * E, xk, sn, vs);
+    sin_vers_tile<(W > 1 ? 128 : NR)>(mr * E, xk, sn, vs);
     double gl = 0.0;
     acc_t out[2][2];
 #pragma unroll
@@ -397,35 +400,35 @@ __device__ __forceinline__ double coupling_adj_pairs(const cx<float>* A, cx<floa
 
 // LDS of the complex64 form: transform tables (compact twiddles), the round's
 // lambda rows and chi rows, the reduction scratch
-template <int NR>
+template <int NR, int W>
 struct Adj32Shape {
-  typedef StagedTables<NR, float, true, false> TBL;
-  static constexpr int SP = fwd_split<NR, float>();
+  typedef StagedTables<NR, float, true, false, W> TBL;
+  static constexpr int SP = fwd_split<NR, float, W>();
   static size_t buf_bytes(int nj) {
-    return (sizeof(cx<float>) * static_cast<size_t>(lds_line_start(2 * nj, fwd_line_stride<NR, float>(), 8)) + 15) / 16 * 16;
+    return (sizeof(cx<float>) * static_cast<size_t>(lds_line_start(2 * nj, fwd_line_stride<NR, float, SP, W>(), 8)) + 15) / 16 * 16;
   }
   static size_t bytes(int nj) { return TBL::bytes + 2 * buf_bytes(nj) + 16 * sizeof(double); }
 };
 
 // Wavefronts per execution unit: four where the lines' 16 points per lane (twice:
 // chi and lambda) and a half-K tile fit 128 registers, three with the full-K tile,
-// two at 32 points per lane (more spilled 54 to 141 registers: 553 -> 725 us for
-// 10,000 molecules at n_r = 256, J <= 6; 394 -> 435 us at three instead of four
-// for 20,000 at n_r = 128).
-template <int NR, bool KH>
-constexpr int adj32_waves() { return FftShape<NR, float>::R1 > 16 ? 2 : (KH ? 4 : 3); }
+// two at 32 points per lane (three spilled 55 to 139 registers at n_r = 512: 703 ->
+// 846 us for 8,000 molecules, J <= 3; 394 -> 435 us at three instead of four for
+// 20,000 at n_r = 128).
+template <int NR, bool KH, int W>
+constexpr int adj32_waves() { return FftShape<NR, float, W>::R1 > 16 ? 2 : (KH ? 4 : 3); }
 
-template <int NR, bool NEXT, bool KH>
+template <int NR, bool NEXT, bool KH, int W>
 __global__ __launch_bounds__(512)
-__attribute__((amdgpu_waves_per_eu(adj32_waves<NR, KH>()))) void mol_adj32_kernel(MolAdjArgs a) {
-  typedef Adj32Shape<NR> S;
+__attribute__((amdgpu_waves_per_eu(adj32_waves<NR, KH, W>()))) void mol_adj32_kernel(MolAdjArgs a) {
+  typedef Adj32Shape<NR, W> S;
   typedef typename S::TBL TBL;
-  constexpr int R1 = FftShape<NR, float>::R1, R2 = FftShape<NR, float>::R2;
+  constexpr int R1 = FftShape<NR, float, W>::R1, R2 = FftShape<NR, float, W>::R2;
   constexpr int SP = S::SP, PH = R1 / SP, NRH = NR / SP, TWC = TBL::TWC;
   extern __shared__ __align__(16) unsigned char smem[];
   const int nj = a.nj;
   const int L = 2 * nj;
-  const int buf = (lds_row<NR, float>(L) + 1) / 2 * 2;
+  const int buf = (lds_row<NR, float, fwd_split<NR, float, W>(), W>(L) + 1) / 2 * 2;
   cx<float>* kin = reinterpret_cast<cx<float>*>(smem);
   cx<float>* tw = kin + NR;
   float* mask = reinterpret_cast<float*>(tw + TBL::tw_elems);
@@ -453,8 +456,8 @@ __attribute__((amdgpu_waves_per_eu(adj32_waves<NR, KH>()))) void mol_adj32_kerne
   const cx<float>* psi = static_cast<const cx<float>*>(a.psi_n) + base;
   const cx<float>* nxt = static_cast<const cx<float>*>(a.psi_np1) + base;
   cx<float>* lpsi = static_cast<cx<float>*>(a.lpsi) + base;
-  cx<float>* slot = B + lds_row<NR, float>(line);    // this line's row of the round
-  cx<float>* aslot = A + lds_row<NR, float>(line);
+  cx<float>* slot = B + lds_row<NR, float, fwd_split<NR, float, W>(), W>(line);    // this line's row of the round
+  cx<float>* aslot = A + lds_row<NR, float, fwd_split<NR, float, W>(), W>(line);
   const int loff = line * NR + q;
 
   // ---- chi = V K psi, and psi_pre = K V C(chi) or psi^{n+1} = m psi_pre (v)
@@ -463,12 +466,12 @@ __attribute__((amdgpu_waves_per_eu(adj32_waves<NR, KH>()))) void mol_adj32_kerne
 #pragma unroll
     for (int p = 0; p < R1; ++p) ch[p] = psi[loff + R2 * p];
   }
-  stage_tables_to_lds<NR, float, true>(kin, tw, mask, reinterpret_cast<const cx<float>*>(ws + a.lay.kin_f),
-                                       reinterpret_cast<const cx<float>*>(ws + a.lay.tw_f),
+  stage_tables_to_lds<NR, float, true, W>(kin, tw, mask, reinterpret_cast<const cx<float>*>(ws + a.lay.kin_f),
+                                       reinterpret_cast<const cx<float>*>(ws + (tw_scaled<NR, float>() ? a.lay.tw_fs : a.lay.tw_f)),
                                        reinterpret_cast<const float*>(ws + a.lay.mask_f));
   __syncthreads();
   if (active) {
-    kinetic_half<float, NR, false, SP, TWC>(ch, slot, q, kin, tw);
+    kinetic_half<float, NR, false, SP, TWC, tw_scaled<NR, float>(), W>(ch, slot, q, kin, tw);
 #pragma unroll
     for (int p = 0; p < R1; ++p) ch[p] = phase_mul(ch[p], vph[loff + R2 * p]);
   }
@@ -485,7 +488,7 @@ __attribute__((amdgpu_waves_per_eu(adj32_waves<NR, KH>()))) void mol_adj32_kerne
         for (int pp = 0; pp < PH; ++pp) aslot[q + R2 * pp] = ch[h * PH + pp];
       }
       __syncthreads();
-      coupling_adj_pairs<NR, false, KH>(A, B, nj, h * NRH, frag, xk, mudt, E);
+      coupling_adj_pairs<NR, false, KH, W>(A, B, nj, h * NRH, frag, xk, mudt, E);
       __syncthreads();
       if (active) {
 #pragma unroll
@@ -495,7 +498,7 @@ __attribute__((amdgpu_waves_per_eu(adj32_waves<NR, KH>()))) void mol_adj32_kerne
         }
       }
     }
-    if (active) kinetic_half<float, NR, false, SP, TWC>(v, slot, q, kin, tw);   // psi_pre (before the absorber)
+    if (active) kinetic_half<float, NR, false, SP, TWC, tw_scaled<NR, float>(), W>(v, slot, q, kin, tw);   // psi_pre (before the absorber)
   }
 
   // ---- reverse: dipole and absorber terms (lambda replaces v), then K^H V^H
@@ -508,8 +511,8 @@ __attribute__((amdgpu_waves_per_eu(adj32_waves<NR, KH>()))) void mol_adj32_kerne
   // rows of the other state's neighbours J - 1 and J + 1 (their own line where
   // there is none: its factor is zero)
   const int sb = (1 - s_of_line) * nj;
-  const cx<float>* rowm = B + lds_row<NR, float>(J_of_line > 0 ? sb + J_of_line - 1 : line);
-  const cx<float>* rowp = B + lds_row<NR, float>(J_of_line + 1 < nj ? sb + J_of_line + 1 : line);
+  const cx<float>* rowm = B + lds_row<NR, float, fwd_split<NR, float, W>(), W>(J_of_line > 0 ? sb + J_of_line - 1 : line);
+  const cx<float>* rowp = B + lds_row<NR, float, fwd_split<NR, float, W>(), W>(J_of_line + 1 < nj ? sb + J_of_line + 1 : line);
 #pragma unroll
   for (int h = 0; h < SP; ++h) {
     if (h > 0) __syncthreads();
@@ -539,7 +542,7 @@ __attribute__((amdgpu_waves_per_eu(adj32_waves<NR, KH>()))) void mol_adj32_kerne
   }
   __syncthreads();
   if (active) {
-    kinetic_half<float, NR, true, SP, TWC>(v, slot, q, kin, tw);
+    kinetic_half<float, NR, true, SP, TWC, tw_scaled<NR, float>(), W>(v, slot, q, kin, tw);
 #pragma unroll
     for (int p = 0; p < R1; ++p) v[p] = phase_mul_conj(v[p], vph[loff + R2 * p]);
   }
@@ -554,7 +557,7 @@ __attribute__((amdgpu_waves_per_eu(adj32_waves<NR, KH>()))) void mol_adj32_kerne
       }
     }
     __syncthreads();
-    grad += coupling_adj_pairs<NR, true, KH>(A, B, nj, h * NRH, frag, xk, mudt, E);
+    grad += coupling_adj_pairs<NR, true, KH, W>(A, B, nj, h * NRH, frag, xk, mudt, E);
     __syncthreads();
     if (active) {
 #pragma unroll
@@ -565,7 +568,7 @@ __attribute__((amdgpu_waves_per_eu(adj32_waves<NR, KH>()))) void mol_adj32_kerne
     }
   }
   if (active) {
-    kinetic_half<float, NR, true, SP, TWC>(v, slot, q, kin, tw);
+    kinetic_half<float, NR, true, SP, TWC, tw_scaled<NR, float>(), W>(v, slot, q, kin, tw);
 #pragma unroll
     for (int p = 0; p < R1; ++p) lpsi[loff + R2 * p] = v[p];
   }
@@ -574,16 +577,16 @@ __attribute__((amdgpu_waves_per_eu(adj32_waves<NR, KH>()))) void mol_adj32_kerne
   if (tid == 0) a.lE[mol] = sums[0];
 }
 
-template <int NR, bool NEXT, bool KH>
+template <int NR, bool NEXT, bool KH, int W>
 static int launch_mol_adj32(const MolAdjArgs& a, hipStream_t s) {
-  const int threads = (2 * a.nj * FftShape<NR, float>::R2 + 63) / 64 * 64;
-  const size_t shm = Adj32Shape<NR>::bytes(a.nj);
+  const int threads = (2 * a.nj * FftShape<NR, float, W>::R2 + 63) / 64 * 64;
+  const size_t shm = Adj32Shape<NR, W>::bytes(a.nj);
   static std::atomic<unsigned long long> lds_set{0};
   if (shm > 64 * 1024) {
-    const hipError_t e = allow_large_lds(reinterpret_cast<const void*>(&mol_adj32_kernel<NR, NEXT, KH>), lds_set);
+    const hipError_t e = allow_large_lds(reinterpret_cast<const void*>(&mol_adj32_kernel<NR, NEXT, KH, W>), lds_set);
     if (e != hipSuccess) return static_cast<int>(e);
   }
-  hipLaunchKernelGGL((mol_adj32_kernel<NR, NEXT, KH>), dim3(a.n_mol), dim3(threads), shm, s, a);
+  hipLaunchKernelGGL((mol_adj32_kernel<NR, NEXT, KH, W>), dim3(a.n_mol), dim3(threads), shm, s, a);
   return static_cast<int>(hipGetLastError());
 }
 
@@ -612,7 +615,7 @@ static int launch_mol_adj64(const MolAdjArgs& a, hipStream_t s) {
 template <typename T, int NR, bool NEXT, bool KH>
 static int launch_mol_adj_n(const MolAdjArgs& a, hipStream_t s) {
   if constexpr (sizeof(T) == 4)
-    return launch_mol_adj32<NR, NEXT, KH>(a, s);
+    return launch_mol_adj32<NR, NEXT, KH, wide_lines<float, NR>() ? 2 : 1>(a, s);
   else
     return launch_mol_adj64<NR, NEXT, KH>(a, s);
 }
