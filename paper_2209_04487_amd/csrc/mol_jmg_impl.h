@@ -70,6 +70,14 @@ struct JmgTabShape {
   static constexpr size_t bytes = ph_bytes + mt_bytes + red_bytes;
 };
 
+// Wide lines (mol_impl.h) at n_r = 256 in complex64: us per step, 8 lanes per line /
+// 16: j_max = 4, 30,000 molecules 4523 / 3850, three steps 9369 / 7985; j_max = 3 1831 /
+// 1729, 4332 / 3879, 100 molecules 35.7 / 27.9.  At j_max = 2 the five wavefronts of a
+// workgroup leave a CU room for two (40,000: 1721 / 2010), at j_max = 5 they would need
+// 1,152 threads.
+template <typename T, int NR, int JM>
+constexpr int jmg_wide() { return wide_lines<T, NR>() && (JM == 3 || JM == 4) ? 2 : 1; }
+
 // Radial rounds of the line exchange.  Complex64 workgroups for j_max >= 4
 // hold one molecule per CU whatever their LDS (their registers exclude a
 // second), so they exchange all radial points in one round when the LDS
@@ -78,22 +86,23 @@ struct JmgTabShape {
 // workgroup small enough for several per CU.
 template <typename T, int NR, int JM>
 struct JmgSplit {
-  static constexpr int R2 = FftShape<NR, T>::R2, L = 2 * (JM + 1) * (JM + 1);
-  static constexpr size_t one_round = StagedTables<NR, T, true, false>::bytes +
+  static constexpr int W = jmg_wide<T, NR, JM>(), R2 = FftShape<NR, T, W>::R2, L = 2 * (JM + 1) * (JM + 1);
+  static constexpr size_t one_round = StagedTables<NR, T, true, false, W>::bytes +
                                       JmgTabShape<T, JM>::a16(sizeof(cx<T>) * static_cast<size_t>(lds_line_start(
                                                                                    L, NR + R2, sizeof(cx<T>)))) +
                                       JmgTabShape<T, JM>::bytes;
-  static constexpr int value = (sizeof(T) == 4 && JM >= 4 && one_round <= 160 * 1024) ? 1 : fwd_split<NR, T>();
+  static constexpr int value = (sizeof(T) == 4 && JM >= 4 && one_round <= 160 * 1024) ? 1 : fwd_split<NR, T, W>();
 };
 
 template <typename T, int NR, int JM>
 struct JmgShape : JmgTabShape<T, JM> {
   typedef JmgTabShape<T, JM> TS;
-  static constexpr int R1 = FftShape<NR, T>::R1, R2 = FftShape<NR, T>::R2;
+  static constexpr int W = jmg_wide<T, NR, JM>();
+  static constexpr int R1 = FftShape<NR, T, W>::R1, R2 = FftShape<NR, T, W>::R2;
   static constexpr int NB = (JM + 1) * (JM + 1), L = 2 * NB, threads = L * R2;
   static constexpr int SP = JmgSplit<T, NR, JM>::value, NRH = NR / SP;
   static constexpr int LS = NRH + R2;   // line stride (elements) of the LDS rows
-  typedef StagedTables<NR, T, true, false> TBL;
+  typedef StagedTables<NR, T, true, false, W> TBL;
   static constexpr size_t rows_bytes =
       TS::a16(sizeof(cx<T>) * static_cast<size_t>(lds_line_start(L, LS, sizeof(cx<T>))));
   static constexpr size_t bytes = TBL::bytes + rows_bytes + TS::bytes;
@@ -311,13 +320,14 @@ __device__ __forceinline__ void jmg_dipole_point(const cx<T>* sh, const double* 
 
 // ---------------------------------------------------------------- kernel
 // Waves per SIMD the register allocation targets (complex64): three where
-// that fits more workgroups on a CU than two does.  A seven-wave workgroup
-// (j_max = 4 at R2 = 8) gets one workgroup per CU either way, so it keeps
-// two waves per SIMD and the registers that come with them.
+// that fits more workgroups on a CU than two does (a seven-wave workgroup gets one
+// per CU either way, so it keeps two waves per SIMD and the registers that come with
+// them); four with wide lines.
 template <typename T, int NR, int JM>
 struct JmgOcc {
   static constexpr int wg_waves = (JmgShape<T, NR, JM>::threads + 63) / 64;
-  static constexpr int waves = sizeof(T) == 8 ? 1 : ((12 / wg_waves) > (8 / wg_waves) ? 3 : 2);
+  static constexpr int waves =
+      sizeof(T) == 8 ? 1 : (jmg_wide<T, NR, JM>() > 1 ? 4 : ((12 / wg_waves) > (8 / wg_waves) ? 3 : 2));
 };
 
 template <typename T, int NR, int JM, bool ONE>
@@ -352,7 +362,7 @@ void mol_jmg_kernel(MolArgs a) {
   const char* ws = a.ws;
   const bool dbl = sizeof(T) == 8;
   const cx<T>* kin_g = reinterpret_cast<const cx<T>*>(ws + (dbl ? a.lay.kin_d : a.lay.kin_f));
-  const cx<T>* tw_g = reinterpret_cast<const cx<T>*>(ws + (dbl ? a.lay.tw_d : a.lay.tw_f));
+  const cx<T>* tw_g = reinterpret_cast<const cx<T>*>(ws + (dbl ? a.lay.tw_d : tw_scaled<NR, T>() ? a.lay.tw_fs : a.lay.tw_f));
   const cx<T>* vph_g = reinterpret_cast<const cx<T>*>(ws + (dbl ? a.lay.vph_d : a.lay.vph_f));
   const T* mudt = reinterpret_cast<const T*>(ws + (dbl ? a.lay.mudt_d : a.lay.mudt_f));
   const T* mask_g = reinterpret_cast<const T*>(ws + (dbl ? a.lay.mask_d : a.lay.mask_f));
@@ -391,7 +401,7 @@ void mol_jmg_kernel(MolArgs a) {
   const int loff = line * NR + q;
   const int voff = (st * a.nj + jl) * NR + q;   // potential phases depend on (state, j)
   cx<T> vv[R1];
-  if constexpr (stage_tables<NR, T>()) stage_tables_to_lds<NR, T, true>(kin_s, tw_s, mask_s, kin_g, tw_g, mask_g);
+  if constexpr (stage_tables<NR, T>()) stage_tables_to_lds<NR, T, true, S::W>(kin_s, tw_s, mask_s, kin_g, tw_g, mask_g);
   // The wavepacket's loads: ahead of the coupling tables' arithmetic, which other
   // workgroups' loads would otherwise wait behind; after it for the complex64 forms
   // of one exchange round, which have a CU or nearly so to themselves (6.00 ms
@@ -497,7 +507,7 @@ void mol_jmg_kernel(MolArgs a) {
       mask = opaque(mask_g);
     }
     const cx<T>* vph = opaque(vph_g);
-    kinetic_half<T, NR, false, SP, TBL::TWC>(vv, slot, q, kin, tw);
+    kinetic_half<T, NR, false, SP, TBL::TWC, tw_scaled<NR, T>(), S::W>(vv, slot, q, kin, tw);
     const JmgOps<T, NR, JM> ops(W, xe);
 #pragma unroll
     for (int h = 0; h < SP; ++h) {
@@ -519,7 +529,7 @@ void mol_jmg_kernel(MolArgs a) {
         vv[p] = phase_mul(vv[p] + cmul_conj(slot[q + R2 * pp], eim), vph[voff + R2 * p]);
       }
     }
-    kinetic_half<T, NR, false, SP, TBL::TWC>(vv, slot, q, kin, tw);
+    kinetic_half<T, NR, false, SP, TBL::TWC, tw_scaled<NR, T>(), S::W>(vv, slot, q, kin, tw);
     constexpr int P0 = (3 * R1) / 4;
     if (a.kmask >= R2 * P0) {
 #pragma unroll
