@@ -589,8 +589,8 @@ static int readout_impl(const qd_desc* d, const void* ws, const void* psi, const
       const int e = launch_mol_readout(a, d->n_r, d->prec != MSQD_FP64, s);
       if (e) return check_hip(static_cast<hipError_t>(e), "molecule readout launch");
     } else {
-      const int rc = launch_mol(d, a, s);
-      if (rc) return rc;
+      const int e = launch_jm_readout(a, d->n_r, d->prec != MSQD_FP64, s);
+      if (e) return check_hip(static_cast<hipError_t>(e), "(j, m) molecule readout launch");
     }
   }
   if (!sums) return MSQD_OK;

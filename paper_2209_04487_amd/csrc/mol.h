@@ -86,5 +86,6 @@ int launch_mol_fp32(const MolArgs& a, int n_r, hipStream_t s);
 int launch_mol_mixed(const MolArgs& a, int n_r, hipStream_t s);
 // dipole, norm and yield of the current m = 0 wavepackets (want_*)
 int launch_mol_readout(const MolArgs& a, int n_r, bool f32, hipStream_t s);
+int launch_jm_readout(const MolArgs& a, int n_r, bool f32, hipStream_t s);
 
 }  // namespace msqd

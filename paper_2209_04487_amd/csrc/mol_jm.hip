@@ -149,21 +149,18 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(JmOcc<T, ON
   const T* mask_g = reinterpret_cast<const T*>(ws + (dbl ? a.lay.mask_d : a.lay.mask_f));
   const double* mu = reinterpret_cast<const double*>(ws + a.lay.mu_d);
 
-  // field at the molecule (each component at its own edge of the cell);
-  // a readout-only launch (no step) reads no field
-  double E3[3] = {0.0, 0.0, 0.0};
-  if (a.n_steps > 0) {
-    if (a.Ex != nullptr) {
-      const int c = a.cell_of_mol[mol];
-      const void* f3[3] = {a.Ex, a.Ey, a.Ez};
+  // field at the molecule (each component at its own edge of the cell)
+  double E3[3];
+  if (a.Ex != nullptr) {
+    const int c = a.cell_of_mol[mol];
+    const void* f3[3] = {a.Ex, a.Ey, a.Ez};
 #pragma unroll
-      for (int k = 0; k < 3; ++k)
-        E3[k] = (a.ex_is_float ? static_cast<double>(static_cast<const float*>(f3[k])[c])
-                               : static_cast<const double*>(f3[k])[c]) * a.inv_eau;
-    } else {
+    for (int k = 0; k < 3; ++k)
+      E3[k] = (a.ex_is_float ? static_cast<double>(static_cast<const float*>(f3[k])[c])
+                             : static_cast<const double*>(f3[k])[c]) * a.inv_eau;
+  } else {
 #pragma unroll
-      for (int k = 0; k < 3; ++k) E3[k] = a.E_mol[3 * mol + k];
-    }
+    for (int k = 0; k < 3; ++k) E3[k] = a.E_mol[3 * mol + k];
   }
   if (a.E_out != nullptr && tid == 0) {
 #pragma unroll
@@ -249,15 +246,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(JmOcc<T, ON
     }
   }
 
-  // readouts: norm, yield, and the dipole vector (in the same rounds of
-  // radial points)
-  double nrm = 0.0, yld = 0.0;
+  // the norm (finiteness check) and the dipole vector, in the same rounds of radial
+  // points
+  double nrm = 0.0;
 #pragma unroll
-  for (int p = 0; p < R1; ++p) {
-    const double n2 = static_cast<double>(norm2(vv[p]));
-    nrm += n2;
-    if (q + R2 * p >= a.kdiss) yld += n2;
-  }
+  for (int p = 0; p < R1; ++p) nrm += static_cast<double>(norm2(vv[p]));
   double dc[3] = {0.0, 0.0, 0.0};
 #pragma unroll
   for (int h = 0; h < SP; ++h) {
@@ -288,39 +281,35 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(JmOcc<T, ON
       dc[2] += m * tz;
     }
   }
-  // workgroup sums of (ab, nrm, yld, dx, dy, dz) in a fixed order
-  double vals[6] = {ab, nrm, yld, dc[0], dc[1], dc[2]};
+  // workgroup sums of (ab, nrm, dx, dy, dz) in a fixed order
+  double vals[5] = {ab, nrm, dc[0], dc[1], dc[2]};
   const int lane = tid & 63, wid = tid >> 6, nw = (nthr + 63) >> 6;
 #pragma unroll
-  for (int k = 0; k < 6; ++k) vals[k] = wave_sum(vals[k]);
+  for (int k = 0; k < 5; ++k) vals[k] = wave_sum(vals[k]);
   __syncthreads();
   if (lane == 0) {
 #pragma unroll
-    for (int k = 0; k < 6; ++k) red[wid * 6 + k] = vals[k];
+    for (int k = 0; k < 5; ++k) red[wid * 5 + k] = vals[k];
   }
   __syncthreads();
   if (tid == 0) {
-    double sm[6];
-    for (int k = 0; k < 6; ++k) {
+    double sm[5];
+    for (int k = 0; k < 5; ++k) {
       double t = 0.0;
-      for (int w = 0; w < nw; ++w) t += red[w * 6 + k];
+      for (int w = 0; w < nw; ++w) t += red[w * 5 + k];
       sm[k] = t;
     }
     const double dr = a.dr;
     const double absorbed = a.absorbed[mol] + sm[0] * dr;
-    if (n_steps > 0) a.absorbed[mol] = absorbed;
+    a.absorbed[mol] = absorbed;
     if (a.want_d && a.d_mol) {
-      for (int k = 0; k < 3; ++k) a.d_mol[3 * mol + k] = 2.0 * dr * sm[3 + k];
+      for (int k = 0; k < 3; ++k) a.d_mol[3 * mol + k] = 2.0 * dr * sm[2 + k];
     }
-    if (a.want_norm && a.norm_mol) a.norm_mol[mol] = sm[1] * dr;
-    if (a.want_yield && a.yield_mol) a.yield_mol[mol] = sm[2] * dr + absorbed;
-    if (!isfinite(sm[1]) || !isfinite(sm[3]) || !isfinite(sm[4]) || !isfinite(sm[5]) || !isfinite(absorbed))
+    if (!isfinite(sm[1]) || !isfinite(sm[2]) || !isfinite(sm[3]) || !isfinite(sm[4]) || !isfinite(absorbed))
       atomicOr(a.status, 1);
   }
-  if (n_steps > 0) {
 #pragma unroll
-    for (int p = 0; p < R1; ++p) psi[loff + R2 * p] = vv[p];
-  }
+  for (int p = 0; p < R1; ++p) psi[loff + R2 * p] = vv[p];
 }
 
 // LDS bytes of one (j, m) workgroup: staged tables, the eight line slots,

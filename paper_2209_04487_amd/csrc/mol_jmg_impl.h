@@ -136,7 +136,8 @@ __device__ __forceinline__ int jmg_row(int line) {
 // -> 3.23 (30,000, n_r = 128, j_max = 5), 2.28 -> 1.92 (10,000, n_r = 512, j_max =
 // 3); three steps at n_r = 256, j_max = 3: 6.08 -> 4.40.  complex128: 2.00 -> 1.47
 // (10,000, n_r = 256, j_max = 3), 1.61 -> 1.04 (j_max = 2), 1.95 -> 1.30 (n_r = 128,
-// j_max = 4), 2.94 -> 2.81 (j_max = 5), 2.88 -> 1.90 (20,000, n_r = 64, j_max = 5).
+// j_max = 4), 2.94 -> 2.81 (j_max = 5), 2.88 -> 1.90 (20,000, n_r = 64, j_max = 5)
+// (with JmgOcc's bound 1.24, 0.98, 1.10, 2.73, 1.78).
 //
 // A task is 16 radial points with the even states of one electronic state and the
 // odd states of the other; its four products are chains of 16x16x4 matrix-core
@@ -327,11 +328,15 @@ template <typename T, int NR, int JM>
 struct JmgOcc {
   static constexpr int wg_waves = (JmgShape<T, NR, JM>::threads + 63) / 64;
   static constexpr int waves =
-      sizeof(T) == 8 ? 1 : (jmg_wide<T, NR, JM>() > 1 ? 4 : ((12 / wg_waves) > (8 / wg_waves) ? 3 : 2));
+      sizeof(T) == 8 ? (NR >= 128 ? 2 : 1) : (jmg_wide<T, NR, JM>() > 1 ? 4 : ((12 / wg_waves) > (8 / wg_waves) ? 3 : 2));
+  // complex128 from n_r = 128 on is told that more than two will not do: aiming at
+  // more, the scheduler issued the phase table's loads one by one (n_r = 128, j_max = 3,
+  // 10,000 molecules: 829 us instead of 530)
+  static constexpr int most = sizeof(T) == 8 && NR >= 128 ? 2 : 8;
 };
 
 template <typename T, int NR, int JM, bool ONE>
-__global__ __launch_bounds__((JmgShape<T, NR, JM>::threads)) __attribute__((amdgpu_waves_per_eu(JmgOcc<T, NR, JM>::waves)))
+__global__ __launch_bounds__((JmgShape<T, NR, JM>::threads)) __attribute__((amdgpu_waves_per_eu(JmgOcc<T, NR, JM>::waves, JmgOcc<T, NR, JM>::most)))
 void mol_jmg_kernel(MolArgs a) {
   typedef JmgShape<T, NR, JM> S;
   constexpr int R1 = S::R1, R2 = S::R2, NB = S::NB, SP = S::SP, PH = R1 / SP, NRH = S::NRH;
@@ -375,21 +380,18 @@ void mol_jmg_kernel(MolArgs a) {
   static_assert(NTAB <= nthr && TB.jx == 0 && TB.q == TB.n_jx && TB.x == TB.n_jx + TB.n_q, "one entry per thread");
   const double tab_e = tg[tid < NTAB ? tid : 0];
 
-  // field at the molecule (each component at its own edge of the cell);
-  // a readout-only launch (no step) reads no field
-  double E3[3] = {0.0, 0.0, 0.0};
-  if (a.n_steps > 0) {
-    if (a.Ex != nullptr) {
-      const int c = a.cell_of_mol[mol];
-      const void* f3[3] = {a.Ex, a.Ey, a.Ez};
+  // field at the molecule (each component at its own edge of the cell)
+  double E3[3];
+  if (a.Ex != nullptr) {
+    const int c = a.cell_of_mol[mol];
+    const void* f3[3] = {a.Ex, a.Ey, a.Ez};
 #pragma unroll
-      for (int k = 0; k < 3; ++k)
-        E3[k] = (a.ex_is_float ? static_cast<double>(static_cast<const float*>(f3[k])[c])
-                               : static_cast<const double*>(f3[k])[c]) * a.inv_eau;
-    } else {
+    for (int k = 0; k < 3; ++k)
+      E3[k] = (a.ex_is_float ? static_cast<double>(static_cast<const float*>(f3[k])[c])
+                             : static_cast<const double*>(f3[k])[c]) * a.inv_eau;
+  } else {
 #pragma unroll
-      for (int k = 0; k < 3; ++k) E3[k] = a.E_mol[3 * mol + k];
-    }
+    for (int k = 0; k < 3; ++k) E3[k] = a.E_mol[3 * mol + k];
   }
   if (a.E_out != nullptr && tid == 0) {
 #pragma unroll
@@ -540,14 +542,11 @@ void mol_jmg_kernel(MolArgs a) {
     }
   }
 
-  // readouts: norm, yield, and the dipole vector (in the same rounds)
-  double nrm = 0.0, yld = 0.0;
+  // the norm (finiteness check) and the dipole vector, in the same rounds of radial
+  // points
+  double nrm = 0.0;
 #pragma unroll
-  for (int p = 0; p < R1; ++p) {
-    const double n2 = static_cast<double>(norm2(vv[p]));
-    nrm += n2;
-    if (q + R2 * p >= a.kdiss) yld += n2;
-  }
+  for (int p = 0; p < R1; ++p) nrm += static_cast<double>(norm2(vv[p]));
   double dc[3] = {0.0, 0.0, 0.0};
   if (a.want_d && a.d_mol) {
     const double* dip = tg + TB.dip;
@@ -579,40 +578,36 @@ void mol_jmg_kernel(MolArgs a) {
       }
     }
   }
-  // workgroup sums of (ab, nrm, yld, dx, dy, dz) in a fixed order
-  double vals[6] = {ab, nrm, yld, dc[0], dc[1], dc[2]};
+  // workgroup sums of (ab, nrm, dx, dy, dz) in a fixed order
+  double vals[5] = {ab, nrm, dc[0], dc[1], dc[2]};
   const int lane = tid & 63, wid = tid >> 6;
   constexpr int nw = (nthr + 63) >> 6;
 #pragma unroll
-  for (int k = 0; k < 6; ++k) vals[k] = wave_sum(vals[k]);
+  for (int k = 0; k < 5; ++k) vals[k] = wave_sum(vals[k]);
   __syncthreads();
   if (lane == 0) {
 #pragma unroll
-    for (int k = 0; k < 6; ++k) red[wid * 6 + k] = vals[k];
+    for (int k = 0; k < 5; ++k) red[wid * 5 + k] = vals[k];
   }
   __syncthreads();
   if (tid == 0) {
-    double sm[6];
-    for (int k = 0; k < 6; ++k) {
+    double sm[5];
+    for (int k = 0; k < 5; ++k) {
       double t = 0.0;
-      for (int w = 0; w < nw; ++w) t += red[w * 6 + k];
+      for (int w = 0; w < nw; ++w) t += red[w * 5 + k];
       sm[k] = t;
     }
     const double dr = a.dr;
     const double absorbed = a.absorbed[mol] + sm[0] * dr;
-    if (n_steps > 0) a.absorbed[mol] = absorbed;
+    a.absorbed[mol] = absorbed;
     if (a.want_d && a.d_mol) {
-      for (int k = 0; k < 3; ++k) a.d_mol[3 * mol + k] = 2.0 * dr * sm[3 + k];
+      for (int k = 0; k < 3; ++k) a.d_mol[3 * mol + k] = 2.0 * dr * sm[2 + k];
     }
-    if (a.want_norm && a.norm_mol) a.norm_mol[mol] = sm[1] * dr;
-    if (a.want_yield && a.yield_mol) a.yield_mol[mol] = sm[2] * dr + absorbed;
-    if (!isfinite(sm[1]) || !isfinite(sm[3]) || !isfinite(sm[4]) || !isfinite(sm[5]) || !isfinite(absorbed))
+    if (!isfinite(sm[1]) || !isfinite(sm[2]) || !isfinite(sm[3]) || !isfinite(sm[4]) || !isfinite(absorbed))
       atomicOr(a.status, 1);
   }
-  if (n_steps > 0) {
 #pragma unroll
-    for (int p = 0; p < R1; ++p) psi[loff + R2 * p] = vv[p];
-  }
+  for (int p = 0; p < R1; ++p) psi[loff + R2 * p] = vv[p];
 }
 
 template <typename T, int NR, int JM, bool ONE>

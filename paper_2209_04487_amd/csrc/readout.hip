@@ -1,5 +1,5 @@
 // Readouts beside the molecular step.
-//  - Dipole, norm and yield of every wavepacket of the m = 0 basis.
+//  - Dipole, norm and yield of every wavepacket (m = 0 and (j, m) bases).
 //  - Excited-state radial moments of every wavepacket (Eq. (8)): per molecule
 //    <chi_e|R|chi_e> = sum_{J,k} r_k |psi_e,J(r_k)|^2 dr and <chi_e|chi_e>,
 //    accumulated in FP64, plus the ensemble sums over molecules and their
@@ -17,6 +17,7 @@
 #include <hip/hip_runtime.h>
 
 #include "mol.h"
+#include "mol_jmg.h"
 #include "readout.h"
 
 namespace msqd {
@@ -104,6 +105,104 @@ __global__ __launch_bounds__(kRdThreads) void mol_readout_kernel(MolArgs a, int 
     if (a.want_yield) a.yield_mol[mol] = yld * a.dr + absorbed;
     const bool check_n = a.want_norm || !a.want_d || a.want_yield;
     if (!isfinite(d) || (check_n && !isfinite(nrm)) || !isfinite(absorbed)) atomicOr(a.status, 1);
+  }
+}
+
+// The same in the (j, m) basis, three dipole components: a lane owns one radial
+// point, holds the states of one j of both electronic states (converted once) and
+// reads those of j + 1.  With the terms Re<g|D_z|e>, P = <g|D_+|e> and P' =
+// <e|D_+|g>, D_+ = D_x + i D_y, d_x and d_y are Re (P + P') / 2 and Im (P + P') / 2.
+// dip: per state <j+1,m|cos|j,m>, <j+1,m+1|sin e^{i ph}|j,m>, <j-1,m+1|sin e^{i ph}|j,m>.
+// When the steps' kernels did this (lines through LDS, one workgroup per molecule)
+// -> here, us: 405 -> 272 (100,000 molecules, n_r = 256, j_max = 1, complex64), 1010 ->
+// 366 (60,000, j_max = 2), 1076 -> 413 (40,000, j_max = 3), 1650 -> 821 (20,000, j_max
+// = 5), 1055 -> 507 (8,000, n_r = 512, j_max = 4); complex128 670 -> 338 (15,000, n_r =
+// 256, j_max = 3), 1196 -> 545 (20,000, n_r = 128, j_max = 5).
+// SPLIT: the four wavefronts of a workgroup share a molecule's radial points, for
+// launches that leave the card idle otherwise.
+template <typename T, int JM, bool SPLIT>
+__global__ __launch_bounds__(kRdThreads) void jm_readout_kernel(MolArgs a, int n_r) {
+  constexpr int NB = (JM + 1) * (JM + 1), NM = 2 * JM + 1;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int mol = SPLIT ? static_cast<int>(blockIdx.x) : static_cast<int>(blockIdx.x) * kRdWaves + wave;
+  if (mol >= a.n_mol) return;
+  const double* mu = reinterpret_cast<const double*>(a.ws + a.lay.mu_d);
+  // j_max = 1 has no tables in the workspace
+  const double one[12] = {0.57735026918962576451, -0.81649658092772603273, 0.0, 0.0, 0.0, 0.81649658092772603273};
+  const double* __restrict__ dip =
+      JM == 1 ? one : reinterpret_cast<const double*>(a.ws + a.lay.total) + jmg_tab(JM).dip;
+  const cx<T>* g = static_cast<const cx<T>*>(a.psi) + static_cast<size_t>(mol) * 2 * NB * n_r;
+  const cx<T>* e = g + static_cast<size_t>(NB) * n_r;
+  double nrm = 0.0, yld = 0.0, dx = 0.0, dy = 0.0, dz = 0.0;
+#pragma unroll 1
+  for (int r = SPLIT ? static_cast<int>(threadIdx.x) : lane; r < n_r; r += SPLIT ? kRdThreads : 64) {
+    double n2 = 0.0, z = 0.0, pr = 0.0, pi = 0.0;
+    cx<double> g0[NM], e0[NM], g1[NM], e1[NM];
+#pragma unroll
+    for (int j = 0; j <= JM; ++j) {
+#pragma unroll
+      for (int i = 0; i < 2 * j + 1; ++i) {
+        const cx<T> u = g[(j * j + i) * n_r + r], w = e[(j * j + i) * n_r + r];
+        n2 += static_cast<double>(norm2(u)) + static_cast<double>(norm2(w));
+        g1[i] = {static_cast<double>(u.x), static_cast<double>(u.y)};
+        e1[i] = {static_cast<double>(w.x), static_cast<double>(w.y)};
+      }
+      // c (conj(p_g) b_e + conj(p_e) b_g)
+      auto link = [&](double c, const cx<double>& pg, const cx<double>& pe, const cx<double>& bg, const cx<double>& be) {
+        pr += c * ((pg.x * be.x + pg.y * be.y) + (pe.x * bg.x + pe.y * bg.y));
+        pi += c * ((pg.x * be.y - pg.y * be.x) + (pe.x * bg.y - pe.y * bg.x));
+      };
+      if (j > 0) {
+        // state (j - 1, m) = [i] with (j, m) = [i + 1] and (j, m + 1) = [i + 2]
+#pragma unroll
+        for (int i = 0; i < 2 * j - 1; ++i) {
+          const double* c = dip + 3 * ((j - 1) * (j - 1) + i);
+          z += c[0] * ((g1[i + 1].x * e0[i].x + g1[i + 1].y * e0[i].y) + (g0[i].x * e1[i + 1].x + g0[i].y * e1[i + 1].y));
+          link(c[1], g1[i + 2], e1[i + 2], g0[i], e0[i]);
+        }
+        // state (j, m) = [i] with (j - 1, m + 1) = [i]
+#pragma unroll
+        for (int i = 0; i < 2 * j - 1; ++i) link(dip[3 * (j * j + i) + 2], g0[i], e0[i], g1[i], e1[i]);
+      }
+#pragma unroll
+      for (int i = 0; i < 2 * j + 1; ++i) {
+        g0[i] = g1[i];
+        e0[i] = e1[i];
+      }
+    }
+    const double m = mu[r];
+    dx += m * (0.5 * pr);
+    dy += m * (0.5 * pi);
+    dz += m * z;
+    nrm += n2;
+    if (r >= a.kdiss) yld += n2;
+  }
+  double sum[5] = {rd_wave_sum(nrm), rd_wave_sum(yld), rd_wave_sum(dx), rd_wave_sum(dy), rd_wave_sum(dz)};
+  if constexpr (SPLIT) {
+    __shared__ double part[kRdWaves][5];
+    if (lane == 0) {
+#pragma unroll
+      for (int k = 0; k < 5; ++k) part[wave][k] = sum[k];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < 5; ++k) sum[k] = (part[0][k] + part[1][k]) + (part[2][k] + part[3][k]);
+  }
+  if (lane == 0 && (!SPLIT || wave == 0)) {
+    const double* d = sum + 2;
+    nrm = sum[0];
+    yld = sum[1];
+    const double absorbed = a.absorbed[mol];
+    bool ok = isfinite(nrm) && isfinite(absorbed);
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      if (!a.want_d) continue;
+      a.d_mol[3 * mol + k] = 2.0 * a.dr * d[k];
+      ok = ok && isfinite(d[k]);
+    }
+    if (a.want_norm) a.norm_mol[mol] = nrm * a.dr;
+    if (a.want_yield) a.yield_mol[mol] = yld * a.dr + absorbed;
+    if (!ok) atomicOr(a.status, 1);
   }
 }
 
@@ -231,6 +330,38 @@ __global__ void spectra_kernel(const double* st, const double* si, const double*
   tra[f] = st[f] / ref;
   tra[n + f] = (ref - si[f]) / ref;
   tra[2 * n + f] = (si[f] - st[f]) / ref;
+}
+
+// Up to kJmSplitMol molecules of 256 radial points or more a workgroup takes one of
+// them instead of four (us, complex64, j_max = 5, n_r = 256, four / one: 10 molecules
+// 28.0 / 19.9, 300 53.8 / 22.7, 1,000 56.3 / 38.7, 2,000 87.8 / 96.0; n_r = 64, 1,000:
+// 21.7 / 33.3).
+constexpr int kJmSplitMol = 1024;
+template <typename T, int JM>
+static int launch_jm_readout_j(const MolArgs& a, int n_r, hipStream_t s) {
+  if (a.n_mol <= kJmSplitMol && n_r >= kRdThreads)
+    hipLaunchKernelGGL((jm_readout_kernel<T, JM, true>), dim3(a.n_mol), dim3(kRdThreads), 0, s, a, n_r);
+  else
+    hipLaunchKernelGGL((jm_readout_kernel<T, JM, false>), dim3((a.n_mol + kRdWaves - 1) / kRdWaves), dim3(kRdThreads), 0, s,
+                       a, n_r);
+  return static_cast<int>(hipGetLastError());
+}
+
+template <typename T>
+static int launch_jm_readout_t(const MolArgs& a, int n_r, hipStream_t s) {
+  switch (a.nj - 1) {
+    case 1: return launch_jm_readout_j<T, 1>(a, n_r, s);
+    case 2: return launch_jm_readout_j<T, 2>(a, n_r, s);
+    case 3: return launch_jm_readout_j<T, 3>(a, n_r, s);
+    case 4: return launch_jm_readout_j<T, 4>(a, n_r, s);
+    case 5: return launch_jm_readout_j<T, 5>(a, n_r, s);
+    default: return static_cast<int>(hipErrorInvalidValue);
+  }
+}
+
+int launch_jm_readout(const MolArgs& a, int n_r, bool f32, hipStream_t s) {
+  if (a.n_mol <= 0) return 0;
+  return f32 ? launch_jm_readout_t<float>(a, n_r, s) : launch_jm_readout_t<double>(a, n_r, s);
 }
 
 int launch_mol_readout(const MolArgs& a, int n_r, bool f32, hipStream_t s) {
