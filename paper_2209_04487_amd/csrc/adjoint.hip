@@ -414,13 +414,15 @@ struct Adj32Shape {
 // chi and lambda) and a half-K tile fit 128 registers, three with the full-K tile,
 // two at 32 points per lane (three spilled 55 to 139 registers at n_r = 512: 703 ->
 // 846 us for 8,000 molecules, J <= 3; 394 -> 435 us at three instead of four for
-// 20,000 at n_r = 128).
+// 20,000 at n_r = 128).  The same number is given as the most there will be, so that
+// the loads are issued together (n_r = 512, 8,000, J <= 3: 707 -> 566 us; n_r = 128,
+// J <= 10, 12,000: 452 -> 426; n_r = 256, J <= 6, 10,000: 517 -> 503).
 template <int NR, bool KH, int W>
 constexpr int adj32_waves() { return FftShape<NR, float, W>::R1 > 16 ? 2 : (KH ? 4 : 3); }
 
 template <int NR, bool NEXT, bool KH, int W>
 __global__ __launch_bounds__(512)
-__attribute__((amdgpu_waves_per_eu(adj32_waves<NR, KH, W>()))) void mol_adj32_kernel(MolAdjArgs a) {
+__attribute__((amdgpu_waves_per_eu(adj32_waves<NR, KH, W>(), adj32_waves<NR, KH, W>()))) void mol_adj32_kernel(MolAdjArgs a) {
   typedef Adj32Shape<NR, W> S;
   typedef typename S::TBL TBL;
   constexpr int R1 = FftShape<NR, float, W>::R1, R2 = FftShape<NR, float, W>::R2;

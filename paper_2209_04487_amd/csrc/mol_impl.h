@@ -848,6 +848,15 @@ __device__ __forceinline__ void absorb_point(cx<T>& v, T m, double& ab) {
 }
 
 // --------------------------------------------------------------- kernel
+// coupling path: BF16 hi/lo split on 16x16x16 (mixed form) or the
+// working precision on 16x16x4 (FP32 and FP64 forms)
+// (kCpExactHalf: the working precision with N_J <= kHalfKMaxNJ, two of the
+// four K instructions; kCpExact3: FP64 with N_J <= 12, whose row order puts the
+// rows from 12 on into the fourth; a launch picks them from N_J, so that a kernel
+// holds one contraction path)
+constexpr int kThreeKMaxNJ = 12;
+enum { kCpExact = 0, kCpBf16x3 = 1, kCpExactHalf = 2, kCpExact3 = 3 };
+
 // Occupancy target (waves per SIMD) of the fused step.  The complex64 forms
 // at n_r = 256 and 512 (three waves per molecule at J_max = 10, n_r = 256)
 // run four molecules per CU within 168 VGPRs, which the LDS copy of a
@@ -859,17 +868,11 @@ __device__ __forceinline__ void absorb_point(cx<T>& v, T m, double& ab) {
 template <typename T, int NR, bool PARTS, int W>
 struct MolOcc {
   static constexpr int waves = sizeof(T) == 8 ? (PARTS && NR < 512 ? 3 : 2) : (NR <= 128 || W > 1 ? 4 : 3);
+  // The mixed form is told that more will not do either: its loads are then issued
+  // further ahead (50,000 molecules, n_r = 256, N_J = 11: 1615 -> 1591 us; n_r = 128,
+  // N_J = 7, 20,000: 261 -> 250).  The others measured the same within 1 to 3%.
+  static constexpr int most(int cp) { return cp == kCpBf16x3 ? waves : 8; }
 };
-
-
-// coupling path: BF16 hi/lo split on 16x16x16 (mixed form) or the
-// working precision on 16x16x4 (FP32 and FP64 forms)
-// (kCpExactHalf: the working precision with N_J <= kHalfKMaxNJ, two of the
-// four K instructions; kCpExact3: FP64 with N_J <= 12, whose row order puts the
-// rows from 12 on into the fourth; a launch picks them from N_J, so that a kernel
-// holds one contraction path)
-constexpr int kThreeKMaxNJ = 12;
-enum { kCpExact = 0, kCpBf16x3 = 1, kCpExactHalf = 2, kCpExact3 = 3 };
 
 // raised wave priority over the contraction rounds (see the step loop)
 template <typename T, int NR, int CP>
@@ -879,7 +882,8 @@ inline constexpr bool kPrioContraction = CP == kCpBf16x3 && NR >= 256;
 // step loop then has no back edge, and the register allocation needs no
 // spills.
 template <typename T, int NR, int CP, bool ONE, bool PARTS, int W>
-__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(MolOcc<T, NR, PARTS, W>::waves)))
+__global__ __launch_bounds__(512)
+__attribute__((amdgpu_waves_per_eu(MolOcc<T, NR, PARTS, W>::waves, MolOcc<T, NR, PARTS, W>::most(CP))))
 void mol_step_kernel(MolArgs a) {
   constexpr int R1 = FftShape<NR, T, W>::R1, R2 = FftShape<NR, T, W>::R2;
   // SP exchange rounds of NRH radial points; round h holds the registers
