@@ -115,12 +115,18 @@ __device__ __forceinline__ void coupling_jm_point(cx<T>* g, cx<T>* e, const cx<T
 // launches (at n_r = 512, whose lines take 128 registers a lane, 1267 -> 941 us per
 // 10,000 molecules), and what it needs in the others, whose step loop would spill
 // there (969 -> 1120 us per 4,000 molecules and three steps at n_r = 512).
+// The complex64 form from n_r = 256 on is given the bound from above too, so that
+// its loads are not spread out to keep registers free (n_r = 256: 351 -> 345 us for
+// 30,000 molecules, 26.3 -> 25.3 for 1,500; at n_r = 128 it measured 7% slower).
 template <typename T, bool ONE, int W>
-struct JmOcc { static constexpr int waves = sizeof(T) == 4 ? (W > 1 ? 4 : 3) : (ONE ? 2 : 1); };
+struct JmOcc {
+  static constexpr int waves = sizeof(T) == 4 ? (W > 1 ? 4 : 3) : (ONE ? 2 : 1);
+  static constexpr int most(int n_r) { return sizeof(T) == 4 && n_r >= 256 ? waves : 8; }
+};
 
 // ONE: the launch advances exactly one step (as in the m = 0 kernel).
 template <typename T, int NR, bool ONE, int W>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(JmOcc<T, ONE, W>::waves))) void mol_jm_kernel(MolArgs a) {
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(JmOcc<T, ONE, W>::waves, JmOcc<T, ONE, W>::most(NR)))) void mol_jm_kernel(MolArgs a) {
   constexpr int R1 = FftShape<NR, T, W>::R1, R2 = FftShape<NR, T, W>::R2;
   constexpr int NB = 4, L = 2 * NB;
   constexpr int SP = fwd_split<NR, T, W>(), PH = R1 / SP, NRH = NR / SP;

@@ -329,10 +329,14 @@ struct JmgOcc {
   static constexpr int wg_waves = (JmgShape<T, NR, JM>::threads + 63) / 64;
   static constexpr int waves =
       sizeof(T) == 8 ? (NR >= 128 ? 2 : 1) : (jmg_wide<T, NR, JM>() > 1 ? 4 : ((12 / wg_waves) > (8 / wg_waves) ? 3 : 2));
-  // complex128 from n_r = 128 on is told that more than two will not do: aiming at
-  // more, the scheduler issued the phase table's loads one by one (n_r = 128, j_max = 3,
-  // 10,000 molecules: 829 us instead of 530)
-  static constexpr int most = sizeof(T) == 8 && NR >= 128 ? 2 : 8;
+  // The bound from above: complex128 from n_r = 128 on and complex64 from n_r = 256 on
+  // are told that more will not do, or the scheduler spreads the phase table's loads
+  // out to keep registers free (complex128, n_r = 128, j_max = 3, 10,000 molecules: 829
+  // -> 530 us; complex64, n_r = 256, j_max = 2, 40,000: 1685 -> 1630, j_max = 5, 30,000:
+  // 5655 -> 5622, n_r = 512, j_max = 3, 10,000: 1872 -> 1813).  On smaller grids
+  // aiming at more is right (complex64, n_r = 128, j_max = 3, 50,000: 1407 / 1618 us;
+  // n_r = 64, j_max = 2, 60,000: 624 / 789).
+  static constexpr int most = sizeof(T) == 8 ? (NR >= 128 ? 2 : 8) : (NR >= 256 ? waves : 8);
 };
 
 template <typename T, int NR, int JM, bool ONE>
