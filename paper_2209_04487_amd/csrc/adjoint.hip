@@ -27,8 +27,9 @@ namespace msqd {
 // Returns this lane's share of dY/dE (zero for the forward).
 // A's rows are LSA elements apart (the LDS line stride, or N_r for chi in
 // device memory), B's LS.  KH: N_J <= kHalfKMaxNJ, two of the four K
-// instructions per product, rows as in the forward step (mf_row).
-template <typename T, int NR, bool ADJ, int LSA, bool KH>
+// instructions per product, rows as in the forward step (mf_row).  LARGE: angles
+// beyond the series may occur.
+template <typename T, int NR, bool ADJ, int LSA, bool KH, bool LARGE>
 __device__ __forceinline__ double coupling_adj_mfma(const cx<T>* A, cx<T>* B, int LS, int nj,
                                                     const T* __restrict__ frag, const T* __restrict__ x,
                                                     const T* __restrict__ mudt, T E) {
@@ -89,7 +90,12 @@ __device__ __forceinline__ double coupling_adj_mfma(const cx<T>* A, cx<T>* B, in
     if constexpr (ADJ) MfmaK4<T>::settle(Lgr, Lgi, Ler, Lei);
     const T md = mudt[r] * E;
     T sn[4], vs[4];
-    sin_vers_tile<NR>(md, xk, sn, vs);
+    if constexpr (LARGE) {
+      sin_vers_tile<NR>(md, xk, sn, vs);
+    } else {
+#pragma unroll
+      for (int i = 0; i < NK; ++i) sin_vers_series(md * xk[i], &sn[i], &vs[i]);
+    }
     double gl = 0.0;
     acc_t Ogr = z, Ogi = z, Oer = z, Oei = z;   // the operand of the T^T product
 #pragma unroll
@@ -174,6 +180,12 @@ __global__ __launch_bounds__(512) void mol_adj_kernel(MolAdjArgs a) {
   const double* cj = reinterpret_cast<const double*>(ws + a.lay.cj_d);
 
   const T E = static_cast<T>(a.E_mol[mol]);
+  // Whether some angle may lie beyond the series: at n_r = 512, whose lines take 128
+  // registers, decided per molecule as in the forward step, so that the library calls
+  // stay out of the common path (4,000 molecules, J <= 3: 1408 -> 1062 us); below it
+  // the split measured the same within 2% and there is one path.
+  const bool large =
+      NR < 512 || !(fabs(E) * *reinterpret_cast<const double*>(ws + a.lay.status + 8) < kSinVersSeries64);
   const size_t base = static_cast<size_t>(mol) * L * NR;
   const cx<T>* psi = reinterpret_cast<const cx<T>*>(a.psi_n) + base;
   cx<T>* lpsi = reinterpret_cast<cx<T>*>(a.lpsi) + base;
@@ -211,7 +223,10 @@ __global__ __launch_bounds__(512) void mol_adj_kernel(MolAdjArgs a) {
     __syncthreads();
   } else {
     __syncthreads();
-    coupling_adj_mfma<T, NR, false, LS, KH>(A, B, LS, nj, frag, xk, mudt, E);
+    if (__builtin_expect(large, 0))
+      coupling_adj_mfma<T, NR, false, LS, KH, true>(A, B, LS, nj, frag, xk, mudt, E);
+    else
+      coupling_adj_mfma<T, NR, false, LS, KH, false>(A, B, LS, nj, frag, xk, mudt, E);
     __syncthreads();
     if (active) {
 #pragma unroll
@@ -262,9 +277,11 @@ __global__ __launch_bounds__(512) void mol_adj_kernel(MolAdjArgs a) {
   __syncthreads();
   double grad;
   if constexpr (NEXT)
-    grad = coupling_adj_mfma<T, NR, true, NR, KH>(chi_g, B, LS, nj, frag, xk, mudt, E);
+    grad = __builtin_expect(large, 0) ? coupling_adj_mfma<T, NR, true, NR, KH, true>(chi_g, B, LS, nj, frag, xk, mudt, E)
+                                      : coupling_adj_mfma<T, NR, true, NR, KH, false>(chi_g, B, LS, nj, frag, xk, mudt, E);
   else
-    grad = coupling_adj_mfma<T, NR, true, LS, KH>(A, B, LS, nj, frag, xk, mudt, E);
+    grad = __builtin_expect(large, 0) ? coupling_adj_mfma<T, NR, true, LS, KH, true>(A, B, LS, nj, frag, xk, mudt, E)
+                                      : coupling_adj_mfma<T, NR, true, LS, KH, false>(A, B, LS, nj, frag, xk, mudt, E);
   __syncthreads();
   if (active) {
 #pragma unroll
