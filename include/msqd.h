@@ -334,7 +334,7 @@ typedef struct {
   double* P_c;               /* [n_occ] cell polarisation (C/m^2)          */
   double* J_mol;             /* [n_occ] last polarisation current (A/m^2)  */
   const int32_t* cell_of_mol;  /* [n_mol] flat E_x index                   */
-  const int32_t* occ_cell;     /* [n_occ]                                  */
+  const int32_t* occ_cell;     /* [n_occ], each cell once, in any order    */
   const int32_t* occ_ptr;      /* [n_occ+1]                                */
   const int32_t* mol_perm;     /* [n_mol]                                  */
   fdtd_fields f;

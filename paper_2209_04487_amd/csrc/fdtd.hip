@@ -263,17 +263,13 @@ __global__ __launch_bounds__(256) void deposit_kernel(DepArgs a) {
   if (c < a.n_occ) deposit_cell<T>(a, c);
 }
 
-// whether a cell is occupied (occ is increasing)
+// whether a cell is occupied.  The list may be in any order, so it is read from
+// end to end: only for marked planes, where the run is lost anyway.
 __device__ __forceinline__ bool occupied(const int* occ, int n_occ, long cell) {
-  int lo = 0, hi = n_occ;
-  while (lo < hi) {
-    const int mid = lo + (hi - lo) / 2;
-    if (occ[mid] < cell)
-      lo = mid + 1;
-    else
-      hi = mid;
-  }
-  return lo < n_occ && occ[lo] == cell;
+  bool hit = false;
+#pragma unroll 8
+  for (int c = 0; c < n_occ; ++c) hit |= occ[c] == cell;
+  return hit;
 }
 
 // Drude current (centred form of Eq. (2)) and
