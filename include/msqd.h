@@ -367,7 +367,8 @@ typedef struct {
                                 alone carry the state (checkpoints need not
                                 hold it).  An occupied cell outside the held
                                 planes sets its E components to NaN (the library
-                                marks such planes in fd_ws). */
+                                marks such planes in fd_ws until its next
+                                fdtd_init; runs may share fd_ws). */
 } cpl_state;
 
 /* n_steps coupled steps from step n0 (section on molecular mapping, with

@@ -975,14 +975,6 @@ int map_planes(int32_t n_occ, const int32_t* occ_cell, int32_t nx, int32_t ny, i
   return MSQD_OK;
 }
 
-// a number for each deposit that marks planes (DepArgs::outside), so that marks
-// left by another step are never taken for this one's
-static uint32_t next_tag() {
-  static std::atomic<uint32_t> last{0};
-  const uint32_t t = last.fetch_add(1, std::memory_order_relaxed) + 1;
-  return t ? t : last.fetch_add(1, std::memory_order_relaxed) + 1;   // zero is the empty mark
-}
-
 int coupled_step(const cpl_desc* d, const cpl_state* st, const double* src_values, int64_t n0,
                  int32_t n_steps, void* stream) {
   if (!d || !st) return fail(MSQD_EINVAL, "NULL descriptor or state");
@@ -1102,11 +1094,9 @@ int coupled_step(const cpl_desc* d, const cpl_state* st, const double* src_value
     if (dep_now) {
       da.update = 1;
       da.outside = reinterpret_cast<uint32_t*>(static_cast<char*>(const_cast<void*>(st->fd_ws)) + fa.lay.outside);
-      da.tag = next_tag();
       e = launch_yee_h_deposit(fa, da, f32, s);
       if (e) return check_hip(static_cast<hipError_t>(e), "H update and deposit launch");
       fa.outside = da.outside;
-      fa.tag = da.tag;
       fa.n_occ = da.n_occ;
       fa.occ_cell = da.occ_cell;
     }

@@ -32,11 +32,10 @@ struct FdArgs {
   // into the ring slot stage[i] ([4][ny][nx])
   int stage_k[2];
   double* stage[2];
-  // planes that the deposit beside this step's H update marked with `tag`
-  // (DepArgs::outside), or nullptr; their occupied cells, of which held_nc
-  // components turn to NaN
+  // marks of the planes in which a deposit beside an H update met occupied cells
+  // outside the held planes (DepArgs::outside), or nullptr; the occupied cells,
+  // of which held_nc components turn to NaN there
   const uint32_t* outside;
-  uint32_t tag;
   int n_occ;
   const int* occ_cell;
 };
@@ -97,9 +96,10 @@ struct DepArgs {
   long plane;                          // nx ny
   // a cell outside the held planes: nullptr: its E components are set to NaN
   // here; else (beside the H update, which reads E) its plane's entry is set to
-  // `tag`, and the E update sets them
+  // one, and the E update sets them.  Marks are only ever set, so that runs which
+  // share a field workspace cannot take each other's away; a mark of another run
+  // or step only has the E update look its own cells up.
   uint32_t* outside;
-  uint32_t tag;
 };
 int launch_deposit(const DepArgs& a, bool f32, hipStream_t s);
 

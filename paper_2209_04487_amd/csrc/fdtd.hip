@@ -156,7 +156,7 @@ __device__ __forceinline__ void deposit_cell(const DepArgs& a, int c) {
         static_cast<T*>(a.held)[(static_cast<long>(k) * a.held_nk + kc - a.held_k0) * a.plane +
                                 (cell - kc * a.plane)] = h;
       else if (a.outside)
-        a.outside[kc] = a.tag;
+        a.outside[kc] = 1u;
       else
         E[cell] = __builtin_nan("");
     } else {
@@ -307,7 +307,7 @@ __global__ __launch_bounds__(256) void yee_e_kernel(FdArgs a) {
   // uniform over the workgroup)
   const bool in_held = k >= a.held_k0 && k < a.held_k0 + a.held_nk;
   // occupied cells outside the held planes turn to NaN (marked planes only)
-  const bool poison = !in_held && a.outside != nullptr && a.outside[k] == a.tag &&
+  const bool poison = !in_held && a.outside != nullptr && a.outside[k] != 0u &&
                       occupied(a.occ_cell, a.n_occ, base + p);
   const long hn = static_cast<long>(a.held_nk) * sz;
 #pragma unroll

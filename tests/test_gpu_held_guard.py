@@ -49,3 +49,39 @@ def test_guard_does_not_depend_on_the_cells_order(prec, basis, order, k0, nk):
             want[outside] = True
         assert np.array_equal(np.isnan(e), want), nm
         assert np.isfinite(e[~want]).all()
+
+
+def test_guard_of_runs_that_share_a_field_workspace():
+    """Runs on streams of their own with one field workspace: two whose cells lie outside
+    their held planes are marked at their update, and one with the right planes keeps the
+    bits it has with a workspace of its own, also after the others marked its planes."""
+    from paper_2209_04487_amd import msqd
+    cfg = get_config("cfg0")
+    banner("held guard with a shared field workspace")
+    src = source_values(cfg, 0, 12)
+    runs = [msqd.Coupled(cfg, prec="fp64") for _ in range(4)]
+    alone, good, bad = runs[0], runs[1], runs[2:]
+    for r in runs[1:]:
+        r.state.fd_ws = good.state.fd_ws
+    for r in bad:
+        r.desc.held_k0, r.desc.held_nk = cfg.nz - 1, 1
+    torch.cuda.synchronize()
+    streams = [torch.cuda.Stream() for _ in runs]
+    for r, st in zip(runs, streams):
+        with torch.cuda.stream(st):
+            r.step(src[:1])
+    torch.cuda.synchronize()
+    for r in bad:
+        ex = r.fields.Ex.cpu().numpy().reshape(-1)
+        want = np.zeros(ex.shape, bool)
+        want[r.occ_cell.cpu().numpy()] = True
+        assert np.array_equal(np.isnan(ex), want)
+    for r, st in zip(runs, streams):
+        with torch.cuda.stream(st):
+            r.step(src[1:])
+    torch.cuda.synchronize()
+    assert float(alone.J_mol.abs().max()) > 0
+    for k in alone._STATE:
+        assert torch.equal(alone.fields.t[k], good.fields.t[k]), k
+    for a, b in ((alone.mol.psi, good.mol.psi), (alone.P_c, good.P_c), (alone.J_mol, good.J_mol)):
+        assert torch.equal(a, b)
