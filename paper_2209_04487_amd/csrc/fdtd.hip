@@ -386,12 +386,16 @@ int launch_yee_h(const FdArgs& a, bool f32, hipStream_t s) {
   return static_cast<int>(hipGetLastError());
 }
 
-// rows of the H update's grid that n extra threads take, or 0 where the grid has
-// no room for them (65,535 rows)
-static int extra_rows(const dim3& g, int n) {
-  const long per = 256L * g.x, rows = (n + per - 1) / per;
-  return rows + g.y <= 65535 ? static_cast<int>(rows) : 0;
+// rows of the H update's grid (gx runs, gy planes) that n extra threads take, or 0
+// where the grid has no room for them (65,535 rows) or the last rows' indices
+// would pass the 32 bits of extra_index
+static constexpr int extra_rows(unsigned gx, unsigned gy, int n) {
+  const long per = 256L * gx, rows = (n + per - 1) / per;
+  return rows + gy <= 65535 && rows * per <= 0x7fffffffL ? static_cast<int>(rows) : 0;
 }
+static_assert(extra_rows(144, 120, 691200) == 19 && extra_rows(1, 24, 64) == 1, "whole rows");
+static_assert(extra_rows(1, 28, 256 * 65508) == 0, "no room beside the planes");
+static_assert(extra_rows(144, 120, 0x7fffffff - 256) == 0 && extra_rows(1024, 120, 0x7fffffff) == 0, "32-bit index");
 
 int launch_deposit(const DepArgs& a, bool f32, hipStream_t s) {
   if (a.n_occ <= 0) return 0;
@@ -405,7 +409,7 @@ int launch_deposit(const DepArgs& a, bool f32, hipStream_t s) {
 
 int launch_yee_h_deposit(const FdArgs& a, const DepArgs& dep, bool f32, hipStream_t s) {
   dim3 g = yee_grid(a);
-  const int rows = dep.n_occ > 0 ? extra_rows(g, dep.n_occ) : 0;
+  const int rows = dep.n_occ > 0 ? extra_rows(g.x, g.y, dep.n_occ) : 0;
   if (rows == 0) {
     const int e = launch_deposit(dep, f32, s);
     return e ? e : launch_yee_h(a, f32, s);
@@ -420,7 +424,7 @@ int launch_yee_h_deposit(const FdArgs& a, const DepArgs& dep, bool f32, hipStrea
 
 int launch_yee_h_bloch(const FdArgs& a, const BlochArgs& bl, bool f32, hipStream_t s) {
   dim3 g = yee_grid(a);
-  const int rows = bl.n > 0 ? extra_rows(g, bl.n) : 0;
+  const int rows = bl.n > 0 ? extra_rows(g.x, g.y, bl.n) : 0;
   if (rows == 0) {
     const int e = launch_bloch(bl, f32, s);
     return e ? e : launch_yee_h(a, f32, s);
