@@ -235,6 +235,7 @@ static int check_fields(const fdtd_desc* d, const fdtd_fields* f) {
 
 static FdArgs make_fd_args(const fdtd_desc* d, const fdtd_fields* f, const void* ws) {
   FdArgs a{};
+  a.runs = yee_runs(d->nx, d->ny);
   a.nx = d->nx;
   a.ny = d->ny;
   a.nz = d->nz;

@@ -15,6 +15,8 @@ struct FdLayout {
 FdLayout fd_layout(const fdtd_desc* d);
 
 struct FdArgs {
+  unsigned runs;   // workgroups per plane of the updates (yee_runs)
+  int extras;      // E update: whether outside or stage_k is set (launch_yee_e)
   int nx, ny, nz, npml, metal_id, src_k;
   double inv_dx, cH;                   // 1/dx, dt/mu0
   double ce[4];                        // dt/(eps0 eps_r[m])
@@ -42,6 +44,7 @@ struct FdArgs {
 
 struct DepArgs;
 struct BlochArgs;
+unsigned yee_runs(int nx, int ny);
 int launch_yee_h(const FdArgs& a, bool f32, hipStream_t s);
 int launch_yee_e(const FdArgs& a, bool f32, hipStream_t s);
 // the H update together with a part of the step that is independent of it: the

@@ -49,19 +49,31 @@ __device__ __forceinline__ const T* prof(const FdArgs& a, size_t off_d, size_t o
 // eighth of every plane's runs (a strip of y rows, the same in all planes, the
 // number of runs padded to a multiple of eight): all XCDs still sweep the
 // planes together, and the neighbours of a strip hit the XCD's own L2.  The E
-// update takes the planes in descending order, so that it begins with
-// the planes that the H update before it finished with, and the next H update
-// with the E update's last ones.  H + E pair, before -> strips -> both:
-// 60.6 -> 54.7 -> 50.3 us at 192x192x120 FP32 (6.6 TB/s of the two kernels'
-// 75 B per cell), 114 -> 100 -> 98.5 us in FP64, 145 -> 140 -> 136 us at
-// 256x256x160, 36.9 -> 28.9 -> 25.4 us at 150x131x97.  At 96x96x80 (36 runs)
-// and 37x41x33 (6 runs) the launches bound the pair and nothing moved; below
-// kStripRuns an eighth is less than two runs and the rows in dispatch order
-// stay as they were.
+// update then takes the planes in descending order, so that it begins with the
+// planes that the H update before it finished with, and the next H update with
+// the E update's last ones.  H + E pair in us, dispatch order / strips / strips
+// and E descending:
+//   FP32 64x64x80 (16 runs) 7.59 / 7.45 / 7.53, 64x64x160 10.9 / 10.7 / 10.7,
+//   61x83x97 (20) 14.0 / 11.0 / 10.9, 80x80x80 (25) 12.7 / 11.1 / 11.1,
+//   96x96x80 (36) 13.8 / 12.4 / 12.5, 128x96x80 (48) 14.4 / 13.9 / 14.1,
+//   150x131x97 (77) 36.4 / 28.1 / 24.9, 192x192x120 (144) 60.4 / 53.4 / 50.2,
+//   256x256x160 (256) 143.9 / 133.4 / 129.9, 512x512x40 (1024) 161 / 149 / 146;
+//   FP64 64x64x80 11.0 / 10.9 / 10.9, 64x68x120 (17) 16.4 / - / 18.4, 96x96x80
+//   25.0 / 21.6 / 20.7, 192x192x120 112.6 / 98.3 / 96.2, 256x256x160 297 / 286 / 268.
+// What they lose is the padding's idle workgroups: the worst of 17 to 33 runs are 17
+// and 33 in FP64 (above; 16.7 -> 16.9 at 37x224x60), against up to 30% gained at 31.
+// At 16 runs they gain 2% in FP64 and the sides are within 2% in FP32; below, an
+// eighth is less than two runs.  In dispatch order E ascends: descending measured
+// 8.7 -> 9.8 us at 60x60x60 (15 runs, FP32), 12.2 -> 13.6 in FP64.
 //
 // Addresses are a uniform base per plane plus a 32-bit offset in the plane, so
-// that a load takes one offset register.
+// that a load takes one offset register.  A workgroup's size and the runs of a
+// plane come as a constant and an argument: read from blockDim and gridDim they
+// put a dependent vector load ahead of each workgroup's others (pair at 192x192x120
+// 51.9 -> 50.1 us, 256x256x160 141 -> 133, 96x96x80 13.3 -> 12.7, FP64 22.3 -> 20.7).
+constexpr int kRunCells = 256;   // threads of a workgroup
 constexpr unsigned kStripRuns = 16;
+__device__ __forceinline__ bool strips(const FdArgs& a) { return a.runs >= kStripRuns; }
 struct CellIdx {
   unsigned p;   // index in the plane
   int i, j, k;
@@ -69,8 +81,8 @@ struct CellIdx {
 __device__ __forceinline__ bool cell_of_thread(const FdArgs& a, int k, CellIdx& c) {
   const int plane = a.nx * a.ny;
   int run = static_cast<int>(blockIdx.x);
-  if (gridDim.x >= kStripRuns) run = (run & 7) * static_cast<int>(gridDim.x >> 3) + (run >> 3);
-  const int p = run * static_cast<int>(blockDim.x) + static_cast<int>(threadIdx.x);
+  if (strips(a)) run = (run & 7) * static_cast<int>(a.runs >> 3) + (run >> 3);
+  const int p = run * kRunCells + static_cast<int>(threadIdx.x);
   if (p >= plane) return false;
   c.k = k;
   c.j = p / a.nx;
@@ -224,7 +236,7 @@ __device__ __forceinline__ void yee_h_block(const FdArgs& a, int plane_k) {
 }
 
 template <typename T>
-__global__ __launch_bounds__(256) void yee_h_kernel(FdArgs a) {
+__global__ __launch_bounds__(kRunCells) void yee_h_kernel(FdArgs a) {
   yee_h_block<T>(a, static_cast<int>(blockIdx.y));
 }
 
@@ -235,22 +247,22 @@ __global__ __launch_bounds__(256) void yee_h_kernel(FdArgs a) {
 //    molecular step (3 launches per coupled step instead of 4; the deposit alone
 //    took 4 us at 64 molecules and 7 us at 100,000, most of it latency);
 //  - the step of the two-level emitters, one emitter per thread (10 us at 691,200).
-__device__ __forceinline__ int extra_index() {
-  return static_cast<int>((blockIdx.y * gridDim.x + blockIdx.x) * blockDim.x + threadIdx.x);
+__device__ __forceinline__ int extra_index(const FdArgs& a) {
+  return static_cast<int>((blockIdx.y * a.runs + blockIdx.x) * kRunCells + threadIdx.x);
 }
 template <typename T>
-__global__ __launch_bounds__(256) void yee_h_deposit_kernel(FdArgs a, DepArgs dep, int rows) {
+__global__ __launch_bounds__(kRunCells) void yee_h_deposit_kernel(FdArgs a, DepArgs dep, int rows) {
   if (static_cast<int>(blockIdx.y) < rows) {
-    const int c = extra_index();
+    const int c = extra_index(a);
     if (c < dep.n_occ) deposit_cell<T>(dep, c);
     return;
   }
   yee_h_block<T>(a, static_cast<int>(blockIdx.y) - rows);
 }
 template <typename T>
-__global__ __launch_bounds__(256) void yee_h_bloch_kernel(FdArgs a, BlochArgs bl, int rows) {
+__global__ __launch_bounds__(kRunCells) void yee_h_bloch_kernel(FdArgs a, BlochArgs bl, int rows) {
   if (static_cast<int>(blockIdx.y) < rows) {
-    const int i = extra_index();
+    const int i = extra_index(a);
     if (i < bl.n) bloch_emitter<T>(bl, i);
     return;
   }
@@ -277,9 +289,9 @@ __device__ __forceinline__ bool occupied(const int* occ, int n_occ, long cell) {
 // E_x, E_y at k = 0 stay zero (the grid ends on tangential E = 0).
 // Loads first, as in the H update.
 template <typename T>
-__global__ __launch_bounds__(256) void yee_e_kernel(FdArgs a) {
+__global__ __launch_bounds__(kRunCells) void yee_e_kernel(FdArgs a) {
   CellIdx cl;
-  if (!cell_of_thread(a, a.nz - 1 - static_cast<int>(blockIdx.y), cl)) return;
+  if (!cell_of_thread(a, strips(a) ? a.nz - 1 - static_cast<int>(blockIdx.y) : static_cast<int>(blockIdx.y), cl)) return;
   const int nx = a.nx, ny = a.ny, nz = a.nz;
   const int k = cl.k;
   const unsigned p = cl.p;
@@ -306,9 +318,6 @@ __global__ __launch_bounds__(256) void yee_e_kernel(FdArgs a) {
   // the held molecular current, on the planes that hold occupied cells (k is
   // uniform over the workgroup)
   const bool in_held = k >= a.held_k0 && k < a.held_k0 + a.held_nk;
-  // occupied cells outside the held planes turn to NaN (marked planes only)
-  const bool poison = !in_held && a.outside != nullptr && a.outside[k] != 0u &&
-                      occupied(a.occ_cell, a.n_occ, base + p);
   const long hn = static_cast<long>(a.held_nk) * sz;
 #pragma unroll
   for (int c = 0; c < 3; ++c)
@@ -354,9 +363,18 @@ __global__ __launch_bounds__(256) void yee_e_kernel(FdArgs a) {
     if (c < 2 && k == 0) e1 = T(0);
     // the molecular current after the update, as the separate pass applies it
     if (in_held && c < a.held_nc) e1 = MolTerm<T>::apply(e1, ce, hv[c]);
-    if (poison && c < a.held_nc) e1 = __builtin_nan("");
     E[c][p] = e1;
     e0[c] = e1;
+  }
+  // what only some steps ask for, behind a test of its own: the tests below in the
+  // common path cost 0.1 to 0.3 us per launch, each a read of the argument block
+  if (!a.extras) return;
+  // occupied cells outside the held planes turn to NaN (marked planes only)
+  if (!in_held && a.outside != nullptr && a.outside[k] != 0u && occupied(a.occ_cell, a.n_occ, base + p)) {
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+      if (c < a.held_nc) E[c][p] = e0[c] = __builtin_nan("");
+    }
   }
   // the monitor's sample of this step, staged from the registers (as mon_values)
 #pragma unroll
@@ -371,18 +389,18 @@ __global__ __launch_bounds__(256) void yee_e_kernel(FdArgs a) {
   }
 }
 
-static dim3 yee_grid(const FdArgs& a) {
-  const long plane = static_cast<long>(a.nx) * a.ny;
-  unsigned runs = static_cast<unsigned>((plane + 255) / 256);
-  if (runs >= kStripRuns) runs = (runs + 7) / 8 * 8;
-  return dim3(runs, static_cast<unsigned>(a.nz));
+static dim3 yee_grid(const FdArgs& a) { return dim3(a.runs, static_cast<unsigned>(a.nz)); }
+
+unsigned yee_runs(int nx, int ny) {
+  const unsigned runs = static_cast<unsigned>((static_cast<long>(nx) * ny + kRunCells - 1) / kRunCells);
+  return runs >= kStripRuns ? (runs + 7) / 8 * 8 : runs;
 }
 
 int launch_yee_h(const FdArgs& a, bool f32, hipStream_t s) {
   if (f32)
-    hipLaunchKernelGGL(yee_h_kernel<float>, yee_grid(a), dim3(256), 0, s, a);
+    hipLaunchKernelGGL(yee_h_kernel<float>, yee_grid(a), dim3(kRunCells), 0, s, a);
   else
-    hipLaunchKernelGGL(yee_h_kernel<double>, yee_grid(a), dim3(256), 0, s, a);
+    hipLaunchKernelGGL(yee_h_kernel<double>, yee_grid(a), dim3(kRunCells), 0, s, a);
   return static_cast<int>(hipGetLastError());
 }
 
@@ -390,7 +408,7 @@ int launch_yee_h(const FdArgs& a, bool f32, hipStream_t s) {
 // where the grid has no room for them (65,535 rows) or the last rows' indices
 // would pass the 32 bits of extra_index
 static constexpr int extra_rows(unsigned gx, unsigned gy, int n) {
-  const long per = 256L * gx, rows = (n + per - 1) / per;
+  const long per = static_cast<long>(kRunCells) * gx, rows = (n + per - 1) / per;
   return rows + gy <= 65535 && rows * per <= 0x7fffffffL ? static_cast<int>(rows) : 0;
 }
 static_assert(extra_rows(144, 120, 691200) == 19 && extra_rows(1, 24, 64) == 1, "whole rows");
@@ -416,9 +434,9 @@ int launch_yee_h_deposit(const FdArgs& a, const DepArgs& dep, bool f32, hipStrea
   }
   g.y += rows;
   if (f32)
-    hipLaunchKernelGGL(yee_h_deposit_kernel<float>, g, dim3(256), 0, s, a, dep, rows);
+    hipLaunchKernelGGL(yee_h_deposit_kernel<float>, g, dim3(kRunCells), 0, s, a, dep, rows);
   else
-    hipLaunchKernelGGL(yee_h_deposit_kernel<double>, g, dim3(256), 0, s, a, dep, rows);
+    hipLaunchKernelGGL(yee_h_deposit_kernel<double>, g, dim3(kRunCells), 0, s, a, dep, rows);
   return static_cast<int>(hipGetLastError());
 }
 
@@ -431,17 +449,19 @@ int launch_yee_h_bloch(const FdArgs& a, const BlochArgs& bl, bool f32, hipStream
   }
   g.y += rows;
   if (f32)
-    hipLaunchKernelGGL(yee_h_bloch_kernel<float>, g, dim3(256), 0, s, a, bl, rows);
+    hipLaunchKernelGGL(yee_h_bloch_kernel<float>, g, dim3(kRunCells), 0, s, a, bl, rows);
   else
-    hipLaunchKernelGGL(yee_h_bloch_kernel<double>, g, dim3(256), 0, s, a, bl, rows);
+    hipLaunchKernelGGL(yee_h_bloch_kernel<double>, g, dim3(kRunCells), 0, s, a, bl, rows);
   return static_cast<int>(hipGetLastError());
 }
 
-int launch_yee_e(const FdArgs& a, bool f32, hipStream_t s) {
+int launch_yee_e(const FdArgs& args, bool f32, hipStream_t s) {
+  FdArgs a = args;
+  a.extras = a.outside != nullptr || a.stage_k[0] >= 0 || a.stage_k[1] >= 0;
   if (f32)
-    hipLaunchKernelGGL(yee_e_kernel<float>, yee_grid(a), dim3(256), 0, s, a);
+    hipLaunchKernelGGL(yee_e_kernel<float>, yee_grid(a), dim3(kRunCells), 0, s, a);
   else
-    hipLaunchKernelGGL(yee_e_kernel<double>, yee_grid(a), dim3(256), 0, s, a);
+    hipLaunchKernelGGL(yee_e_kernel<double>, yee_grid(a), dim3(kRunCells), 0, s, a);
   return static_cast<int>(hipGetLastError());
 }
 
