@@ -115,13 +115,20 @@ __device__ __forceinline__ void coupling_jm_point(cx<T>* g, cx<T>* e, const cx<T
 // launches (at n_r = 512, whose lines take 128 registers a lane, 1267 -> 941 us per
 // 10,000 molecules), and what it needs in the others, whose step loop would spill
 // there (969 -> 1120 us per 4,000 molecules and three steps at n_r = 512).
-// The complex64 form from n_r = 256 on is given the bound from above too, so that
-// its loads are not spread out to keep registers free (n_r = 256: 351 -> 345 us for
-// 30,000 molecules, 26.3 -> 25.3 for 1,500; at n_r = 128 it measured 7% slower).
+// A bound from above keeps the scheduler from spreading the loads out to save
+// registers for more waves than help: the complex64 form from n_r = 256 on is given
+// its own number (n_r = 256: 351 -> 345 us for 30,000 molecules, 26.3 -> 25.3 for
+// 1,500; at n_r = 128 it measured 7% slower), the complex128 form three at n_r = 64
+// (two steps, 1 molecule 11.5 -> 9.1 us, 20,000 139 -> 125; with two 96 instead of 81
+// us for 20,000 and one step) and two at n_r = 128 and 256 (one step, 3,000 at n_r =
+// 128 36.8 -> 34.7 us, 1,536 at n_r = 256 41.5 -> 39.7, 20,000 within 1.5%).
 template <typename T, bool ONE, int W>
 struct JmOcc {
   static constexpr int waves = sizeof(T) == 4 ? (W > 1 ? 4 : 3) : (ONE ? 2 : 1);
-  static constexpr int most(int n_r) { return sizeof(T) == 4 && n_r >= 256 ? waves : 8; }
+  static constexpr int most(int n_r) {
+    if (sizeof(T) == 4) return n_r >= 256 ? waves : 8;
+    return n_r == 64 ? 3 : (n_r == 512 ? 8 : 2);
+  }
 };
 
 // ONE: the launch advances exactly one step (as in the m = 0 kernel).
