@@ -1154,12 +1154,19 @@ int launch_mol_t1(const MolArgs& a, hipStream_t s) {
 //  n_r = 256, N_J <= 8, single steps: up to four wavefronts per workgroup, three
 //    workgroups instead of two per CU (N_J = 6, 20,000 molecules: 835 / 714).  Its
 //    multi-step loop spills (817 / 893), and from five wavefronts on a CU takes one
-//    workgroup either way (N_J = 11: 1709 / 2153);
-//  n_r = 64, N_J > 8 (30,000 molecules: 665 / 531; N_J = 6: 294 / 303).
+//    workgroup either way (N_J = 11: 1709 / 2153).  Up to 1,024 molecules it loses 1 to
+//    6% (N_J = 4, 512: 27.3 / 28.4, 1,024: 31.8 / 33.6; N_J = 8, 64: 16.9 / 17.5; from
+//    1,536 on it gains 3 to 20%); the line is not drawn there, so that an FP64 molecule's
+//    bits do not depend on the batch;
+//  n_r = 64, 9 <= N_J <= 12 (N_J = 9, 1 molecule: 10.5 / 10.5, 1,024: 27.6 / 20.7, 30,000:
+//    715 / 498, two steps 1160 / 785; N_J = 6, 30,000: 294 / 303).  With the fourth K
+//    instruction its step loop loses (N_J = 13, two steps, 1 molecule: 14.3 / 18.6, 10,000:
+//    359 / 415) and single steps gain for large batches only (1: 9.2 / 10.6, 2,048: 49.4 /
+//    49.5, 30,000: 690 / 627).
 // At n_r = 128 the one-round exchange fits as many (N_J = 7: 614 / 653).
 template <int NR, int CP, bool ONE>
 constexpr bool mol_parts() {
-  return NR == 512 || (NR == 256 && CP == kCpExactHalf && ONE) || (NR == 64 && CP != kCpExactHalf);
+  return NR == 512 || (NR == 256 && CP == kCpExactHalf && ONE) || (NR == 64 && CP == kCpExact3);
 }
 
 // Where wide lines (complex64, n_r = 256: 16 values on 16 lanes, one exchange round,
