@@ -323,13 +323,13 @@ __global__ __launch_bounds__(512) void mol_adj_kernel(MolAdjArgs a) {
 // A: chi; B: the adjoint at the coupling's output, on return at its input (the
 // recompute: C(E) chi).  Rows as in the forward step; rows J >= nj read row
 // nj - 1, whose column of T is zero.
-template <int NR, bool ADJ, bool KH, int W>
+template <int NR, bool ADJ, bool KH, int W, int SP>
 __device__ __forceinline__ double coupling_adj_pairs(const cx<float>* A, cx<float>* B, int nj, int r0,
                                                      const float* __restrict__ frag, const float* __restrict__ x,
                                                      const float* __restrict__ mudt, float E) {
   typedef MfmaK4<float> MK;
   typedef MK::acc acc_t;
-  constexpr int NK = KH ? 2 : 4, NRH = NR / fwd_split<NR, float, W>();
+  constexpr int NK = KH ? 2 : 4, NRH = NR / SP;
   const int lane = fresh_lane();
   const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) >> 6);
   const int nwaves = (blockDim.x + 63) >> 6;
@@ -345,8 +345,8 @@ __device__ __forceinline__ double coupling_adj_pairs(const cx<float>* A, cx<floa
       Tf[i < NK ? i : 0] = frag[(0 * 64 + lane) * 4 + i];
       Tt[i < NK ? i : 0] = frag[(1 * 64 + lane) * 4 + i];
       const int Jc = J < nj ? J : nj - 1;
-      og[i < NK ? i : 0] = lds_row<NR, float, fwd_split<NR, float, W>(), W>(Jc);
-      oe[i < NK ? i : 0] = lds_row<NR, float, fwd_split<NR, float, W>(), W>(nj + Jc);
+      og[i < NK ? i : 0] = lds_row<NR, float, SP, W>(Jc);
+      oe[i < NK ? i : 0] = lds_row<NR, float, SP, W>(nj + Jc);
     }
   }
   double grad = 0.0;
@@ -417,10 +417,9 @@ __device__ __forceinline__ double coupling_adj_pairs(const cx<float>* A, cx<floa
 
 // LDS of the complex64 form: transform tables (compact twiddles), the round's
 // lambda rows and chi rows, the reduction scratch
-template <int NR, int W>
+template <int NR, int W, int SP>
 struct Adj32Shape {
   typedef StagedTables<NR, float, true, false, W> TBL;
-  static constexpr int SP = fwd_split<NR, float, W>();
   static size_t buf_bytes(int nj) {
     return (sizeof(cx<float>) * static_cast<size_t>(lds_line_start(2 * nj, fwd_line_stride<NR, float, SP, W>(), 8)) + 15) / 16 * 16;
   }
@@ -437,17 +436,17 @@ struct Adj32Shape {
 template <int NR, bool KH, int W>
 constexpr int adj32_waves() { return FftShape<NR, float, W>::R1 > 16 ? 2 : (KH ? 4 : 3); }
 
-template <int NR, bool NEXT, bool KH, int W>
+template <int NR, bool NEXT, bool KH, int W, int SP>
 __global__ __launch_bounds__(512)
 __attribute__((amdgpu_waves_per_eu(adj32_waves<NR, KH, W>(), adj32_waves<NR, KH, W>()))) void mol_adj32_kernel(MolAdjArgs a) {
-  typedef Adj32Shape<NR, W> S;
+  typedef Adj32Shape<NR, W, SP> S;
   typedef typename S::TBL TBL;
   constexpr int R1 = FftShape<NR, float, W>::R1, R2 = FftShape<NR, float, W>::R2;
-  constexpr int SP = S::SP, PH = R1 / SP, NRH = NR / SP, TWC = TBL::TWC;
+  constexpr int PH = R1 / SP, NRH = NR / SP, TWC = TBL::TWC;
   extern __shared__ __align__(16) unsigned char smem[];
   const int nj = a.nj;
   const int L = 2 * nj;
-  const int buf = (lds_row<NR, float, fwd_split<NR, float, W>(), W>(L) + 1) / 2 * 2;
+  const int buf = (lds_row<NR, float, SP, W>(L) + 1) / 2 * 2;
   cx<float>* kin = reinterpret_cast<cx<float>*>(smem);
   cx<float>* tw = kin + NR;
   float* mask = reinterpret_cast<float*>(tw + TBL::tw_elems);
@@ -475,8 +474,8 @@ __attribute__((amdgpu_waves_per_eu(adj32_waves<NR, KH, W>(), adj32_waves<NR, KH,
   const cx<float>* psi = static_cast<const cx<float>*>(a.psi_n) + base;
   const cx<float>* nxt = static_cast<const cx<float>*>(a.psi_np1) + base;
   cx<float>* lpsi = static_cast<cx<float>*>(a.lpsi) + base;
-  cx<float>* slot = B + lds_row<NR, float, fwd_split<NR, float, W>(), W>(line);    // this line's row of the round
-  cx<float>* aslot = A + lds_row<NR, float, fwd_split<NR, float, W>(), W>(line);
+  cx<float>* slot = B + lds_row<NR, float, SP, W>(line);    // this line's row of the round
+  cx<float>* aslot = A + lds_row<NR, float, SP, W>(line);
   const int loff = line * NR + q;
 
   // ---- chi = V K psi, and psi_pre = K V C(chi) or psi^{n+1} = m psi_pre (v)
@@ -507,7 +506,7 @@ __attribute__((amdgpu_waves_per_eu(adj32_waves<NR, KH, W>(), adj32_waves<NR, KH,
         for (int pp = 0; pp < PH; ++pp) aslot[q + R2 * pp] = ch[h * PH + pp];
       }
       __syncthreads();
-      coupling_adj_pairs<NR, false, KH, W>(A, B, nj, h * NRH, frag, xk, mudt, E);
+      coupling_adj_pairs<NR, false, KH, W, SP>(A, B, nj, h * NRH, frag, xk, mudt, E);
       __syncthreads();
       if (active) {
 #pragma unroll
@@ -530,8 +529,8 @@ __attribute__((amdgpu_waves_per_eu(adj32_waves<NR, KH, W>(), adj32_waves<NR, KH,
   // rows of the other state's neighbours J - 1 and J + 1 (their own line where
   // there is none: its factor is zero)
   const int sb = (1 - s_of_line) * nj;
-  const cx<float>* rowm = B + lds_row<NR, float, fwd_split<NR, float, W>(), W>(J_of_line > 0 ? sb + J_of_line - 1 : line);
-  const cx<float>* rowp = B + lds_row<NR, float, fwd_split<NR, float, W>(), W>(J_of_line + 1 < nj ? sb + J_of_line + 1 : line);
+  const cx<float>* rowm = B + lds_row<NR, float, SP, W>(J_of_line > 0 ? sb + J_of_line - 1 : line);
+  const cx<float>* rowp = B + lds_row<NR, float, SP, W>(J_of_line + 1 < nj ? sb + J_of_line + 1 : line);
 #pragma unroll
   for (int h = 0; h < SP; ++h) {
     if (h > 0) __syncthreads();
@@ -576,7 +575,7 @@ __attribute__((amdgpu_waves_per_eu(adj32_waves<NR, KH, W>(), adj32_waves<NR, KH,
       }
     }
     __syncthreads();
-    grad += coupling_adj_pairs<NR, true, KH, W>(A, B, nj, h * NRH, frag, xk, mudt, E);
+    grad += coupling_adj_pairs<NR, true, KH, W, SP>(A, B, nj, h * NRH, frag, xk, mudt, E);
     __syncthreads();
     if (active) {
 #pragma unroll
@@ -596,16 +595,16 @@ __attribute__((amdgpu_waves_per_eu(adj32_waves<NR, KH, W>(), adj32_waves<NR, KH,
   if (tid == 0) a.lE[mol] = sums[0];
 }
 
-template <int NR, bool NEXT, bool KH, int W>
+template <int NR, bool NEXT, bool KH, int W, int SP>
 static int launch_mol_adj32(const MolAdjArgs& a, hipStream_t s) {
   const int threads = (2 * a.nj * FftShape<NR, float, W>::R2 + 63) / 64 * 64;
-  const size_t shm = Adj32Shape<NR, W>::bytes(a.nj);
+  const size_t shm = Adj32Shape<NR, W, SP>::bytes(a.nj);
   static std::atomic<unsigned long long> lds_set{0};
   if (shm > 64 * 1024) {
-    const hipError_t e = allow_large_lds(reinterpret_cast<const void*>(&mol_adj32_kernel<NR, NEXT, KH, W>), lds_set);
+    const hipError_t e = allow_large_lds(reinterpret_cast<const void*>(&mol_adj32_kernel<NR, NEXT, KH, W, SP>), lds_set);
     if (e != hipSuccess) return static_cast<int>(e);
   }
-  hipLaunchKernelGGL((mol_adj32_kernel<NR, NEXT, KH, W>), dim3(a.n_mol), dim3(threads), shm, s, a);
+  hipLaunchKernelGGL((mol_adj32_kernel<NR, NEXT, KH, W, SP>), dim3(a.n_mol), dim3(threads), shm, s, a);
   return static_cast<int>(hipGetLastError());
 }
 
@@ -631,10 +630,22 @@ static int launch_mol_adj64(const MolAdjArgs& a, hipStream_t s) {
   return static_cast<int>(hipGetLastError());
 }
 
+// At n_r = 128 small batches take one exchange round instead of two: twice the LDS,
+// but fewer barriers where the launch is one molecule's serial work.  Reverse step in
+// us, two rounds / one (whole-line form before), psi^{n+1} given, J <= 6: 5 molecules
+// 28.7 / 26.9 (27.4), 1,000 43.1 / 40.1 (42.8), 1,500 52.1 / 59.7; J <= 10: 333 37.7 /
+// 35.5 (37.2), 600 47.7 / 45.8, 1,000 58.8 / 59.3; J <= 15: 333 40.7 / 38.8, 600 49.4 /
+// 56.1; recomputed, J <= 10: 100 39.4 / 35.0 (36.2), 1,000 68.7 / 71.0.
+constexpr int adj32_one_round_max(bool half_k) { return half_k ? 1024 : 512; }
+
 template <typename T, int NR, bool NEXT, bool KH>
 static int launch_mol_adj_n(const MolAdjArgs& a, hipStream_t s) {
+  constexpr int W = wide_lines<float, NR>() ? 2 : 1;
+  if constexpr (sizeof(T) == 4 && NR == 128) {
+    if (a.n_mol <= adj32_one_round_max(KH)) return launch_mol_adj32<NR, NEXT, KH, W, 1>(a, s);
+  }
   if constexpr (sizeof(T) == 4)
-    return launch_mol_adj32<NR, NEXT, KH, wide_lines<float, NR>() ? 2 : 1>(a, s);
+    return launch_mol_adj32<NR, NEXT, KH, W, fwd_split<NR, float, W>()>(a, s);
   else
     return launch_mol_adj64<NR, NEXT, KH>(a, s);
 }
