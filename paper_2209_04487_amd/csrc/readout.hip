@@ -24,6 +24,7 @@ namespace msqd {
 
 constexpr int kRdThreads = 256;
 constexpr int kRdWaves = kRdThreads / 64;
+constexpr int kRdMaxNr = 512;
 
 namespace {
 
@@ -53,19 +54,34 @@ __device__ __forceinline__ double rd_wave_sum(double v) {
 // dipole; the norm also when no dipole is asked for, as the finiteness check.
 // 100,000 molecules of n_r = 256, J <= 10 in complex64 (4.5 GB): 1221 us when the
 // step's kernel did this (lines through LDS, barriers), 734 us here (6.1 TB/s).
-template <typename T>
+// SPLIT: the four wavefronts of a workgroup take a molecule's points in turn and the
+// first one adds their terms up from LDS, where lines hold a load for each of them
+// (n_r = 256 in complex128, 512 in complex64): a wavefront alone goes through four or
+// eight loads of every line one after another, which is what a small batch waits for,
+// and streams less well in a large one.  us, one wavefront / four: complex128, n_r = 256,
+// J <= 15: 8 molecules 9.1 / 5.2 (6.1 in the step's kernel), 333 17.7 / 10.1 (13.6),
+// 30,000 644 / 636; J <= 10, 50,000: 825 / 745; complex64, n_r = 512, J <= 8: 8 6.5 /
+// 4.2, 60,000 771 / 704.  Shorter lines lose by it in large batches (complex64, n_r =
+// 256, J <= 10, 100,000: 737 / 746; complex128, n_r = 128, J = 0, 200,000: 156 / 165).
+template <typename T, bool SPLIT>
 __global__ __launch_bounds__(kRdThreads) void mol_readout_kernel(MolArgs a, int n_r) {
-  constexpr int V = RdVec<T>::V;
-  const int lane = threadIdx.x & 63;
-  const int mol = blockIdx.x * kRdWaves + (threadIdx.x >> 6);
+  constexpr int V = RdVec<T>::V, kUnroll = SPLIT ? 8 : 4;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int mol = SPLIT ? static_cast<int>(blockIdx.x) : static_cast<int>(blockIdx.x) * kRdWaves + wave;
   if (mol >= a.n_mol) return;
   const int nj = a.nj;
   const double* mu = reinterpret_cast<const double*>(a.ws + a.lay.mu_d);
   const double* cj = reinterpret_cast<const double*>(a.ws + a.lay.cj_d);
   const cx<T>* g = static_cast<const cx<T>*>(a.psi) + static_cast<size_t>(mol) * 2 * nj * n_r;
   const cx<T>* e = g + static_cast<size_t>(nj) * n_r;
+  __shared__ double terms[2][SPLIT ? kRdMaxNr : 1];
   double nrm = 0.0, yld = 0.0, dd = 0.0;
-  for (int r = lane * V; r < n_r; r += 64 * V) {
+  auto add = [&](int r, double acc, double n2) {
+    dd += mu[r] * acc;
+    nrm += n2;
+    if (r >= a.kdiss) yld += n2;
+  };
+  for (int r = (SPLIT ? static_cast<int>(threadIdx.x) : lane) * V; r < n_r; r += (SPLIT ? kRdThreads : 64) * V) {
     RdVec<T> g0 = rd_load(g + r), e0 = rd_load(e + r);
     T acc[V];
     double n2[V];
@@ -74,7 +90,7 @@ __global__ __launch_bounds__(kRdThreads) void mol_readout_kernel(MolArgs a, int 
       acc[i] = T(0);
       n2[i] = static_cast<double>(norm2(g0.p[i])) + static_cast<double>(norm2(e0.p[i]));
     }
-#pragma unroll 4
+#pragma unroll kUnroll
     for (int J = 0; J + 1 < nj; ++J) {
       const RdVec<T> g1 = rd_load(g + (J + 1) * n_r + r), e1 = rd_load(e + (J + 1) * n_r + r);
       const T c = static_cast<T>(cj[J]);
@@ -89,9 +105,20 @@ __global__ __launch_bounds__(kRdThreads) void mol_readout_kernel(MolArgs a, int 
     }
 #pragma unroll
     for (int i = 0; i < V; ++i) {
-      dd += mu[r + i] * static_cast<double>(acc[i]);
-      nrm += n2[i];
-      if (r + i >= a.kdiss) yld += n2[i];
+      if constexpr (SPLIT) {
+        terms[0][r + i] = static_cast<double>(acc[i]);
+        terms[1][r + i] = n2[i];
+      } else {
+        add(r + i, static_cast<double>(acc[i]), n2[i]);
+      }
+    }
+  }
+  if constexpr (SPLIT) {
+    __syncthreads();
+    if (wave > 0) return;
+    for (int r = lane * V; r < n_r; r += 64 * V) {
+#pragma unroll
+      for (int i = 0; i < V; ++i) add(r + i, terms[0][r + i], terms[1][r + i]);
     }
   }
   nrm = rd_wave_sum(nrm);
@@ -364,14 +391,19 @@ int launch_jm_readout(const MolArgs& a, int n_r, bool f32, hipStream_t s) {
   return f32 ? launch_jm_readout_t<float>(a, n_r, s) : launch_jm_readout_t<double>(a, n_r, s);
 }
 
+template <typename T>
+static int launch_mol_readout_t(const MolArgs& a, int n_r, hipStream_t s) {
+  if (n_r >= kRdThreads * RdVec<T>::V)
+    hipLaunchKernelGGL((mol_readout_kernel<T, true>), dim3(a.n_mol), dim3(kRdThreads), 0, s, a, n_r);
+  else
+    hipLaunchKernelGGL((mol_readout_kernel<T, false>), dim3((a.n_mol + kRdWaves - 1) / kRdWaves), dim3(kRdThreads), 0, s, a,
+                       n_r);
+  return static_cast<int>(hipGetLastError());
+}
+
 int launch_mol_readout(const MolArgs& a, int n_r, bool f32, hipStream_t s) {
   if (a.n_mol <= 0) return 0;
-  const dim3 grid((a.n_mol + kRdWaves - 1) / kRdWaves);
-  if (f32)
-    hipLaunchKernelGGL(mol_readout_kernel<float>, grid, dim3(kRdThreads), 0, s, a, n_r);
-  else
-    hipLaunchKernelGGL(mol_readout_kernel<double>, grid, dim3(kRdThreads), 0, s, a, n_r);
-  return static_cast<int>(hipGetLastError());
+  return f32 ? launch_mol_readout_t<float>(a, n_r, s) : launch_mol_readout_t<double>(a, n_r, s);
 }
 
 int launch_excited_r(const RdArgs& a, bool f32, hipStream_t s) {
