@@ -141,12 +141,14 @@ __global__ __launch_bounds__(kRdThreads) void mol_readout_kernel(MolArgs a, int 
 // <e|D_+|g>, D_+ = D_x + i D_y, d_x and d_y are Re (P + P') / 2 and Im (P + P') / 2.
 // dip: per state <j+1,m|cos|j,m>, <j+1,m+1|sin e^{i ph}|j,m>, <j-1,m+1|sin e^{i ph}|j,m>.
 // When the steps' kernels did this (lines through LDS, one workgroup per molecule)
-// -> here, us: 405 -> 272 (100,000 molecules, n_r = 256, j_max = 1, complex64), 1010 ->
-// 366 (60,000, j_max = 2), 1076 -> 413 (40,000, j_max = 3), 1650 -> 821 (20,000, j_max
-// = 5), 1055 -> 507 (8,000, n_r = 512, j_max = 4); complex128 670 -> 338 (15,000, n_r =
-// 256, j_max = 3), 1196 -> 545 (20,000, n_r = 128, j_max = 5).
-// SPLIT: the four wavefronts of a workgroup share a molecule's radial points, for
-// launches that leave the card idle otherwise.
+// -> here, us: 389 -> 265 (100,000 molecules, n_r = 256, j_max = 1, complex64), 1009 ->
+// 354 (60,000, j_max = 2), 1072 -> 415 (40,000, j_max = 3), 1644 -> 676 (20,000, j_max
+// = 5), 1041 -> 489 (8,000, n_r = 512, j_max = 4); complex128 662 -> 336 (15,000, n_r =
+// 256, j_max = 3), 1197 -> 537 (20,000, n_r = 128, j_max = 5).
+// SPLIT: the wavefronts of a workgroup share a molecule's radial points, for launches
+// that leave the card idle otherwise; the first one adds their terms up from LDS in the
+// order in which a single wavefront meets them.  The products are stated as fused, so
+// that both forms round alike and a molecule's readouts do not depend on the batch.
 template <typename T, int JM, bool SPLIT>
 __global__ __launch_bounds__(kRdThreads) void jm_readout_kernel(MolArgs a, int n_r) {
   constexpr int NB = (JM + 1) * (JM + 1), NM = 2 * JM + 1;
@@ -160,7 +162,16 @@ __global__ __launch_bounds__(kRdThreads) void jm_readout_kernel(MolArgs a, int n
       JM == 1 ? one : reinterpret_cast<const double*>(a.ws + a.lay.total) + jmg_tab(JM).dip;
   const cx<T>* g = static_cast<const cx<T>*>(a.psi) + static_cast<size_t>(mol) * 2 * NB * n_r;
   const cx<T>* e = g + static_cast<size_t>(NB) * n_r;
+  __shared__ double terms[4][SPLIT ? kRdMaxNr : 1];
   double nrm = 0.0, yld = 0.0, dx = 0.0, dy = 0.0, dz = 0.0;
+  auto add = [&](int r, double n2, double pr, double pi, double z) {
+    const double m = mu[r];
+    dx = fma(m, 0.5 * pr, dx);
+    dy = fma(m, 0.5 * pi, dy);
+    dz = fma(m, z, dz);
+    nrm += n2;
+    if (r >= a.kdiss) yld += n2;
+  };
 #pragma unroll 1
   for (int r = SPLIT ? static_cast<int>(threadIdx.x) : lane; r < n_r; r += SPLIT ? kRdThreads : 64) {
     double n2 = 0.0, z = 0.0, pr = 0.0, pi = 0.0;
@@ -170,21 +181,22 @@ __global__ __launch_bounds__(kRdThreads) void jm_readout_kernel(MolArgs a, int n
 #pragma unroll
       for (int i = 0; i < 2 * j + 1; ++i) {
         const cx<T> u = g[(j * j + i) * n_r + r], w = e[(j * j + i) * n_r + r];
-        n2 += static_cast<double>(norm2(u)) + static_cast<double>(norm2(w));
+        n2 += static_cast<double>(fma(u.x, u.x, u.y * u.y)) + static_cast<double>(fma(w.x, w.x, w.y * w.y));
         g1[i] = {static_cast<double>(u.x), static_cast<double>(u.y)};
         e1[i] = {static_cast<double>(w.x), static_cast<double>(w.y)};
       }
       // c (conj(p_g) b_e + conj(p_e) b_g)
       auto link = [&](double c, const cx<double>& pg, const cx<double>& pe, const cx<double>& bg, const cx<double>& be) {
-        pr += c * ((pg.x * be.x + pg.y * be.y) + (pe.x * bg.x + pe.y * bg.y));
-        pi += c * ((pg.x * be.y - pg.y * be.x) + (pe.x * bg.y - pe.y * bg.x));
+        pr = fma(c, fma(pg.x, be.x, fma(pg.y, be.y, fma(pe.x, bg.x, pe.y * bg.y))), pr);
+        pi = fma(c, fma(pg.x, be.y, fma(-pg.y, be.x, fma(pe.x, bg.y, -pe.y * bg.x))), pi);
       };
       if (j > 0) {
         // state (j - 1, m) = [i] with (j, m) = [i + 1] and (j, m + 1) = [i + 2]
 #pragma unroll
         for (int i = 0; i < 2 * j - 1; ++i) {
           const double* c = dip + 3 * ((j - 1) * (j - 1) + i);
-          z += c[0] * ((g1[i + 1].x * e0[i].x + g1[i + 1].y * e0[i].y) + (g0[i].x * e1[i + 1].x + g0[i].y * e1[i + 1].y));
+          z = fma(c[0], fma(g1[i + 1].x, e0[i].x, fma(g1[i + 1].y, e0[i].y,
+                                                      fma(g0[i].x, e1[i + 1].x, g0[i].y * e1[i + 1].y))), z);
           link(c[1], g1[i + 2], e1[i + 2], g0[i], e0[i]);
         }
         // state (j, m) = [i] with (j - 1, m + 1) = [i]
@@ -197,25 +209,22 @@ __global__ __launch_bounds__(kRdThreads) void jm_readout_kernel(MolArgs a, int n
         e0[i] = e1[i];
       }
     }
-    const double m = mu[r];
-    dx += m * (0.5 * pr);
-    dy += m * (0.5 * pi);
-    dz += m * z;
-    nrm += n2;
-    if (r >= a.kdiss) yld += n2;
-  }
-  double sum[5] = {rd_wave_sum(nrm), rd_wave_sum(yld), rd_wave_sum(dx), rd_wave_sum(dy), rd_wave_sum(dz)};
-  if constexpr (SPLIT) {
-    __shared__ double part[kRdWaves][5];
-    if (lane == 0) {
-#pragma unroll
-      for (int k = 0; k < 5; ++k) part[wave][k] = sum[k];
+    if constexpr (SPLIT) {
+      terms[0][r] = n2;
+      terms[1][r] = pr;
+      terms[2][r] = pi;
+      terms[3][r] = z;
+    } else {
+      add(r, n2, pr, pi, z);
     }
-    __syncthreads();
-#pragma unroll
-    for (int k = 0; k < 5; ++k) sum[k] = (part[0][k] + part[1][k]) + (part[2][k] + part[3][k]);
   }
-  if (lane == 0 && (!SPLIT || wave == 0)) {
+  if constexpr (SPLIT) {
+    __syncthreads();
+    if (wave > 0) return;
+    for (int r = lane; r < n_r; r += 64) add(r, terms[0][r], terms[1][r], terms[2][r], terms[3][r]);
+  }
+  const double sum[5] = {rd_wave_sum(nrm), rd_wave_sum(yld), rd_wave_sum(dx), rd_wave_sum(dy), rd_wave_sum(dz)};
+  if (lane == 0) {
     const double* d = sum + 2;
     nrm = sum[0];
     yld = sum[1];
@@ -359,14 +368,15 @@ __global__ void spectra_kernel(const double* st, const double* si, const double*
   tra[2 * n + f] = (si[f] - st[f]) / ref;
 }
 
-// Up to kJmSplitMol molecules of 256 radial points or more a workgroup takes one of
-// them instead of four (us, complex64, j_max = 5, n_r = 256, four / one: 10 molecules
-// 28.0 / 19.9, 300 53.8 / 22.7, 1,000 56.3 / 38.7, 2,000 87.8 / 96.0; n_r = 64, 1,000:
-// 21.7 / 33.3).
-constexpr int kJmSplitMol = 1024;
+// Small batches give each molecule a workgroup (us, a wavefront / a workgroup; j_max =
+// 5, n_r = 256, complex64: 1 molecule 20.7 / 8.9, 1,000 44.0 / 32.9, 2,000 71.2 / 80.2;
+// j_max = 3: 1,000 17.3 / 15.0, 2,000 23.6 / 23.6, 40,000 415 / 455; j_max = 4, n_r =
+// 128, complex128: 1 10.1 / 7.1, 333 20.1 / 13.2, 1,000 22.7 / 25.2; at n_r = 64 a line
+// has points for one wavefront).
+static bool jm_split(int n_mol, int n_r) { return n_mol <= (n_r >= 256 ? 1024 : 512) && n_r >= 128; }
 template <typename T, int JM>
 static int launch_jm_readout_j(const MolArgs& a, int n_r, hipStream_t s) {
-  if (a.n_mol <= kJmSplitMol && n_r >= kRdThreads)
+  if (jm_split(a.n_mol, n_r))
     hipLaunchKernelGGL((jm_readout_kernel<T, JM, true>), dim3(a.n_mol), dim3(kRdThreads), 0, s, a, n_r);
   else
     hipLaunchKernelGGL((jm_readout_kernel<T, JM, false>), dim3((a.n_mol + kRdWaves - 1) / kRdWaves), dim3(kRdThreads), 0, s,

@@ -1,0 +1,39 @@
+"""A molecule's readouts (dipole, norm, yield, the moments of Eq. (8)) do not depend on
+the batch it is in: nine random molecules repeated over a batch give each copy the bits
+that the nine have alone, with batch sizes on both sides of every rule that the launches
+have (no tolerance)."""
+
+import numpy as np
+import pytest
+import torch
+
+from gpu_helpers import banner, random_state
+from workloads import get_config
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("n", [512, 513, 1024, 1025])
+@pytest.mark.parametrize("prec, basis, n_r, j_max", [("fp32", "jm", 64, 2), ("fp64", "jm", 128, 4), ("fp32", "jm", 128, 5),
+                                                     ("fp32", "jm", 256, 5), ("fp64", "jm", 256, 2), ("mixed", "jm", 256, 1),
+                                                     ("fp64", "jm", 512, 1), ("fp32", "jm", 512, 3), ("fp64", "m0", 64, 3),
+                                                     ("fp64", "m0", 128, 10), ("mixed", "m0", 256, 10),
+                                                     ("fp64", "m0", 256, 4), ("fp32", "m0", 512, 2)])
+def test_readouts_do_not_depend_on_the_batch(prec, basis, n_r, j_max, n):
+    from paper_2209_04487_amd import msqd
+    banner(f"readouts {prec} {basis} n_r={n_r} j_max={j_max} in a batch of {n}")
+    few = 9
+    psi = torch.as_tensor(random_state(n_r + j_max, few, (j_max + 1) ** (2 if basis == "jm" else 1), n_r, 11.0 / n_r))
+    out = []
+    for size in (few, n):
+        m = msqd.Molecules.from_config(get_config("cfg0", n_r=n_r, j_max=j_max, basis=basis, n_mol=size), prec=prec)
+        at = torch.arange(size, device="cuda") % few
+        m.psi.copy_(psi.cuda().to(m.psi.dtype)[at])
+        m.absorbed.copy_(0.01 * at)
+        d, nrm, yld = m.readout()
+        num, pop, _ = msqd.excited_r(m)
+        out.append([v.cpu().numpy()[:size] for v in (d, nrm, yld, num, pop)])
+    at = np.arange(n) % few
+    for name, a, b in zip(("dipole", "norm", "yield", "r_num", "pop"), *out):
+        assert np.abs(a).max() > 0
+        assert np.array_equal(a[at], b), name
