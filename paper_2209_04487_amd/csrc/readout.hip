@@ -242,15 +242,25 @@ __global__ __launch_bounds__(kRdThreads) void jm_readout_kernel(MolArgs a, int n
   }
 }
 
-template <typename T>
+// The moments of Eq. (8), with the wavefronts of a workgroup sharing long lines as in
+// mol_readout_kernel (us with the ensemble sums, one wavefront / four, and one pass of a
+// workgroup over all lines before: complex128, n_r = 256, J <= 15, 10,000 molecules 156 /
+// 120, 131; J <= 10, 64 molecules 7.6 / 6.1, 6.9; complex64, n_r = 512, J <= 8, 30,000
+// 224 / 196, 268).
+template <typename T, bool SPLIT>
 __global__ __launch_bounds__(kRdThreads) void excited_r_kernel(RdArgs a) {
   constexpr int V = RdVec<T>::V;
-  const int lane = threadIdx.x & 63;
-  const int mol = blockIdx.x * kRdWaves + (threadIdx.x >> 6);
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int mol = SPLIT ? static_cast<int>(blockIdx.x) : static_cast<int>(blockIdx.x) * kRdWaves + wave;
   if (mol >= a.n_mol) return;
   const cx<T>* e = static_cast<const cx<T>*>(a.psi) + (static_cast<size_t>(mol) * 2 + 1) * a.nj * a.n_r;
+  __shared__ double terms[SPLIT ? kRdMaxNr : 1];
   double num = 0.0, pop = 0.0;
-  for (int r = lane * V; r < a.n_r; r += 64 * V) {
+  auto add = [&](int r, double p2) {
+    pop += p2;
+    num += (a.r_min + r * a.dr) * p2;
+  };
+  for (int r = (SPLIT ? static_cast<int>(threadIdx.x) : lane) * V; r < a.n_r; r += (SPLIT ? kRdThreads : 64) * V) {
     double p2[V];
 #pragma unroll
     for (int i = 0; i < V; ++i) p2[i] = 0.0;
@@ -265,8 +275,18 @@ __global__ __launch_bounds__(kRdThreads) void excited_r_kernel(RdArgs a) {
     }
 #pragma unroll
     for (int i = 0; i < V; ++i) {
-      pop += p2[i];
-      num += (a.r_min + (r + i) * a.dr) * p2[i];
+      if constexpr (SPLIT)
+        terms[r + i] = p2[i];
+      else
+        add(r + i, p2[i]);
+    }
+  }
+  if constexpr (SPLIT) {
+    __syncthreads();
+    if (wave > 0) return;
+    for (int r = lane * V; r < a.n_r; r += 64 * V) {
+#pragma unroll
+      for (int i = 0; i < V; ++i) add(r + i, terms[r + i]);
     }
   }
   num = rd_wave_sum(num);
@@ -277,19 +297,20 @@ __global__ __launch_bounds__(kRdThreads) void excited_r_kernel(RdArgs a) {
   }
 }
 
-// ensemble sums over molecules (one workgroup, fixed order) and their ratio: a
-// single CU's read of 16 bytes per molecule, kept busy by 1,024 threads with eight
-// independent loads each (100,000 molecules: 164 us with 256 threads and one
-// load in flight each)
+// ensemble sums over molecules (one workgroup, an order fixed by their number) and
+// their ratio: a single CU's read of 16 bytes per molecule, kept busy by 1,024 threads
+// with eight independent loads each (100,000 molecules: 164 us with 256 threads and one
+// load in flight each), one wavefront where that is one pass (0.5 us less at 64 molecules)
 constexpr int kPairThreads = 1024, kPairLoads = 8;
-__global__ __launch_bounds__(kPairThreads) void pair_sum_kernel(const double* x, const double* y, int n, double* out) {
-  __shared__ double sx[kPairThreads / 64], sy[kPairThreads / 64];
+template <int THREADS>
+__global__ __launch_bounds__(THREADS) void pair_sum_kernel(const double* x, const double* y, int n, double* out) {
+  __shared__ double sx[THREADS / 64], sy[THREADS / 64];
   const int tid = threadIdx.x;
   double ax[kPairLoads] = {}, ay[kPairLoads] = {};
-  for (int i0 = tid; i0 < n; i0 += kPairLoads * kPairThreads) {
+  for (int i0 = tid; i0 < n; i0 += kPairLoads * THREADS) {
 #pragma unroll
     for (int u = 0; u < kPairLoads; ++u) {
-      const int i = i0 + u * kPairThreads;
+      const int i = i0 + u * THREADS;
       ax[u] += i < n ? x[i] : 0.0;
       ay[u] += i < n ? y[i] : 0.0;
     }
@@ -307,7 +328,7 @@ __global__ __launch_bounds__(kPairThreads) void pair_sum_kernel(const double* x,
   __syncthreads();
   if (tid == 0) {
     double tx = 0.0, ty = 0.0;
-    for (int w = 0; w < kPairThreads / 64; ++w) {
+    for (int w = 0; w < THREADS / 64; ++w) {
       tx += sx[w];
       ty += sy[w];
     }
@@ -416,16 +437,26 @@ int launch_mol_readout(const MolArgs& a, int n_r, bool f32, hipStream_t s) {
   return f32 ? launch_mol_readout_t<float>(a, n_r, s) : launch_mol_readout_t<double>(a, n_r, s);
 }
 
+template <typename T>
+static void launch_excited_r_t(const RdArgs& a, hipStream_t s) {
+  if (a.n_r >= kRdThreads * RdVec<T>::V)
+    hipLaunchKernelGGL((excited_r_kernel<T, true>), dim3(a.n_mol), dim3(kRdThreads), 0, s, a);
+  else
+    hipLaunchKernelGGL((excited_r_kernel<T, false>), dim3((a.n_mol + kRdWaves - 1) / kRdWaves), dim3(kRdThreads), 0, s, a);
+}
+
 int launch_excited_r(const RdArgs& a, bool f32, hipStream_t s) {
   if (a.n_mol <= 0) return 0;
-  const dim3 grid((a.n_mol + kRdWaves - 1) / kRdWaves);
   if (f32)
-    hipLaunchKernelGGL(excited_r_kernel<float>, grid, dim3(kRdThreads), 0, s, a);
+    launch_excited_r_t<float>(a, s);
   else
-    hipLaunchKernelGGL(excited_r_kernel<double>, grid, dim3(kRdThreads), 0, s, a);
+    launch_excited_r_t<double>(a, s);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || a.sums == nullptr) return static_cast<int>(e);
-  hipLaunchKernelGGL(pair_sum_kernel, dim3(1), dim3(kPairThreads), 0, s, a.r_num, a.pop, a.n_mol, a.sums);
+  if (a.n_mol <= 64 * kPairLoads)
+    hipLaunchKernelGGL(pair_sum_kernel<64>, dim3(1), dim3(64), 0, s, a.r_num, a.pop, a.n_mol, a.sums);
+  else
+    hipLaunchKernelGGL(pair_sum_kernel<kPairThreads>, dim3(1), dim3(kPairThreads), 0, s, a.r_num, a.pop, a.n_mol, a.sums);
   return static_cast<int>(hipGetLastError());
 }
 

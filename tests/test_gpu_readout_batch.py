@@ -37,3 +37,18 @@ def test_readouts_do_not_depend_on_the_batch(prec, basis, n_r, j_max, n):
     for name, a, b in zip(("dipole", "norm", "yield", "r_num", "pop"), *out):
         assert np.abs(a).max() > 0
         assert np.array_equal(a[at], b), name
+
+
+@pytest.mark.parametrize("n", [1, 64, 512, 513, 8193])
+def test_excited_sums_at_the_edges_of_their_passes(n):
+    """The ensemble sums of Eq. (8): one and several passes of their loads, one wavefront
+    and sixteen (1e-12: at most 8,193 positive terms, each addition rounded to 1.1e-16)."""
+    from paper_2209_04487_amd import msqd
+    banner(f"excited-state sums over {n} molecules")
+    m = msqd.Molecules.from_config(get_config("cfg0", n_r=64, j_max=0, n_mol=n), prec="fp64")
+    g = torch.Generator(device="cuda").manual_seed(n)
+    m.psi.copy_(torch.randn(m.psi.shape, generator=g, device="cuda", dtype=m.psi.dtype))
+    num, pop, r_e = msqd.excited_r(m)
+    num, pop = num.cpu().numpy(), pop.cpu().numpy()
+    assert num.min() > 0 and pop.min() > 0
+    np.testing.assert_allclose(float(r_e), num.sum() / pop.sum(), rtol=1e-12)
