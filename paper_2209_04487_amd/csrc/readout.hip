@@ -34,10 +34,12 @@ struct RdVec {
   static constexpr int V = 16 / static_cast<int>(sizeof(cx<T>));
   cx<T> p[V];
 };
+// (one load of 16 bytes on the elements' own alignment: excited_r_readout takes any)
+typedef unsigned RdRaw __attribute__((ext_vector_type(4), aligned(4)));
 template <typename T>
 __device__ __forceinline__ RdVec<T> rd_load(const cx<T>* p) {
   RdVec<T> v;
-  *reinterpret_cast<uint4*>(&v) = *reinterpret_cast<const uint4*>(p);
+  *reinterpret_cast<RdRaw*>(&v) = *reinterpret_cast<const RdRaw*>(p);
   return v;
 }
 

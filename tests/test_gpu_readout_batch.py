@@ -52,3 +52,24 @@ def test_excited_sums_at_the_edges_of_their_passes(n):
     num, pop = num.cpu().numpy(), pop.cpu().numpy()
     assert num.min() > 0 and pop.min() > 0
     np.testing.assert_allclose(float(r_e), num.sum() / pop.sum(), rtol=1e-12)
+
+
+@pytest.mark.parametrize("prec, n_r", [("fp32", 64), ("fp32", 512), ("fp64", 256)])
+def test_excited_readout_of_a_wavepacket_buffer_off_16_bytes(prec, n_r):
+    """excited_r_readout takes wavepackets on their elements' own alignment (8 bytes off a
+    multiple of 16 here) and gives the bits of the aligned buffer."""
+    from paper_2209_04487_amd import msqd
+    banner(f"excited-state readout off 16 bytes {prec} n_r={n_r}")
+    m = msqd.Molecules.from_config(get_config("cfg0", n_r=n_r, j_max=3, n_mol=7), prec=prec)
+    psi = torch.as_tensor(random_state(n_r, 7, 4, n_r, 11.0 / n_r)).to(m.psi.dtype).cuda()
+    m.psi.copy_(psi)
+    want = [v.cpu().numpy() for v in msqd.excited_r(m)]
+    real = torch.view_as_real(psi).reshape(-1)
+    buf = torch.empty(real.numel() + 2, dtype=real.dtype, device="cuda")
+    off = 2 if prec == "fp32" else 1
+    buf[off:off + real.numel()] = real
+    assert buf.data_ptr() % 16 == 0
+    m.psi = buf[off:off + real.numel()]
+    assert m.psi.data_ptr() % 16 == 8
+    for a, b in zip(want, msqd.excited_r(m)):
+        assert np.array_equal(a, b.cpu().numpy())
