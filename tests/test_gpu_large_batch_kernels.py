@@ -1,0 +1,72 @@
+"""The complex64 kernels that large batches take at n_r = 256, where small ones take 16
+lanes per line: the (j, m) step at j_max = 1 from 2,049 molecules on against the oracle,
+every copy of a few seeded states, on both sides of the limit; and the norm over 20,000
+steps of the m = 0 step at N_J = 11 from 513 molecules on.
+
+Tolerances as for the same quantities of the small batches: 3e-5 of the largest
+amplitude, ten times that for the sums; 5e-5 for the norm's drift."""
+
+import numpy as np
+import pytest
+import torch
+
+from gpu_helpers import TOL, banner, random_state, rel_err
+from oracle.molecule_jm import jm_model_from_config
+from workloads import get_config
+from workloads.molecule_inputs import potentials
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("n_steps", [1, 3])
+@pytest.mark.parametrize("n", [2048, 2049])
+@pytest.mark.parametrize("prec", ["fp32", "mixed"])
+def test_jm1_step_on_both_sides_of_the_lane_limit(prec, n, n_steps):
+    from paper_2209_04487_amd import msqd
+    cfg = get_config("cfg0", n_r=256, j_max=1, basis="jm", n_mol=n)
+    banner(f"jm j_max=1 {prec} n_mol={n} steps={n_steps}")
+    m = msqd.Molecules.from_config(cfg, prec=prec)
+    few, dr = 7, (cfg.r_max - cfg.r_min) / 256
+    psi = random_state(n + n_steps, few, 4, 256, dr).astype(np.complex64)
+    at = np.arange(n) % few
+    rng = np.random.default_rng(n)
+    E3 = rng.uniform(-0.05, 0.05, (few, 3))
+    E3[0] = 0.0
+    E3[1] = [1e-30, 0.0, 0.0]                 # a vanishing field
+    E3[2] = [0.3, -0.2, 0.25]                 # a strong field (large-angle branch)
+    m.psi.copy_(torch.as_tensor(psi[at]))
+    m.step(torch.as_tensor(E3[at], device="cuda"), n_steps=n_steps)
+    d, nrm, yld = (t.cpu().numpy() for t in m.readout())
+    om = jm_model_from_config(cfg, *potentials(cfg))
+    p, ab = psi.astype(np.complex128), np.zeros(few)
+    for _ in range(n_steps):
+        p, ab = om.step(p, E3, ab)
+    tol = TOL[prec]
+    got = m.psi.cpu().numpy()
+    assert np.array_equal(got, got[:few][at])
+    assert rel_err(got[:few], p) < tol
+    for v in (m.d.cpu().numpy(), d):
+        assert np.array_equal(v, v[:few][at]) and rel_err(v[:few], om.dipole(p)) < 10 * tol
+    np.testing.assert_allclose(nrm, om.norm(p)[at], rtol=10 * tol)
+    np.testing.assert_allclose(yld, om.dissociated(p, ab)[at], rtol=10 * tol, atol=1e-12)
+    np.testing.assert_allclose(m.absorbed.cpu().numpy(), ab[at], rtol=10 * tol, atol=1e-12)
+
+
+@pytest.mark.parametrize("prec", ["fp32", "mixed"])
+def test_large_batch_norm_does_not_drift(prec):
+    """20,000 field-free steps of the 256-point, J <= 10 molecule in the kernel that the
+    100,000-molecule workload runs (8 lanes per line, two exchange rounds): the norm stays
+    within 5e-5 of one at every checkpoint."""
+    from paper_2209_04487_amd import msqd
+    n = 513
+    banner(f"{prec} field-free norm over 20000 steps, {n} molecules")
+    m = msqd.Molecules.from_config(get_config("cfg2"), n_mol=n, prec=prec)
+    E = torch.zeros(n, dtype=torch.float64, device="cuda")
+    worst = 0.0
+    for _ in range(10):
+        m.step(E, n_steps=2000)
+        _, nrm, _ = m.readout()
+        tot = nrm.cpu().numpy() + m.absorbed.cpu().numpy()
+        worst = max(worst, float(np.abs(tot - 1.0).max()))
+    print(f"max |norm + absorbed - 1| = {worst:.3e}")
+    assert worst < 5e-5
