@@ -1176,11 +1176,18 @@ constexpr bool mol_parts() {
 //    three (30,000 molecules, N_J = 1: 428 / 316; 3: 558 / 406; 4: 636 / 512; 7: 724 /
 //    676; 8: 846 / 727; mixed form 423 / 342, 556 / 430, 634 / 538, 731 / 712, 827 /
 //    795).  From N_J = 9 a workgroup has five to eight wavefronts, of which a CU takes
-//    two instead of four of half as many (N_J = 9: 1030 / 1425; 11: 1068 / 1431);
+//    two instead of four of half as many (N_J = 9: 1030 / 1425; 11: 1068 / 1431).  Where
+//    one wave of the narrow workgroups holds the batch and one of the wide ones does not,
+//    wide lines lose (FP32 N_J = 4, 1,408 to 1,536 molecules 2 to 5%: 37.1 / 38.9; N_J =
+//    8, 900 to 1,024 1 to 4%; mixed N_J = 4 and 5 at 1,408 to 1,536 5 to 6%: 36.7 / 38.9,
+//    6 and 7 at 1,152 to 1,280 3 to 7%: 36.8 / 38.4, 8 at 900 to 1,024 10 to 12%: 34.2 /
+//    37.6); on either side they gain 7 to 40%.  The rule has no such band, so that up to
+//    N_J = 8 a molecule's bits do not depend on the batch;
 //  any N_J up to 512 molecules, where two workgroups per CU hold all of them and the
 //    serial work of a wavefront is what a launch takes (N_J = 11, 64 molecules: 26.8 /
 //    19.9, mixed 24.8 / 18.8; 512: 37.4 / 31.8, 32.2 / 28.2; 700: 46.5 / 43.9, 39.2 /
-//    41.6; N_J = 16, 512: 40.0 / 35.3).
+//    41.6; N_J = 16, 512: 40.0 / 35.3).  The two forms transform in another order, so
+//    there a molecule's last digits change between 512 and 513 molecules.
 constexpr int kWideMaxNJ = 8, kWideMaxMol = 512;
 template <typename T, int NR>
 constexpr bool wide_lines() { return sizeof(T) == 4 && NR == 256; }

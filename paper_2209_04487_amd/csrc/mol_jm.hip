@@ -352,7 +352,11 @@ int launch_jm_t1(const MolArgs& a, hipStream_t s) {
 
 // Wide lines (mol_impl.h) while the launch is bound by the serial work of a
 // wavefront: us per step, 8 lanes per line / 16: 1 molecule 18.6 / 13.1, 333 20.9 /
-// 16.0, 1,500 29.1 / 26.9, 5,000 72.4 / 70.7, 30,000 360 / 370, 200,000 2106 / 2200.
+// 16.0, 1,024 23.2 / 16.9, 1,536 25.1 / 22.1, 1,792 27.1 / 26.8, 2,048 30.0 / 31.1 (two
+// steps 48.5 / 47.2).  That is one wave of workgroups, and the line.  The sides cross once
+// more: 3,072 47.6 / 41.4, 5,000 64.0 / 59.8, 8,000 91.8 / 87.2, 20,000 214 / 221, 200,000
+// 2106 / 2200.  The two forms transform in another order, so a molecule's last digits
+// change between them.
 constexpr int kJmWideMaxMol = 2048;
 
 // a single-step instantiation for the coupled step's launches
