@@ -420,11 +420,14 @@ __device__ __forceinline__ double coupling_adj_pairs(const cx<float>* A, cx<floa
 template <int NR, int W, int SP>
 struct Adj32Shape {
   typedef StagedTables<NR, float, true, false, W> TBL;
-  static size_t buf_bytes(int nj) {
+  static constexpr size_t buf_bytes(int nj) {
     return (sizeof(cx<float>) * static_cast<size_t>(lds_line_start(2 * nj, fwd_line_stride<NR, float, SP, W>(), 8)) + 15) / 16 * 16;
   }
-  static size_t bytes(int nj) { return TBL::bytes + 2 * buf_bytes(nj) + 16 * sizeof(double); }
+  static constexpr size_t bytes(int nj) { return TBL::bytes + 2 * buf_bytes(nj) + 16 * sizeof(double); }
 };
+// (the forms that can take more than the two line buffers of mol_adj_lds_bytes)
+static_assert(Adj32Shape<256, 2, 1>::bytes(kMaxNJ) <= 160 * 1024 && Adj32Shape<128, 1, 1>::bytes(kMaxNJ) <= 160 * 1024,
+              "the largest basis");
 
 // Wavefronts per execution unit: four where the lines' 16 points per lane (twice:
 // chi and lambda) and a half-K tile fit 128 registers, three with the full-K tile,
@@ -599,6 +602,7 @@ template <int NR, bool NEXT, bool KH, int W, int SP>
 static int launch_mol_adj32(const MolAdjArgs& a, hipStream_t s) {
   const int threads = (2 * a.nj * FftShape<NR, float, W>::R2 + 63) / 64 * 64;
   const size_t shm = Adj32Shape<NR, W, SP>::bytes(a.nj);
+  if (shm > mol_lds_limit()) return static_cast<int>(hipErrorInvalidValue);
   static std::atomic<unsigned long long> lds_set{0};
   if (shm > 64 * 1024) {
     const hipError_t e = allow_large_lds(reinterpret_cast<const void*>(&mol_adj32_kernel<NR, NEXT, KH, W, SP>), lds_set);
@@ -609,7 +613,7 @@ static int launch_mol_adj32(const MolAdjArgs& a, hipStream_t s) {
 }
 
 // LDS that a molecule's two line buffers take: the limit on what is accepted (the
-// complex64 form needs about half of it)
+// complex64 form needs about half of it in two rounds, a little more in one)
 size_t mol_adj_lds_bytes(int n_r, int nj, bool f32) {
   const size_t el = f32 ? 8 : 16;
   const int r2 = n_r / fft_r1(n_r, static_cast<int>(el / 2));

@@ -1126,6 +1126,17 @@ void mol_step_kernel(MolArgs a) {
   }
 }
 
+// LDS of a workgroup with L lines: tables, lines, the contractions' spare row, the
+// reduction scratch.  What is accepted is decided by the 8-lane form (mol_lds_bytes);
+// the wide one takes more, within the 160 KB of a CU for every accepted size.
+template <typename T, int NR, int SP, int W>
+constexpr size_t mol_step_lds(int L) {
+  return lds_table_bytes<NR, T, W>() +
+         sizeof(cx<T>) * (static_cast<size_t>(lds_line_start(L, fwd_line_stride<NR, T, SP, W>(), sizeof(cx<T>))) + NR / SP) +
+         16 * 4 * sizeof(double);
+}
+static_assert(mol_step_lds<float, 256, 1, 2>(2 * kMaxNJ) <= 160 * 1024, "wide lines of the largest basis");
+
 template <typename T, int NR, int CP, bool ONE, bool PARTS, int W>
 int launch_mol_t1(const MolArgs& a, hipStream_t s) {
   static_assert(NR == FftShape<NR, T, W>::R1 * FftShape<NR, T, W>::R2, "FFT shape");
@@ -1133,10 +1144,8 @@ int launch_mol_t1(const MolArgs& a, hipStream_t s) {
   const int L = 2 * a.nj;
   int threads = ((L * R2 + 63) / 64) * 64;
   if (threads < 64) threads = 64;
-  const size_t shm = lds_table_bytes<NR, T, W>() +
-                     sizeof(cx<T>) * (static_cast<size_t>(lds_line_start(L, fwd_line_stride<NR, T, SP, W>(), sizeof(cx<T>))) +
-                                      NR / SP) +
-                     16 * 4 * sizeof(double);
+  const size_t shm = mol_step_lds<T, NR, SP, W>(L);
+  if (shm > mol_lds_limit()) return static_cast<int>(hipErrorInvalidValue);
   static std::atomic<unsigned long long> lds_set{0};
   if (shm > 64 * 1024) {
     const hipError_t e = allow_large_lds(reinterpret_cast<const void*>(&mol_step_kernel<T, NR, CP, ONE, PARTS, W>), lds_set);
