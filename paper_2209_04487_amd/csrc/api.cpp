@@ -574,9 +574,7 @@ static int readout_impl(const qd_desc* d, const void* ws, const void* psi, const
     if (!ws || !psi || !absorbed) return fail(MSQD_EINVAL, "NULL device pointer");
     if (!aligned16(ws) || !aligned16(psi)) return fail(MSQD_EINVAL, "misaligned device pointer");
     MolArgs a = make_mol_args(d, ws);
-    a.n_steps = 0;
     a.psi = const_cast<void*>(psi);
-    a.E_mol = nullptr;   // no step: the kernels read no field
     a.absorbed = const_cast<double*>(absorbed);
     a.d_mol = d_mol;
     a.norm_mol = norm_mol;

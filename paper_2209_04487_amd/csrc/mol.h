@@ -44,7 +44,7 @@ QdLayout qd_layout(int n_r, int nj);
 struct MolArgs {
   int n_mol;
   int nj;
-  int n_steps;          // 0 ((j, m) kernels): readouts only, state untouched
+  int n_steps;          // at least 1 in the step kernels; the readouts do not look at it
   int kdiss;            // first radial index with r > r_diss
   int kmask;            // first radial index where the absorber mask is below one
   int want_d, want_norm, want_yield;

@@ -410,9 +410,10 @@ void mol_jmg_kernel(MolArgs a) {
   if constexpr (stage_tables<NR, T>()) stage_tables_to_lds<NR, T, true, S::W>(kin_s, tw_s, mask_s, kin_g, tw_g, mask_g);
   // The wavepacket's loads: ahead of the coupling tables' arithmetic, which other
   // workgroups' loads would otherwise wait behind; after it for the complex64 forms
-  // of one exchange round, which have a CU or nearly so to themselves (6.00 ms
-  // instead of 6.41 for 30,000 molecules at n_r = 256, j_max = 5; 1.84 instead of
-  // 2.02 the other way round at j_max = 3).
+  // of one exchange round (ms, after / ahead: n_r = 256, j_max = 3, 30,000 molecules 1.72 /
+  // 1.86; n_r = 64, j_max = 2, 60,000 0.62 / 0.71, j_max = 5, 20,000 1.39 / 1.41; n_r =
+  // 128, j_max = 5, 20,000 2.12 / 2.15; n_r = 256, j_max = 4 and 5, 30,000 within 2%:
+  // 3.75 / 3.69, 5.65 / 5.61).
   constexpr bool LATE = sizeof(T) == 4 && SP == 1;
   if constexpr (!LATE) {
 #pragma unroll
