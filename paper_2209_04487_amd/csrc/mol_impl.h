@@ -868,12 +868,14 @@ enum { kCpExact = 0, kCpBf16x3 = 1, kCpExactHalf = 2, kCpExact3 = 3 };
 template <typename T, int NR, bool PARTS, int W>
 struct MolOcc {
   static constexpr int waves = sizeof(T) == 8 ? (PARTS && NR < 512 ? 3 : 2) : (NR <= 128 || W > 1 ? 4 : 3);
-  // The mixed form, and complex64 up to n_r = 128, are told that more will not do
+  // The mixed form, and complex64 at n_r = 128, are told that more will not do
   // either: their loads are then issued further ahead (mixed, 50,000 molecules, n_r =
   // 256, N_J = 11: 1615 -> 1591 us; n_r = 128, N_J = 7, 20,000: 261 -> 250; FP32, n_r =
-  // 128, N_J = 7, 20,000: 237.8 -> 235.6, N_J = 11: 428 -> 425).  The others measured
-  // the same within 1 to 3%.
-  static constexpr int most(int cp) { return cp == kCpBf16x3 || (sizeof(T) == 4 && NR <= 128) ? waves : 8; }
+  // 128, N_J = 7, 20,000: 237.8 -> 235.6, N_J = 11: 428 -> 425).  The FP32 form at n_r =
+  // 64 does hold more (100,000 molecules, four at most / free: N_J = 1 287 / 262, 4 348 /
+  // 353, 8 599 / 557; the same within 1% from N_J = 9 on).  The others measured the same
+  // within 1 to 3%.
+  static constexpr int most(int cp) { return cp == kCpBf16x3 || (sizeof(T) == 4 && NR == 128) ? waves : 8; }
 };
 
 // raised wave priority over the contraction rounds (see the step loop)
