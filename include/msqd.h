@@ -154,9 +154,14 @@ int qd_jm_tables(int32_t j_max, double* out, size_t n_out);
  * [n_mol][3], the dipole <mu12 d_c sigma_x> along x, y, z; the coupling is
  * exp(i mu12 dt sigma_x (x) sum_c E_c D_c), exact on the truncated basis,
  * D_c the direction cosines of the molecular axis (Eq. (3) with all m):
- * a closed form for j_max = 1; for j_max >= 2 the rotation of the field
- * direction onto z, per-m' Gauss transforms of cos(theta), the 2x2 rotation
- * of each eigenvector's (g, e) pair and the way back. */
+ * a closed form for j_max = 1; for j_max >= 2 the rotation of the (g, e)
+ * parts of pairs of eigenvectors of the direction cosine along the field.
+ * The FP32 and mixed forms at n_r = 256 pick a kernel by the batch size, and
+ * the two round differently: with j_max >= 8 (m = 0) up to 512 molecules and
+ * beyond, in the (j, m) basis with j_max = 1 up to 2,048 and beyond.  Across
+ * these sizes a molecule's result may change in its last digits; otherwise,
+ * and in FP64 always, it does not depend on n_mol.  (adjoint_step likewise in
+ * FP32 at n_r = 128, around 512 and 1,024 molecules.) */
 int qd_step(const qd_desc* d, const void* ws, void* psi, const double* E_mol,
             double* absorbed, double* d_mol, int32_t n_steps, void* stream);
 
@@ -174,6 +179,7 @@ int qd_step(const qd_desc* d, const void* ws, void* psi, const double* E_mol,
  *             order (blocks of 1024 consecutive molecules, then the block
  *             partials), bit-reproducible for a given n_mol; or NULL.  The
  *             stage-one partials use the tail of ws (qd_workspace_bytes).
+ * A molecule's own values do not depend on the batch it is in.
  * Per-molecule outputs may be NULL when sums is NULL; sums needs all three
  * (it reduces them): MSQD_EINVAL otherwise.  With n_mol = 0 only sums is
  * written (zeros).  The state is not modified. */

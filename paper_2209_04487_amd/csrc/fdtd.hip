@@ -52,7 +52,8 @@ __device__ __forceinline__ const T* prof(const FdArgs& a, size_t off_d, size_t o
 // update then takes the planes in descending order, so that it begins with the
 // planes that the H update before it finished with, and the next H update with
 // the E update's last ones.  H + E pair in us, dispatch order / strips / strips
-// and E descending:
+// and E descending (replays of a captured graph, all builds on the same buffers; a
+// metal film of three planes, six CPML planes):
 //   FP32 64x64x80 (16 runs) 7.59 / 7.45 / 7.53, 64x64x160 10.9 / 10.7 / 10.7,
 //   61x83x97 (20) 14.0 / 11.0 / 10.9, 80x80x80 (25) 12.7 / 11.1 / 11.1,
 //   96x96x80 (36) 13.8 / 12.4 / 12.5, 128x96x80 (48) 14.4 / 13.9 / 14.1,

@@ -70,3 +70,24 @@ def test_large_batch_norm_does_not_drift(prec):
         worst = max(worst, float(np.abs(tot - 1.0).max()))
     print(f"max |norm + absorbed - 1| = {worst:.3e}")
     assert worst < 5e-5
+
+
+@pytest.mark.parametrize("prec, basis, n_r, j_max", [("fp64", "m0", 64, 9), ("fp64", "m0", 256, 4), ("fp64", "m0", 256, 10),
+                                                     ("fp64", "jm", 256, 1), ("fp64", "jm", 128, 2), ("fp32", "m0", 256, 7),
+                                                     ("mixed", "m0", 128, 8), ("fp32", "jm", 256, 4), ("fp32", "jm", 128, 1)])
+def test_step_does_not_depend_on_the_batch(prec, basis, n_r, j_max):
+    """Sizes whose kernel is not picked by the batch: nine molecules give the same bits alone
+    and repeated in a batch past every limit (2,051 molecules)."""
+    from paper_2209_04487_amd import msqd
+    banner(f"step {prec} {basis} n_r={n_r} j_max={j_max} in two batches")
+    few, out = 9, []
+    psi = torch.as_tensor(random_state(j_max, few, (j_max + 1) ** (2 if basis == "jm" else 1), n_r, 11.0 / n_r)).cuda()
+    E = torch.linspace(-0.05, 0.05, 3 * few, dtype=torch.float64, device="cuda").reshape(few, 3)
+    for n in (few, 2051):
+        m = msqd.Molecules.from_config(get_config("cfg0", n_r=n_r, j_max=j_max, basis=basis, n_mol=n), prec=prec)
+        at = torch.arange(n, device="cuda") % few
+        m.psi.copy_(psi.to(m.psi.dtype)[at])
+        m.step((E if basis == "jm" else E[:, 0].contiguous())[at].contiguous(), n_steps=1)
+        out.append((m.psi, m.d, m.absorbed))
+    for a, b in zip(*out):
+        assert torch.equal(a[at], b)
